@@ -237,6 +237,18 @@ pb_status autotune_impl(const Layout& L, const SolveBufs<T>& s, const SolveWs& w
             best_t = t;
         }
     }
+    // the resident form of the same solve, where the grid fits it
+    Tiling rt = best_t;
+    rt.resident = 1;
+    if (resident_fits<T>(L, 0)) {
+        double us = 0.0;
+        pb_status e = time_tiling<T>(L, s, w, rt, iters, st, us);
+        if (e != PB_OK) return e;
+        if (us < best_us) {
+            best_us = us;
+            best_t = rt;
+        }
+    }
     record_tiling<T>(L, best_t);
     if (best) {
         best->block = best_t.bs;

@@ -41,6 +41,7 @@
 // cache lines, and after the barrier every workgroup sums all tile slots in
 // the same fixed order and derives alpha, beta and the stopping test itself.
 // Results do not depend on the number of workgroups or on scheduling.
+#include "jpcg_device.hpp"
 #include "solver.hpp"
 
 #include <algorithm>
@@ -86,52 +87,6 @@ struct KArgs {
     const float* ctab;   // and the dictionary (kCodedTableSize values)
     const int* fit;      // runtime-checked coded launches: 1 when this problem's dictionary holds its operator
 };
-
-__device__ __forceinline__ double ld_agent_d(const double* p) {
-    unsigned long long v = __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-    return __longlong_as_double((long long)v);
-}
-__device__ __forceinline__ int ld_agent_i(const int* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Workgroup barrier for the LDS hand-off between planes.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
-// Cross-lane moves of a double through DPP (two 32-bit halves).
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double v) {
-    const long long u = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xF, 0xF, false);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-__device__ __forceinline__ double readlane_d(double v, int lane) {
-    const long long u = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)u, lane);
-    const int hi = __builtin_amdgcn_readlane((int)(u >> 32), lane);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-constexpr int kDppXor1 = 0xB1;         // quad permute [1,0,3,2]
-constexpr int kDppXor2 = 0x4E;         // quad permute [2,3,0,1]
-constexpr int kDppHalfMirror = 0x141;  // lane i of 8 reads lane 7-i
-constexpr int kDppMirror = 0x140;      // lane i of 16 reads lane 15-i
-constexpr int kDppRor8 = 0x128;        // lane i of 16 reads lane (i+8) mod 16
-
-// Sum over the 64 lanes of a wave (every lane active) in a fixed order: a
-// butterfly inside each 16-lane row, then (row0 + row1) + (row2 + row3).
-__device__ __forceinline__ double wave_sum(double v) {
-    v += dpp_d<kDppXor1>(v);
-    v += dpp_d<kDppXor2>(v);
-    v += dpp_d<kDppHalfMirror>(v);
-    v += dpp_d<kDppMirror>(v);
-    return (readlane_d(v, 0) + readlane_d(v, 16)) + (readlane_d(v, 32) + readlane_d(v, 48));
-}
 
 // LDS scratch of the reductions below, in doubles.
 template <int BS>
@@ -288,14 +243,6 @@ __device__ __forceinline__ void sstore(T* p, const typename Vec<T>::type& v) {
     if constexpr (NT) vstore_nt(p, v);
     else vstore(p, v);
 }
-// Jacobi scaling 1/d: the hardware reciprocal in FP32 (about 1 ulp), an
-// exact division in FP64. Every use of M^-1 in a solve goes through this one
-// function, so the preconditioner is the same fixed positive diagonal in the
-// direction update and in the dot products.
-__device__ __forceinline__ float jacobi_inv(float d) { return __builtin_amdgcn_rcpf(d); }
-__device__ __forceinline__ uint32_t bits(float f) { return __float_as_uint(f); }
-__device__ __forceinline__ double jacobi_inv(double d) { return 1.0 / d; }
-
 template <typename T>
 __device__ __forceinline__ typename Vec<T>::type vzero() {
     typename Vec<T>::type v;
@@ -822,25 +769,6 @@ __device__ void pass_tile(const KArgs<T>& a, int tile, int o, int n, T alpha, T 
 }
 
 // Final update x += alpha p (or x = 0 for a zero right-hand side).
-// (A v) at one node: d v minus the six couplings times the neighbour values,
-// summed in one fixed order (x, then y, then z). Every evaluation of the
-// operator in the 40-byte pass goes through this function, so a node's value
-// recomputed in a tile's halo is the one its own tile computes.
-// (A v)_n at one node. The rounding is fixed by explicit fused multiply-adds
-// (no compiler contraction), so every kernel variant computes the same value.
-template <typename T>
-__device__ __forceinline__ T apply_point(T d, T v, T cr, T vr, T cl, T vl, T cu, T vu, T cd, T vd, T ca, T va, T cb,
-                                         T vb) {
-#pragma clang fp contract(off)
-    T nb = cr * vr;
-    nb = fma(cl, vl, nb);
-    nb = fma(cu, vu, nb);
-    nb = fma(cd, vd, nb);
-    nb = fma(ca, va, nb);
-    nb = fma(cb, vb, nb);
-    return fma(d, v, -nb);
-}
-
 // ---- periodic boundary in the ghost-row layout (40-byte pass)
 //
 // Each plane holds two ghost rows below row 0 (copies of rows ny-2, ny-1) and
@@ -2089,6 +2017,17 @@ void record_tiling(const Layout& L, const Tiling& t) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     g_tuned[tune_key<T>(L)] = t;
 }
+
+// Whether a solve of this shape runs the streaming form although the resident
+// one may take it: a tiling recorded by the caller, an autotuner's verdict, or a
+// periodic pass form.
+template <typename T>
+bool streaming_asked(const Layout& L, int periodic) {
+    if (periodic && periodic_pass() >= 0) return true;
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    const auto it = g_tuned.find(tune_key<T>(L));
+    return it != g_tuned.end() && !it->second.resident;
+}
 template void record_tiling<float>(const Layout&, const Tiling&);
 template void record_tiling<double>(const Layout&, const Tiling&);
 
@@ -2232,6 +2171,11 @@ unsigned copy_grid(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 2
 template <typename T>
 pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, double* partials, double tol,
                      int maxiter, hipStream_t st, SolveResult* res, const Tiling* force, int periodic) {
+    if (force ? force->resident != 0 : !streaming_asked<T>(L, periodic)) {
+        bool ran = false;
+        const pb_status e = resident_jpcg<T>(L, s, sync, partials, tol, maxiter, st, res, periodic, ran);
+        if (e != PB_OK || ran) return e;
+    }
     const Tiling t = !periodic && force && force->grid > 0 ? *force : solve_tiling<T>(L, periodic);
     if (t.grid <= 0) {
         set_error("fused JPCG: no feasible tiling for this grid (nx too large for the in-plane halo)");

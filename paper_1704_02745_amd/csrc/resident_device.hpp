@@ -1,0 +1,532 @@
+// The resident Jacobi-CG: a persistent kernel for grids whose whole iteration
+// state fits the registers and LDS of the device.
+//
+// Each workgroup owns a brick: a tile of columns (one per thread) times NZ
+// planes. A thread keeps r, x, q = A p and the operator of its NZ nodes in
+// registers; p of the brick sits in LDS with a halo of one node around the tile.
+// Between iterations nothing of the state touches memory except the q of the
+// nodes on the brick's faces, which the neighbours need.
+//
+// The iteration is that of the streaming form (one grid barrier per
+// iteration, r.z and ||r||^2 of the next step from the expansion of this step's
+// sums; see the comment at the head of jpcg.hip). It lets the halo travel one
+// barrier behind: pass l needs p_{l-1} = r_{l-1}/d + beta p_{l-2} on the halo,
+// with r_{l-1} = r_{l-2} - alpha q_{l-1}. A brick keeps r, 1/d and p of its halo
+// nodes itself, so it reads only q_{l-1} there, which the owner published before
+// the barrier that gave alpha and beta: the exchange needs no second barrier.
+// The halo's values are computed by the owner's own operations, so they are
+// bitwise the owner's.
+//
+// Barrier: every workgroup stores its sums into its own slot as 8-byte words
+// (half of a double, barrier tag), and every workgroup polls all slots until
+// the tags match, then adds them in one fixed order. A word carries its own
+// tag, so there is no arrival counter, no second round trip for the data and no
+// order to keep between words. The face values of q, stored before, are waited
+// for (vmcnt) before the slot is written. All cross-workgroup accesses go past
+// the L2 of the XCD (agent scope).
+#pragma once
+
+#include "jpcg_device.hpp"
+#include "solver.hpp"
+
+namespace pb {
+namespace {
+
+template <typename T>
+struct RArgs {
+    Op<T> op;
+    const T* b;
+    const T* r0;          // initial residual: b, or b - A x0 with a warm start
+    T* x;
+    T* faces[2];          // published q by pass parity: per workgroup x-, x+, y-, y+, z-, z+ (face_len elements)
+    int nx, ny, nz;
+    int64_t sp;
+    int tx, ty;           // largest tile (columns per workgroup: tx * ty <= block)
+    int nxt, nyt, nzc;    // bricks per axis
+    double tol;
+    int maxiter;
+    int warm;
+    SyncState* S;
+    unsigned long long* slots;   // 2 x workgroups x kSlotWords, cleared before the launch
+    long long timeout_ticks;
+};
+
+constexpr int kSlotWords = 16;            // two words per sum (low half, high half), 8 sums
+constexpr int kMaxResidentGroups = 256;   // workgroups that the poll of one barrier covers
+
+// The value, unknown to the optimizer: keeps what is derived from it (1/d,
+// offsets) from being hoisted out of the iteration into registers of its own.
+__device__ __forceinline__ int opaque_v(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ int opaque_s(int v) {   // v uniform over the wave
+    asm volatile("" : "+s"(v));
+    return v;
+}
+__device__ __forceinline__ uint32_t opaque_v(uint32_t v) { return (uint32_t)opaque_v((int)v); }
+__device__ __forceinline__ float opaque_v(float v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ double opaque_v(double v) { return v; }
+
+constexpr int kDppRor4 = 0x124;   // lane i of 16 reads a lane 4 away (cyclic)
+
+// Sums of eight values over each row of 16 lanes by exchange: afterwards lane
+// l holds the row's sum of value l & 7. Fixed order; every lane active.
+__device__ __forceinline__ double row_sum8(const double (&v)[8]) {
+    const int lane = threadIdx.x & 63;
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
+    double w[4], u[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const double keep = b0 ? v[2 * j + 1] : v[2 * j], send = b0 ? v[2 * j] : v[2 * j + 1];
+        w[j] = keep + dpp_d<kDppXor1>(send);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const double keep = b1 ? w[2 * j + 1] : w[2 * j], send = b1 ? w[2 * j] : w[2 * j + 1];
+        u[j] = keep + dpp_d<kDppXor2>(send);
+    }
+    const double keep = b2 ? u[1] : u[0], send = b2 ? u[0] : u[1];
+    const double t = keep + dpp_d<kDppRor4>(send);
+    return t + dpp_d<kDppRor8>(t);
+}
+// Sum of `rows` partial rows of eight values in LDS (a multiple of 8), made by
+// every wave for itself: lane l returns the total of value l & 7.
+__device__ __forceinline__ double lds_rows_sum8(const double* red, int rows) {
+    const int lane = threadIdx.x & 63;
+    double t = 0.0;
+    for (int g = lane >> 3; g < rows; g += 8) t += red[g * 8 + (lane & 7)];
+    t += dpp_d<kDppRor8>(t);
+    t += __shfl_xor(t, 16);
+    t += __shfl_xor(t, 32);
+    return t;
+}
+
+using Rsrc = __amdgpu_buffer_rsrc_t;
+constexpr int kRawWord3 = 0x00020000;       // raw (unformatted, unswizzled) buffer
+constexpr int kAgentScope = 16;             // sc1: past the XCD's L2
+constexpr uint32_t kNowhere = 0x80000000u;  // past the end of every resource: loads return 0, stores are dropped
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+template <typename T>
+__device__ __forceinline__ Rsrc rsrc_of(const T* base, int64_t elems) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, (int)(elems * (int64_t)sizeof(T)), kRawWord3);
+}
+template <int AUX>
+__device__ __forceinline__ float bload(Rsrc r, uint32_t off, float) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, AUX));
+}
+template <int AUX>
+__device__ __forceinline__ double bload(Rsrc r, uint32_t off, double) {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, AUX));
+}
+__device__ __forceinline__ void agent_store(Rsrc r, uint32_t off, float v) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, (int)off, 0, kAgentScope);
+}
+__device__ __forceinline__ void agent_store(Rsrc r, uint32_t off, double v) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, kAgentScope);
+}
+
+// Published face values of one workgroup, in elements: two x-faces of ty * NZ,
+// two y-faces of tx * NZ, two z-faces of one value per thread.
+__host__ __device__ constexpr int face_len(int bs, int nzb, int tx, int ty) { return 2 * (tx + ty) * nzb + 2 * bs; }
+
+// One in-plane halo node: its r and 1/d, where its q is published (byte offset
+// in the faces) and the LDS element of its p.
+template <typename T>
+struct HaloNode {
+    T r, inv;
+    uint32_t from;
+    int p;
+};
+
+// LDS of one workgroup, in bytes: the reduction scratch, p by columns (the NZ
+// values of a column together, at an odd stride, so that a lane's accesses
+// are one address plus constants and the lanes fall into different banks) over
+// the tile and its halo, and the halo nodes.
+// Whether the couplings to the lower x and y neighbours sit in LDS (each thread
+// its own) instead of registers: from 17 planes of FP32 or 9 of FP64 on the
+// rest of the state fills the 256 registers of a thread and they would spill
+// (129^3, 19 planes: 13.1 us per iteration with the spills, 7.5 without).
+template <typename T>
+__host__ __device__ constexpr bool lower_in_lds(int bs, int nzb) { return nzb > (sizeof(T) == 4 ? 16 : 8); }
+template <typename T>
+__host__ __device__ constexpr size_t resident_lds_bytes(int bs, int nzb, int tx, int ty) {
+    return (lower_in_lds<T>(bs, nzb) ? sizeof(T) * 2 * (size_t)bs * nzb : 0) + sizeof(double) * (size_t)(bs / 64) * 4 * 8 * 2 + 256 +
+           (sizeof(T) * (size_t)(nzb | 1) * (tx + 2) * (ty + 2) + 15) / 16 * 16 +
+           sizeof(HaloNode<T>) * (size_t)nzb * 2 * (tx + ty);
+}
+
+// The whole solve of one problem by workgroup `w` of its nxt * nyt * nzc.
+template <typename T, int BS, int NZ, bool PER>
+__device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_raw) {
+#pragma clang fp contract(off)
+    constexpr int ROWS = BS / 64 * 4;
+    constexpr int E = (int)sizeof(T);
+    // 1/d kept beside d where the registers allow
+    constexpr bool LL = lower_in_lds<T>(BS, NZ);
+    constexpr bool KEEP = E == 8 || NZ <= (LL ? 17 : 12);
+    constexpr int SZ = NZ | 1;   // LDS stride of a column
+    const int G = a.nxt * a.nyt * a.nzc;
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const int64_t sp = a.sp;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // the brick: columns [x0, x1) x [y0, y1), planes [k0, k0 + nk)
+    const int bx = w % a.nxt, by = w / a.nxt % a.nyt, bz = w / (a.nxt * a.nyt);
+    const int x0 = (int)((int64_t)bx * nx / a.nxt), x1 = (int)((int64_t)(bx + 1) * nx / a.nxt);
+    const int y0 = (int)((int64_t)by * ny / a.nyt), y1 = (int)((int64_t)(by + 1) * ny / a.nyt);
+    const int k0 = bz * NZ, nk = min(NZ, nz - k0);
+    const int wx = x1 - x0, wy = y1 - y0, row = a.tx + 2;
+    const int cxx = tid % a.tx, cyy = tid / a.tx;
+    const bool valid = cxx < wx && cyy < wy;
+    const int i = x0 + cxx, j = y0 + cyy, pos = j * nx + i;
+
+    double* red = reinterpret_cast<double*>(lds_raw);
+    double* red2 = red + ROWS * 8;
+    int* s_flag = reinterpret_cast<int*>(red2 + ROWS * 8);
+    T* P = reinterpret_cast<T*>(lds_raw + sizeof(double) * ROWS * 16 + 256);
+    HaloNode<T>* HN = reinterpret_cast<HaloNode<T>*>(
+        lds_raw + sizeof(double) * ROWS * 16 + 256 + (sizeof(T) * (size_t)SZ * row * (a.ty + 2) + 15) / 16 * 16);
+
+    T* const CL = reinterpret_cast<T*>(HN + (size_t)NZ * 2 * (a.tx + a.ty)) + tid;   // LL: x and y of plane kk at 2kk, 2kk+1
+
+    // p of this thread's column and of the four around it. With one brick
+    // along a periodic axis the neighbour across the end is in the tile itself.
+    // Threads without a column share the halo's corner, which stays zero.
+    const bool wrap_x = PER && a.nxt == 1, wrap_y = PER && a.nyt == 1;
+    T* const pl = P + SZ * (valid ? (cyy + 1) * row + cxx + 1 : 0);
+    const T* const pR = !valid ? pl : wrap_x && i == nx - 1 ? pl - SZ * (nx - 1) : pl + SZ;
+    const T* const pL = !valid ? pl : wrap_x && i == 0 ? pl + SZ * (nx - 1) : pl - SZ;
+    const T* const pU = !valid ? pl : wrap_y && j == ny - 1 ? pl - SZ * row * (ny - 1) : pl + SZ * row;
+    const T* const pD = !valid ? pl : wrap_y && j == 0 ? pl + SZ * row * (ny - 1) : pl - SZ * row;
+
+    // ---- the operator and the state of the own nodes
+    T r[NZ], x[NZ], q[NZ], cx[NZ], cy[NZ], cz[NZ], d[NZ], iv[KEEP ? NZ : 1];
+    T cxm[LL ? 1 : NZ], cym[LL ? 1 : NZ];
+    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    {
+        // positions without a node and planes past nk read as zero
+        auto from = [&](const T* p) { return rsrc_of(p + (int64_t)k0 * sp, (int64_t)nk * sp); };
+        const Rsrc rcx = from(a.op.cx), rcy = from(a.op.cy), rcz = from(a.op.cz), rd = from(a.op.d), rr0 = from(a.r0),
+                   rb0 = from(a.b), rx = from(a.x);
+        auto at = [&](bool in, int p) { return valid && in ? (uint32_t)p * E : kNowhere; };
+        uint32_t o = at(true, pos), ox = at(i > 0 || PER, i > 0 ? pos - 1 : pos + nx - 1),
+                 oy = at(j > 0 || PER, j > 0 ? pos - nx : pos + (ny - 1) * nx);
+        const uint32_t plane_bytes = (uint32_t)(sp * E);
+#pragma unroll
+        for (int kk = 0; kk < NZ; ++kk) {
+            cx[kk] = bload<0>(rcx, o, T());
+            cy[kk] = bload<0>(rcy, o, T());
+            cz[kk] = bload<0>(rcz, o, T());
+            d[kk] = bload<0>(rd, o, T());
+            const T cxl = bload<0>(rcx, ox, T()), cyl = bload<0>(rcy, oy, T());
+            if constexpr (LL) {
+                CL[2 * kk * BS] = cxl;
+                CL[(2 * kk + 1) * BS] = cyl;
+            } else {
+                cxm[kk] = cxl;
+                cym[kk] = cyl;
+            }
+            r[kk] = bload<0>(rr0, o, T());
+            x[kk] = bload<0>(rx, a.warm ? o : kNowhere, T());
+            q[kk] = T(0);
+            const T bv = bload<0>(rb0, o, T());
+            if (d[kk] == T(0)) d[kk] = T(1);
+            acc[0] = fma((double)r[kk], (double)r[kk], acc[0]);
+            acc[1] = fma((double)bv, (double)bv, acc[1]);
+            if constexpr (KEEP) iv[kk] = jacobi_inv(d[kk]);
+            o += plane_bytes;
+            ox += plane_bytes;
+            oy += plane_bytes;
+        }
+    }
+    auto inv = [&](int kk) -> T {
+        if constexpr (KEEP) return iv[kk];
+        else return jacobi_inv(opaque_v(d[kk]));
+    };
+    // planes below and above the brick, in this thread's column
+    const bool has_b = PER || bz > 0, has_t = PER || bz + 1 < a.nzc;
+    const int kb = k0 > 0 ? k0 - 1 : nz - 1, kt = k0 + nk < nz ? k0 + nk : 0;
+    T czb = T(0), rb = T(0), ib = T(0), pb_ = T(0), rt = T(0), it_ = T(0), pt = T(0);
+    if (valid && has_b) {
+        const int64_t g = (int64_t)kb * sp + pos;
+        czb = a.op.cz[g];
+        rb = a.r0[g];
+        ib = jacobi_inv(a.op.d[g]);
+    }
+    if (valid && has_t) {
+        const int64_t g = (int64_t)kt * sp + pos;
+        rt = a.r0[g];
+        it_ = jacobi_inv(a.op.d[g]);
+    }
+    // ---- where the faces of this brick are published and the halo's are read
+    // (byte offsets); kNowhere where no neighbour reads or is
+    const int FX = a.ty * NZ, FY = a.tx * NZ;
+    const uint32_t face_bytes = (uint32_t)face_len(BS, NZ, a.tx, a.ty) * E;
+    auto brick = [&](int ux, int uy, int uz) -> uint32_t {   // wrapped coordinates
+        ux = ux < 0 ? ux + a.nxt : (ux >= a.nxt ? ux - a.nxt : ux);
+        uy = uy < 0 ? uy + a.nyt : (uy >= a.nyt ? uy - a.nyt : uy);
+        uz = uz < 0 ? uz + a.nzc : (uz >= a.nzc ? uz - a.nzc : uz);
+        return (uint32_t)((uz * a.nyt + uy) * a.nxt + ux) * face_bytes;
+    };
+    const uint32_t mine = (uint32_t)w * face_bytes;
+    const bool face_x = a.nxt > 1, face_y = a.nyt > 1;
+    const uint32_t pub_x = !valid || !face_x ? kNowhere
+                           : cxx == 0        ? mine + (uint32_t)cyy * E
+                           : cxx == wx - 1   ? mine + (uint32_t)(FX + cyy) * E
+                                             : kNowhere;
+    const uint32_t pub_y = !valid || !face_y ? kNowhere
+                           : cyy == 0        ? mine + (uint32_t)(2 * FX + cxx) * E
+                           : cyy == wy - 1   ? mine + (uint32_t)(2 * FX + FY + cxx) * E
+                                             : kNowhere;
+    const uint32_t zlo = (uint32_t)(2 * FX + 2 * FY + tid) * E, zhi = zlo + (uint32_t)BS * E;
+    const bool face_z = PER || a.nzc > 1;
+    const uint32_t pub_zlo = valid && face_z ? mine + zlo : kNowhere, pub_zhi = valid && face_z ? mine + zhi : kNowhere;
+    const uint32_t off_b = valid && has_b ? brick(bx, by, bz - 1) + zhi : kNowhere;
+    const uint32_t off_t = valid && has_t ? brick(bx, by, bz + 1) + zlo : kNowhere;
+    const int64_t face_elems = (int64_t)G * face_len(BS, NZ, a.tx, a.ty);
+    // in-plane halo nodes, in the order of the faces they are read from
+    const int hx = face_x ? 2 * FX : 0, hn = hx + (face_y ? 2 * FY : 0);
+    for (int h = tid; h < SZ * row * (a.ty + 2); h += BS) P[h] = T(0);
+    for (int h = tid; h < hn; h += BS) {
+        HaloNode<T> n{T(0), T(0), kNowhere, 0};
+        const bool alongx = h < hx;
+        const int F = alongx ? FX : FY, g = alongx ? h : h - hx, hi = g >= F ? 1 : 0, l = g - hi * F;
+        const int stride = alongx ? a.ty : a.tx, kk = l / stride, c = l - kk * stride;
+        int hi_i, hi_j, col;
+        uint32_t there;
+        bool in;
+        if (alongx) {
+            in = c < wy && (PER || (hi ? x1 < nx : x0 > 0));
+            hi_i = hi ? (x1 < nx ? x1 : 0) : (x0 > 0 ? x0 - 1 : nx - 1);
+            hi_j = y0 + c;
+            col = (c + 1) * row + (hi ? wx + 1 : 0);
+            there = brick(bx + (hi ? 1 : -1), by, bz) + (uint32_t)((hi ? 0 : FX) + l) * E;
+        } else {
+            in = c < wx && (PER || (hi ? y1 < ny : y0 > 0));
+            hi_j = hi ? (y1 < ny ? y1 : 0) : (y0 > 0 ? y0 - 1 : ny - 1);
+            hi_i = x0 + c;
+            col = (hi ? wy + 1 : 0) * row + c + 1;
+            there = brick(bx, by + (hi ? 1 : -1), bz) + (uint32_t)(2 * FX + (hi ? 0 : FY) + l) * E;
+        }
+        n.p = SZ * col + kk;
+        if (in && kk < nk) {
+            const int64_t g0 = (int64_t)(k0 + kk) * sp + (int64_t)hi_j * nx + hi_i;
+            n.r = a.r0[g0];
+            n.inv = jacobi_inv(a.op.d[g0]);
+            n.from = there;
+        } else {
+            n.p = kk;   // a corner column, whose p stays zero (1/d = 0)
+        }
+        HN[h] = n;
+    }
+
+    // ---- grid barrier with the reduction of the sums in acc; the totals in
+    // every thread
+    int b = 0;
+    auto reduce = [&](double (&out)[8]) -> bool {
+        const double t = row_sum8(acc);
+        if ((lane & 15) < 8) red[(wave * 4 + (lane >> 4)) * 8 + (lane & 7)] = t;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's face values have arrived
+        __syncthreads();
+        const unsigned tag = (unsigned)(b + 1);
+        unsigned long long* slots = a.slots + (size_t)(b & 1) * G * kSlotWords;
+        if (wave == 0) {
+            const double v = lds_rows_sum8(red, ROWS);
+            if (lane < 8) {
+                const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+                unsigned long long* m = slots + (size_t)w * kSlotWords + 2 * lane;
+                __hip_atomic_store(m, (u << 32) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(m + 1, (u & 0xffffffff00000000ull) | tag, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        // thread n polls the sum n & 7 of slots n/8, n/8 + BS/8, ...
+        constexpr int M = (kMaxResidentGroups * 8 + BS - 1) / BS;
+        double part = 0.0;
+        if (opaque_v(tid >> 3) < G) {
+            unsigned long long lo[M], hi[M];
+            long long t0 = 0;
+            while (true) {
+                unsigned bad = 0;
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    if (m > 0 && m * (BS / 8) >= G) break;   // uniform
+                    const int slot = min((tid >> 3) + m * (BS / 8), G - 1);
+                    const unsigned long long* p = slots + (size_t)slot * kSlotWords + 2 * (tid & 7);
+                    lo[m] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    hi[m] = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    if (m > 0 && m * (BS / 8) >= G) break;
+                    bad |= ((unsigned)lo[m] ^ tag) | ((unsigned)hi[m] ^ tag);
+                }
+                if (bad == 0) break;
+                const long long now = wall_clock64();
+                if (t0 == 0) t0 = now;
+                if (now - t0 > a.timeout_ticks) {
+                    s_flag[0] = 1;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+                if ((tid >> 3) + m * (BS / 8) < G)
+                    part += __longlong_as_double((long long)((hi[m] & 0xffffffff00000000ull) | (lo[m] >> 32)));
+        }
+        asm volatile("" ::: "memory");
+        part += dpp_d<kDppRor8>(part);
+        if ((lane & 15) < 8) red2[(wave * 4 + (lane >> 4)) * 8 + (lane & 7)] = part;
+        __syncthreads();
+        const double tot = lds_rows_sum8(red2, ROWS);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) out[k] = readlane_d(tot, k);
+        ++b;
+        return s_flag[0] == 0;
+    };
+    auto timed_out = [&] {
+        if (tid == 0) __hip_atomic_store(&a.S->status, (int)PB_ERR_TIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+
+    if (tid == 0) s_flag[0] = 0;
+    __syncthreads();
+    double v[8];
+    if (!reduce(v)) return timed_out();
+    double alpha = 0.0, beta = 0.0, rr = v[0];
+    const double bb = v[1], sqrt_bb = sqrt(bb);
+    int done = 0, status = PB_OK, zero = 0, iters = 0;
+    if (!(bb - bb == 0.0) || !(rr - rr == 0.0)) { done = 1; status = PB_ERR_NONFINITE; }
+    else if (bb == 0.0) { done = 1; zero = 1; }
+    else if (sqrt(rr) / sqrt_bb < a.tol) { done = 1; }
+    else if (a.maxiter <= 0) { done = 1; status = PB_NOT_CONVERGED; }
+
+    for (int pass = 0; !done; ++pass) {
+        const T al = (T)alpha, be = (T)beta;
+        // ---- q of the halo, on its way while the own nodes are updated (the
+        // first pass has alpha = 0 and reads nothing)
+        const uint32_t none = pass > 0 ? 0u : kNowhere;
+        const Rsrc qo = rsrc_of((pass & 1) ? a.faces[0] : a.faces[1], face_elems);
+        const T qb = bload<kAgentScope>(qo, off_b | none, T());
+        const T qt = bload<kAgentScope>(qo, off_t | none, T());
+        constexpr int U = E == 4 ? 4 : 2;   // halo nodes in flight per thread
+        T qh[U];
+        auto fetch = [&](int h0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                qh[u] = bload<kAgentScope>(qo, (h0 + u * BS < hn ? HN[h0 + u * BS].from : kNowhere) | none, T());
+        };
+        fetch(tid);
+        // ---- r, p, x of the own nodes
+#pragma unroll
+        for (int kk = 0; kk < NZ; ++kk) {
+            const T po = pl[kk];
+            r[kk] = fma(-al, q[kk], r[kk]);
+            x[kk] = fma(al, po, x[kk]);
+            pl[kk] = fma(be, po, r[kk] * inv(kk));
+        }
+        // ---- r and p of the halo
+        for (int h0 = tid; h0 < hn;) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int h = h0 + u * BS;
+                if (h < hn) {
+                    const T rh = fma(-al, qh[u], HN[h].r);
+                    HN[h].r = rh;
+                    T* pp = P + HN[h].p;
+                    *pp = fma(be, *pp, rh * HN[h].inv);
+                }
+            }
+            h0 += U * BS;
+            if (h0 < hn) fetch(h0);
+        }
+        rb = fma(-al, qb, rb);
+        pb_ = fma(be, pb_, rb * ib);
+        rt = fma(-al, qt, rt);
+        pt = fma(be, pt, rt * it_);
+        __syncthreads();
+        // ---- q = A p and the sums
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[k] = 0.0;
+        const Rsrc qn = rsrc_of((pass & 1) ? a.faces[1] : a.faces[0], face_elems);
+        T pm = pb_, pc = pl[0];
+        uint32_t ox = opaque_v(pub_x), oy = opaque_v(pub_y);
+        const int nkv = opaque_s(nk);   // compared in place, not kept as NZ masks
+#pragma unroll
+        for (int kk = 0; kk < NZ; ++kk) {
+            const T up = kk + 1 < NZ ? pl[kk + 1 < NZ ? kk + 1 : 0] : T(0);
+            const T pu = kk + 1 == NZ || kk + 1 == nkv ? pt : up;
+            T cb = kk == 0 ? czb : cz[kk > 0 ? kk - 1 : 0];
+            if (PER && kk > 0) cb = kk < nkv ? cb : T(0);
+            const T cl = LL ? CL[2 * kk * BS] : cxm[LL ? 0 : kk], cd = LL ? CL[(2 * kk + 1) * BS] : cym[LL ? 0 : kk];
+            const T qq = apply_point(d[kk], pc, cx[kk], pR[kk], cl, pL[kk], cy[kk], pU[kk], cd, pD[kk], cz[kk], pu, cb, pm);
+            q[kk] = qq;
+            agent_store(qn, ox, qq);   // dropped at kNowhere
+            agent_store(qn, oy, qq);
+            if (kk == 0) agent_store(qn, pub_zlo, qq);
+            if (kk + 1 == nkv) agent_store(qn, pub_zhi, qq);
+            ox += (uint32_t)(a.ty * E);
+            oy += (uint32_t)(a.tx * E);
+            const T ivk = inv(kk);
+            const double pd = (double)pc, qd = (double)qq, rd = (double)r[kk];
+            const double zd = (double)(r[kk] * ivk), wd = (double)(qq * ivk);
+            acc[0] = fma(pd, qd, acc[0]);
+            acc[1] = fma(rd, zd, acc[1]);
+            acc[2] = fma(rd, wd, acc[2]);
+            acc[3] = fma(qd, wd, acc[3]);
+            acc[4] = fma(rd, rd, acc[4]);
+            acc[5] = fma(rd, qd, acc[5]);
+            acc[6] = fma(qd, qd, acc[6]);
+            pm = pc;
+            pc = up;
+        }
+        if (!reduce(v)) return timed_out();
+        const double pq = v[0], rrd = v[1], rqd = v[2], qqd = v[3];
+        if (!(pq > 0.0) || !(pq - pq == 0.0) || !(rrd > 0.0)) {
+            done = 1;
+            status = PB_ERR_BREAKDOWN;   // x holds the last good iterate
+        } else {
+            const double alp = rrd / pq;
+            const double rho = fmax(rrd - 2.0 * alp * rqd + alp * alp * qqd, 0.0);
+            rr = fmax(v[4] - 2.0 * alp * v[5] + alp * alp * v[6], 0.0);
+            ++iters;
+            alpha = alp;
+            beta = rho / rrd;
+            const double rel = sqrt(rr) / sqrt_bb;
+            if (!(rel - rel == 0.0)) { done = 1; status = PB_ERR_BREAKDOWN; }
+            else if (rel < a.tol) { done = 1; }
+            else if (iters >= a.maxiter) { done = 1; status = PB_NOT_CONVERGED; }
+            if (done && status != PB_ERR_BREAKDOWN) {
+                // last x update with the final alpha and direction
+#pragma unroll
+                for (int kk = 0; kk < NZ; ++kk) x[kk] = fma((T)alpha, pl[kk], x[kk]);
+            }
+        }
+    }
+    if (valid)
+#pragma unroll
+        for (int kk = 0; kk < NZ; ++kk)
+            if (kk < nk) a.x[(int64_t)(k0 + kk) * sp + pos] = zero ? T(0) : x[kk];
+    if (w == 0 && tid == 0) {
+        a.S->rr = rr;
+        a.S->bb = bb;
+        a.S->alpha = alpha;
+        a.S->beta = beta;
+        a.S->iters = iters;
+        a.S->done = done;
+        a.S->status = status;
+        a.S->zero_rhs = zero;
+    }
+}
+
+template <typename T, int BS, int NZ, bool PER>
+__global__ __launch_bounds__(BS) void k_jpcg_resident(RArgs<T> a) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    resident_problem<T, BS, NZ, PER>(a, blockIdx.x, lds_raw);
+}
+
+}  // namespace
+}  // namespace pb

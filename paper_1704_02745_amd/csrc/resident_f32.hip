@@ -1,0 +1,20 @@
+// The resident Jacobi-CG in FP32: kernel variants.
+#include "resident_impl.hpp"
+
+namespace pb {
+namespace {
+template <>
+const std::vector<ResVariant>& res_variants<float>() {
+    static const std::vector<ResVariant> v = {
+        PB_RES_VARIANT(float, 256, 2),  PB_RES_VARIANT(float, 256, 4),  PB_RES_VARIANT(float, 512, 4),
+        PB_RES_VARIANT(float, 512, 6),  PB_RES_VARIANT(float, 512, 8),  PB_RES_VARIANT(float, 512, 10),
+        PB_RES_VARIANT(float, 512, 12), PB_RES_VARIANT(float, 512, 14), PB_RES_VARIANT(float, 512, 16),
+        PB_RES_VARIANT(float, 512, 17), PB_RES_VARIANT(float, 512, 19), PB_RES_VARIANT(float, 512, 22),
+    };
+    return v;
+}
+}  // namespace
+template pb_status resident_jpcg<float>(const Layout&, const SolveBufs<float>&, SyncState*, double*, double, int,
+                                        hipStream_t, SolveResult*, int, bool&);
+template bool resident_fits<float>(const Layout&, int);
+}  // namespace pb

@@ -1,0 +1,18 @@
+// The resident Jacobi-CG in FP64: kernel variants.
+#include "resident_impl.hpp"
+
+namespace pb {
+namespace {
+template <>
+const std::vector<ResVariant>& res_variants<double>() {
+    static const std::vector<ResVariant> v = {
+        PB_RES_VARIANT(double, 256, 2), PB_RES_VARIANT(double, 256, 4), PB_RES_VARIANT(double, 512, 4),
+        PB_RES_VARIANT(double, 512, 6), PB_RES_VARIANT(double, 512, 8), PB_RES_VARIANT(double, 512, 10),
+    };
+    return v;
+}
+}  // namespace
+template pb_status resident_jpcg<double>(const Layout&, const SolveBufs<double>&, SyncState*, double*, double, int,
+                                         hipStream_t, SolveResult*, int, bool&);
+template bool resident_fits<double>(const Layout&, int);
+}  // namespace pb

@@ -39,6 +39,7 @@ struct Tiling {
     int nseg, nzc, ntiles;
     int halo;        // in-plane halo, >= nx, multiple of the vector width
     int grid;        // workgroups of the cooperative launch
+    int resident;    // 1: the resident form was the faster one for this shape (autotuner)
 };
 
 constexpr int kMaxTiles = 65536;
@@ -116,6 +117,15 @@ template <typename T>
 pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, double* partials,
                      double tol, int maxiter, hipStream_t st, SolveResult* res, const Tiling* force,
                      int periodic = 0);
+
+// resident_f32.hip, resident_f64.hip: the same solve with the whole iteration
+// state in registers and LDS. ran = false: the grid does not fit, nothing was
+// enqueued.
+template <typename T>
+pb_status resident_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, double* partials, double tol,
+                        int maxiter, hipStream_t st, SolveResult* res, int periodic, bool& ran);
+template <typename T>
+bool resident_fits(const Layout& L, int periodic);
 
 template <typename T>
 Tiling choose_tiling(const Layout& L);
