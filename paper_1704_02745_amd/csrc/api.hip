@@ -173,12 +173,14 @@ pb_status residual(const Layout& L, const SolveWs& w, int periodic, float* r32, 
 // the operator annihilates constants; b then has its mean removed here.
 pb_status prepare(const Layout& L, double h, const double* eps_x, const double* eps_y, const double* eps_z,
                   const double* kappa2, const double* rhs, const double* x, int warm, int periodic,
-                  const SolveWs& w, hipStream_t st, bool* singular) {
+                  const SolveWs& w, int prec, hipStream_t st, bool* singular) {
     int* flags = (int*)w.small;
     pb_status e = launch_fill<int>(flags, 1, 0, st);
     if (e != PB_OK) return e;
-    e = launch_prepare64(eps_x, eps_y, eps_z, kappa2, rhs, x, warm, periodic, L, h, w.op64, w.b64, w.x64, flags,
-                         st);
+    // the refinement's right-hand sides and iterates come later
+    float* b32 = prec == PB_F32 ? (float*)w.s32.b : nullptr;
+    e = launch_prepare64(eps_x, eps_y, eps_z, kappa2, rhs, x, warm, periodic, L, h, w.op64, w.b64, w.x64, flags, st,
+                         prec == PB_F64 ? nullptr : &w.s32.op, b32, prec == PB_F32 ? w.s32.x : nullptr);
     if (e != PB_OK) return e;
     int hflags = 0;
     PB_HIP(hipMemcpyAsync(&hflags, flags, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -193,7 +195,11 @@ pb_status prepare(const Layout& L, double h, const double* eps_x, const double* 
     }
     const bool sing = periodic && !(hflags & FLAG_HAS_SALT);
     if (singular) *singular = sing;
-    if (sing) return launch_remove_mean(w.b64, L, w.res64, w.small + 8, st);
+    if (sing) {
+        e = launch_remove_mean(w.b64, L, w.res64, w.small + 8, st);
+        if (e != PB_OK) return e;
+        if (b32) return launch_round32(w.b64, L.npad, b32, st);
+    }
     return PB_OK;
 }
 
@@ -315,7 +321,7 @@ pb_status solve_impl(int32_t nx, int32_t ny, int32_t nz, double h, const double*
     }
     hipStream_t st = (hipStream_t)stream_;
     bool singular = false;
-    pb_status e = prepare(L, h, eps_x, eps_y, eps_z, kappa2, rhs, x, opts->warm_start ? 1 : 0, per, w, st,
+    pb_status e = prepare(L, h, eps_x, eps_y, eps_z, kappa2, rhs, x, opts->warm_start ? 1 : 0, per, w, prec, st,
                           &singular);
     if (e != PB_OK) return e;
 
@@ -338,8 +344,6 @@ pb_status solve_impl(int32_t nx, int32_t ny, int32_t nz, double h, const double*
     } else if (prec == PB_F32) {
         SolveBufs<float> s = w.s32;
         s.warm = opts->warm_start ? 1 : 0;
-        e = launch_round32(w.op64, w.b64, w.x64, L.npad, s.op, (float*)s.b, s.x, st);
-        if (e != PB_OK) return e;
         e = run_inner<float>(L, s, w, op, per, opts->tol, maxiter, st, &r);
         if (e != PB_OK) return e;
         ++launches;
@@ -354,8 +358,6 @@ pb_status solve_impl(int32_t nx, int32_t ny, int32_t nz, double h, const double*
         // iterative refinement: FP64 residual, FP32 correction solve, FP64 update
         SolveBufs<float> s = w.s32;
         s.warm = 0;
-        e = launch_round32(w.op64, w.b64, w.x64, L.npad, s.op, nullptr, nullptr, st);
-        if (e != PB_OK) return e;
         const double inner_tol = opts->inner_tol > 0 ? opts->inner_tol : 1e-4;
         const int max_outer = opts->max_outer > 0 ? opts->max_outer : 20;
         double rr = 0, bb = 0, rr_prev = -1;
@@ -500,7 +502,8 @@ extern "C" pb_status pb_autotune(int32_t nx, int32_t ny, int32_t nz, double h, c
         return PB_ERR_NOMEM;
     }
     hipStream_t st = (hipStream_t)stream_;
-    pb_status e = prepare(L, h, eps_x, eps_y, eps_z, kappa2, rhs, nullptr, 0, 0, w, st, nullptr);
+    pb_status e = prepare(L, h, eps_x, eps_y, eps_z, kappa2, rhs, nullptr, 0, 0, w, opts->precision == PB_F64 ? PB_F64 : PB_F32, st,
+                        nullptr);
     if (e != PB_OK) return e;
     if (opts->precision == PB_F64) {
         SolveBufs<double> s = w.s64;
@@ -509,8 +512,6 @@ extern "C" pb_status pb_autotune(int32_t nx, int32_t ny, int32_t nz, double h, c
     }
     SolveBufs<float> s = w.s32;
     s.warm = 0;
-    e = launch_round32(w.op64, w.b64, w.x64, L.npad, s.op, (float*)s.b, s.x, st);
-    if (e != PB_OK) return e;
     return autotune_impl<float>(L, s, w, iters_per_trial, st, best);
 }
 

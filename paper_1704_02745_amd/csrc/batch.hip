@@ -142,14 +142,17 @@ std::vector<int> share_workgroups(const std::vector<Layout>& L, const std::vecto
 template <typename T>
 pb_status enqueue_prepare(const Plan<T>& P, const pb_problem* probs, hipStream_t st) {
     for (int i = 0; i < P.nprob; ++i) {
+        const Op<float>* op32 = nullptr;
+        float *b32 = nullptr, *x32 = nullptr;
+        if constexpr (sizeof(T) == sizeof(float)) {
+            op32 = &P.s[i].op;
+            b32 = (float*)P.s[i].b;
+            x32 = P.s[i].x;
+        }
         pb_status e = launch_prepare64(probs[i].eps_x, probs[i].eps_y, probs[i].eps_z, probs[i].kappa2, probs[i].rhs,
                                        probs[i].x, probs[i].warm_start ? 1 : 0, 0, P.L[i], probs[i].h, P.op64[i],
-                                       P.b64[i], P.x64[i], &P.rec[i].flags, st);
+                                       P.b64[i], P.x64[i], &P.rec[i].flags, st, op32, b32, x32);
         if (e != PB_OK) return e;
-        if constexpr (sizeof(T) == sizeof(float)) {
-            e = launch_round32(P.op64[i], P.b64[i], P.x64[i], P.L[i].npad, P.s[i].op, (float*)P.s[i].b, P.s[i].x, st);
-            if (e != PB_OK) return e;
-        }
     }
     return PB_OK;
 }

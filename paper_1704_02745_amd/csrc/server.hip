@@ -475,19 +475,16 @@ extern "C" pb_status pb_server_step(pb_server* S, int32_t chunk, void* stream, i
             PB_HIP(hipMemcpyAsync(&s.rec->setup_flags, s.sw.flags, sizeof(int), hipMemcpyDeviceToDevice, ad));
         }
         e = launch_prepare64(s.req.eps_x, s.req.eps_y, s.req.eps_z, s.req.kappa2, s.req.rhs, s.req.x,
-                             s.req.warm_start ? 1 : 0, 0, s.L, s.req.h, s.op64, s.b64, s.x64, &s.rec->flags, ad);
+                             s.req.warm_start ? 1 : 0, 0, s.L, s.req.h, s.op64, s.b64, s.x64, &s.rec->flags, ad, &s.s.op,
+                             s.precision == PB_F32 ? (float*)s.s.b : nullptr, s.precision == PB_F32 ? s.s.x : nullptr);
         if (e != PB_OK) return e;
         if (s.precision == PB_F32) {
-            e = launch_round32(s.op64, s.b64, s.x64, s.L.npad, s.s.op, (float*)s.s.b, s.s.x, ad);
-            if (e != PB_OK) return e;
             e = launch_fill<int>((int*)s.S, (int64_t)(sizeof(SyncState) / sizeof(int)), 0, ad);
             if (e != PB_OK) return e;
             s.s.warm = s.req.warm_start ? 1 : 0;
             s.resume = false;
             s.solving = true;
         } else {
-            e = launch_round32(s.op64, s.b64, s.x64, s.L.npad, s.s.op, nullptr, nullptr, ad);
-            if (e != PB_OK) return e;
             s.s.warm = 0;
             e = enqueue_outer_residual(s, ad);
             if (e != PB_OK) return e;

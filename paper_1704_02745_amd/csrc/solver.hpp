@@ -8,11 +8,13 @@
 namespace pb {
 
 // operator.hip
+// op32 (with b32, x32 where given): also the FP32 roundings; the inner matrix of
+// refinement is the FP32 rounding of the FP64 coefficients.
 pb_status launch_prepare64(const double* ex, const double* ey, const double* ez, const double* k2,
                            const double* rhs, const double* xin, int warm, int periodic, const Layout& L,
-                           double h, Op<double> op, double* b, double* x, int* flags, hipStream_t st);
-pb_status launch_round32(Op<double> op64, const double* b, const double* x, int64_t npad, Op<float> op32,
-                         float* b32, float* x32, hipStream_t st);
+                           double h, Op<double> op, double* b, double* x, int* flags, hipStream_t st,
+                           const Op<float>* op32 = nullptr, float* b32 = nullptr, float* x32 = nullptr);
+pb_status launch_round32(const double* b, int64_t npad, float* b32, hipStream_t st);
 int residual_blocks(const Layout& L);
 pb_status launch_residual64(Op<double> op, const double* b, const double* x, const Layout& L, int periodic,
                             double* r64, float* r32, double* partials, double* out2, hipStream_t st);
