@@ -36,6 +36,18 @@ struct Plan {
     SyncState* sync = nullptr;      // device: one per problem
     ProbRec* rec = nullptr;         // device: one per problem
     int* fit = nullptr;             // device: one per problem (coded coefficients fit the dictionary)
+    // problems whose state fits the device run in the resident form, the
+    // others in the streaming form, one launch each
+    std::vector<int> res, str;      // their indices
+    std::vector<ResBatchPlan> rp;   // per problem (grid 0: streaming)
+    std::vector<char*> slots;       // device: barrier words per problem
+    char* all_slots = nullptr;      // and the range that holds them all
+    size_t slot_bytes = 0, res_lds = 0;
+    char* res_table = nullptr;      // device: RArgs records of the problems in res
+    int* job_off = nullptr;         // device: job list offsets per workgroup
+    char* jobs = nullptr;           // device: (index in res, workgroup) pairs
+    int groups = 0;                 // workgroups of the resident launch
+    size_t str_lds = 0;             // LDS of the streaming form over every problem of the batch
     std::vector<Layout> L;
     std::vector<Tiling> t;
     std::vector<SolveBufs<T>> s;
@@ -53,7 +65,7 @@ bool problem_ok(const pb_problem& p) {
 // Carve the workspace (base may be null to size it). Returns false with an
 // error set if a problem cannot be tiled.
 template <typename T>
-bool carve_batch(void* base, int nprob, const pb_problem* probs, Plan<T>& P, int zchunk = 0) {
+bool carve_batch(void* base, int nprob, const pb_problem* probs, Plan<T>& P, int zchunk = 0, bool resident = true) {
     size_t off = 0;
     auto take = [&](size_t bytes) -> void* {
         const size_t o = off;
@@ -74,7 +86,17 @@ bool carve_batch(void* base, int nprob, const pb_problem* probs, Plan<T>& P, int
             set_error("batch: problem %d (nx = %d) is too wide for the batch kernel's in-plane halo", i, L.nx);
             return false;
         }
-        P.lds = std::max(P.lds, t.lds);
+        const ResBatchPlan rp = resident ? resident_batch_plan<T>(L) : ResBatchPlan{};
+        P.rp.push_back(rp);
+        P.str_lds = std::max(P.str_lds, t.lds);
+        if (rp.grid > 0) {
+            P.res.push_back(i);
+            P.res_lds = std::max(P.res_lds, rp.lds);
+            P.groups = rp.groups;
+        } else {
+            P.str.push_back(i);
+            P.lds = std::max(P.lds, t.lds);
+        }
         const size_t n8 = sizeof(double) * (size_t)L.npad, nT = sizeof(T) * (size_t)L.npad;
         P.L.push_back(L);
         P.t.push_back(t);
@@ -104,8 +126,63 @@ bool carve_batch(void* base, int nprob, const pb_problem* probs, Plan<T>& P, int
         s.warm = probs[i].warm_start ? 1 : 0;
         P.s.push_back(s);
     }
+    size_t njobs = 0;
+    P.all_slots = base ? (char*)base + off : nullptr;
+    const size_t slots0 = off;
+    for (int i = 0; i < nprob; ++i) {
+        P.slots.push_back(P.rp[i].grid > 0 ? (char*)take(P.rp[i].slot_bytes) : nullptr);
+        njobs += (size_t)P.rp[i].grid;
+    }
+    P.slot_bytes = off - slots0;
+    if (!P.res.empty()) {
+        P.res_table = (char*)take(resident_batch_args_bytes<T>() * P.res.size());
+        P.job_off = (int*)take(sizeof(int) * (size_t)(P.groups + 1));
+        P.jobs = (char*)take(2 * sizeof(int) * njobs);
+    }
     P.bytes = off;
     return true;
+}
+
+// Jacobi-CG iterations of a problem relative to others (the count grows about
+// with the root of the edge once the salt screens the long waves).
+double expected_iterations(const Layout& L) { return std::sqrt((double)std::max(L.nx, std::max(L.ny, L.nz))); }
+
+// The job lists of the resident launch: problems in order of decreasing
+// expected duration (wider ones first among equals), each on the workgroups
+// that are free first. off: P.groups + 1 offsets; jobs: (index in P.res,
+// workgroup of the problem) pairs.
+template <typename T>
+void resident_schedule(const Plan<T>& P, std::vector<int>& off, std::vector<int>& jobs) {
+    const int n = (int)P.res.size();
+    std::vector<int> order(n);
+    for (int k = 0; k < n; ++k) order[k] = k;
+    auto cost = [&](int k) { return P.rp[P.res[k]].us * expected_iterations(P.L[P.res[k]]); };
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+        const int ga = P.rp[P.res[a]].grid, gb = P.rp[P.res[b]].grid;
+        return ga != gb ? ga > gb : cost(a) > cost(b);
+    });
+    std::vector<std::vector<int>> list(P.groups);
+    std::vector<double> free_at(P.groups, 0.0);
+    std::vector<int> by(P.groups);
+    for (int g = 0; g < P.groups; ++g) by[g] = g;
+    for (int k : order) {
+        const int G = P.rp[P.res[k]].grid;
+        std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return free_at[a] < free_at[b]; });
+        const double end = free_at[by[G - 1]] + cost(k);
+        std::vector<int> gang(by.begin(), by.begin() + G);
+        std::sort(gang.begin(), gang.end());
+        for (int w = 0; w < G; ++w) {
+            list[gang[w]].push_back(k);
+            list[gang[w]].push_back(w);
+            free_at[gang[w]] = end;
+        }
+    }
+    off.assign(1, 0);
+    jobs.clear();
+    for (int g = 0; g < P.groups; ++g) {
+        jobs.insert(jobs.end(), list[g].begin(), list[g].end());
+        off.push_back((int)jobs.size() / 2);
+    }
 }
 
 // Workgroups per problem, proportional to nodes x max edge, at least one,
@@ -171,6 +248,9 @@ pb_status enqueue_finish(const Plan<T>& P, const pb_problem* probs, hipStream_t 
     return PB_OK;
 }
 
+template <typename T>
+pb_status launch_solves(const Plan<T>& P, int grid, hipStream_t st, bool cooperative, int coded);
+
 // The whole batch on `st`: clear flags and barrier state, prepare, solve,
 // finish; nothing is read back to the host, so it can be recorded in a graph.
 // coded == 2 (FP32): every problem's dictionary, fit flag and code words are
@@ -195,8 +275,7 @@ pb_status enqueue_batch(const Plan<T>& P, const pb_problem* probs, int grid, boo
                 if (e != PB_OK) return e;
             }
     }
-    e = batch_launch<T>(P.table, P.first, P.nprob, grid, coded ? P.lds + kCodedLdsBytes : P.lds, st, cooperative,
-                        coded);
+    e = launch_solves<T>(P, grid, st, cooperative, coded);
     if (e != PB_OK) return e;
     return enqueue_finish<T>(P, probs, st);
 }
@@ -205,31 +284,72 @@ pb_status enqueue_batch(const Plan<T>& P, const pb_problem* probs, int grid, boo
 // dictionary when `coded`, and its fit flag when coded == 2).
 template <typename T>
 pb_status fill_table(const Plan<T>& P, const pb_problem* probs, int coded, hipStream_t st) {
-    std::vector<char> host(batch_kargs_bytes<T>() * (size_t)P.nprob);
+    std::vector<char> host(batch_kargs_bytes<T>() * P.str.size()), rhost(resident_batch_args_bytes<T>() * P.res.size());
+    size_t ns = 0, nr = 0;
     for (int i = 0; i < P.nprob; ++i) {
         const int maxiter = probs[i].maxiter > 0 ? probs[i].maxiter
                                                  : 10 * std::max(probs[i].nx, std::max(probs[i].ny, probs[i].nz));
         const float* cw = coded ? (const float*)P.s[i].q2 : nullptr;
         const float* tab = coded ? dictionary_table(P.s[i].q) : nullptr;
-        batch_fill_kargs<T>(host.data() + batch_kargs_bytes<T>() * i, P.L[i], P.s[i], &P.sync[i], P.partials[i],
-                            P.t[i], probs[i].tol, maxiter, 0, 0, cw, tab, coded == 2 ? P.fit + i : nullptr);
+        const int* fit = coded == 2 ? P.fit + i : nullptr;
+        if (P.rp[i].grid > 0)
+            resident_batch_fill<T>(rhost.data() + resident_batch_args_bytes<T>() * nr++, P.L[i], P.s[i], &P.sync[i],
+                                   P.slots[i], probs[i].tol, maxiter, (int)P.res.size(), cw, tab, fit);
+        else
+            batch_fill_kargs<T>(host.data() + batch_kargs_bytes<T>() * ns++, P.L[i], P.s[i], &P.sync[i], P.partials[i],
+                                P.t[i], probs[i].tol, maxiter, 0, 0, cw, tab, fit);
     }
-    PB_HIP(hipMemcpyAsync(P.table, host.data(), host.size(), hipMemcpyHostToDevice, st));
+    if (ns) PB_HIP(hipMemcpyAsync(P.table, host.data(), host.size(), hipMemcpyHostToDevice, st));
+    if (nr) PB_HIP(hipMemcpyAsync(P.res_table, rhost.data(), rhost.size(), hipMemcpyHostToDevice, st));
     PB_HIP(hipStreamSynchronize(st));
     return PB_OK;
+}
+
+// The solves: one resident launch, then one streaming launch, each over the
+// problems of its form. grid: workgroups of the streaming launch.
+template <typename T>
+pb_status launch_solves(const Plan<T>& P, int grid, hipStream_t st, bool cooperative, int coded) {
+    if (!P.res.empty()) {
+        pb_status e = launch_fill<int>((int*)P.all_slots, (int64_t)(P.slot_bytes / sizeof(int)), 0, st);
+        if (e != PB_OK) return e;
+        for (int i : P.res)
+            if ((e = resident_batch_start<T>(P.L[i], P.s[i], st)) != PB_OK) return e;
+        e = resident_batch_launch<T>(P.res_table, P.job_off, P.jobs, P.groups, P.res_lds, st, cooperative);
+        if (e != PB_OK) return e;
+    }
+    if (P.str.empty()) return PB_OK;
+    return batch_launch<T>(P.table, P.first, (int)P.str.size(), grid, coded ? P.lds + kCodedLdsBytes : P.lds, st,
+                           cooperative, coded);
 }
 
 // Upload the per-problem kernel arguments and workgroup offsets.
 template <typename T>
 pb_status upload_table(const Plan<T>& P, const pb_problem* probs, int& grid, hipStream_t st) {
-    const int cap = batch_capacity<T>(P.lds);
-    if (cap < P.nprob) {
-        set_error("batch: %d problems but only %d co-resident workgroups; split the batch", P.nprob, cap);
+    grid = 0;
+    std::vector<int> first, off, jobs;
+    // a batch holds at most as many problems as the streaming form has
+    // co-resident workgroups, whatever form its problems run in
+    if (const int most = batch_capacity<T>(P.str_lds); most < P.nprob) {
+        set_error("batch: %d problems but only %d co-resident workgroups; split the batch", P.nprob, most);
         return PB_ERR_ARG;
     }
-    const std::vector<int> first = share_workgroups(P.L, P.t, cap);
-    grid = first.back();
-    PB_HIP(hipMemcpyAsync(P.first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice, st));
+    if (!P.str.empty()) {
+        const int cap = batch_capacity<T>(P.lds);
+        std::vector<Layout> L;
+        std::vector<Tiling> t;
+        for (int i : P.str) {
+            L.push_back(P.L[i]);
+            t.push_back(P.t[i]);
+        }
+        first = share_workgroups(L, t, cap);
+        grid = first.back();
+        PB_HIP(hipMemcpyAsync(P.first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice, st));
+    }
+    if (!P.res.empty()) {
+        resident_schedule<T>(P, off, jobs);
+        PB_HIP(hipMemcpyAsync(P.job_off, off.data(), sizeof(int) * off.size(), hipMemcpyHostToDevice, st));
+        PB_HIP(hipMemcpyAsync(P.jobs, jobs.data(), sizeof(int) * jobs.size(), hipMemcpyHostToDevice, st));
+    }
     return fill_table<T>(P, probs, 0, st);
 }
 
@@ -249,7 +369,7 @@ pb_status enqueue_batch_direct(const Plan<T>& P, const pb_problem* probs, int gr
     e = enqueue_prepare<T>(P, probs, st);
     if (e != PB_OK) return e;
     if constexpr (sizeof(T) == sizeof(float)) {
-        bool can = coded_coefficients() != 0 && batch_capacity<T>(P.lds + kCodedLdsBytes, true) >= grid;
+        bool can = coded_coefficients() != 0 && (P.str.empty() || batch_capacity<T>(P.lds + kCodedLdsBytes, true) >= grid);
         for (int i = 0; i < P.nprob && can; ++i) can = coded_layout_ok(P.L[i]);
         if (can) {
             for (int i = 0; i < P.nprob; ++i) {
@@ -271,7 +391,7 @@ pb_status enqueue_batch_direct(const Plan<T>& P, const pb_problem* probs, int gr
             coded = true;
         }
     }
-    e = batch_launch<T>(P.table, P.first, P.nprob, grid, coded ? P.lds + kCodedLdsBytes : P.lds, st, true, coded);
+    e = launch_solves<T>(P, grid, st, true, coded);
     if (e != PB_OK) return e;
     return enqueue_finish<T>(P, probs, st);
 }
@@ -366,7 +486,7 @@ pb_status batch_autotune_impl(int nprob, const pb_problem* probs, int iters, voi
     pb_status e = PB_OK;
     for (int z : kBatchZCandidates) {
         Plan<T> P;
-        if (!carve_batch<T>(ws, nprob, trial.data(), P, z)) { e = PB_ERR_ARG; break; }
+        if (!carve_batch<T>(ws, nprob, trial.data(), P, z, false)) { e = PB_ERR_ARG; break; }
         if (wsb < P.bytes) {
             set_error("pb_batch_autotune: workspace of %zu bytes, %zu needed", wsb, P.bytes);
             e = PB_ERR_NOMEM;
@@ -478,10 +598,10 @@ extern "C" size_t pb_batch_autotune_workspace_bytes(int32_t nprob, const pb_prob
         size_t b = 0;
         if (precision == PB_F64) {
             Plan<double> P;
-            b = carve_batch<double>(nullptr, nprob, probs, P, z) ? P.bytes : 0;
+            b = carve_batch<double>(nullptr, nprob, probs, P, z, false) ? P.bytes : 0;
         } else {
             Plan<float> P;
-            b = carve_batch<float>(nullptr, nprob, probs, P, z) ? P.bytes : 0;
+            b = carve_batch<float>(nullptr, nprob, probs, P, z, false) ? P.bytes : 0;
         }
         if (b == 0) return 0;
         most = std::max(most, b);
@@ -521,7 +641,8 @@ pb_status graph_build(pb_batch_graph* G, Plan<T>& P, void* ws, size_t wsb, hipSt
     // coefficients may change between replays)
     G->coded = 0;
     if constexpr (sizeof(T) == sizeof(float)) {
-        bool can = coded_coefficients() != 0 && batch_capacity<T>(P.lds + kCodedLdsBytes, 2) >= grid;
+        bool can = coded_coefficients() != 0 &&
+                   (P.str.empty() || batch_capacity<T>(P.lds + kCodedLdsBytes, 2) >= grid);
         for (int i = 0; i < P.nprob && can; ++i) can = coded_layout_ok(P.L[i]);
         if (can) {
             e = fill_table<T>(P, G->probs.data(), 2, st);

@@ -29,6 +29,8 @@
 #include "jpcg_device.hpp"
 #include "solver.hpp"
 
+#include <vector>
+
 namespace pb {
 namespace {
 
@@ -49,6 +51,13 @@ struct RArgs {
     SyncState* S;
     unsigned long long* slots;   // 2 x workgroups x kSlotWords, cleared before the launch
     long long timeout_ticks;
+    long long first_timeout_ticks;   // of the first barrier (a batch's workgroups come to it from earlier problems)
+    int planes;           // batch: planes per brick (the kernel's NZ)
+    // batch: the operator as code words and their dictionary, read instead of
+    // its arrays when given and (fit given) *fit == 1
+    const uint32_t* cw;
+    const float* ctab;
+    const int* fit;
 };
 
 constexpr int kSlotWords = 16;            // two words per sum (low half, high half), 8 sums
@@ -122,6 +131,9 @@ __device__ __forceinline__ float bload(Rsrc r, uint32_t off, float) {
 template <int AUX>
 __device__ __forceinline__ double bload(Rsrc r, uint32_t off, double) {
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, AUX));
+}
+__device__ __forceinline__ uint32_t word_load(Rsrc r, uint32_t off) {
+    return __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
 }
 __device__ __forceinline__ void agent_store(Rsrc r, uint32_t off, float v) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, (int)off, 0, kAgentScope);
@@ -203,6 +215,9 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
     const T* const pU = !valid ? pl : wrap_y && j == ny - 1 ? pl - SZ * row * (ny - 1) : pl + SZ * row;
     const T* const pD = !valid ? pl : wrap_y && j == 0 ? pl + SZ * row * (ny - 1) : pl - SZ * row;
 
+    const bool coded = E == 4 && a.cw && (!a.fit || *a.fit == 1);
+    auto decode = [&](uint32_t c, int byte) -> T { return (T)a.ctab[(c >> (8 * byte)) & 255u]; };
+    auto diag_at = [&](int64_t g) -> T { return coded ? decode(a.cw[g], 3) : a.op.d[g]; };
     // ---- the operator and the state of the own nodes
     T r[NZ], x[NZ], q[NZ], cx[NZ], cy[NZ], cz[NZ], d[NZ], iv[KEEP ? NZ : 1];
     T cxm[LL ? 1 : NZ], cym[LL ? 1 : NZ];
@@ -212,17 +227,30 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
         auto from = [&](const T* p) { return rsrc_of(p + (int64_t)k0 * sp, (int64_t)nk * sp); };
         const Rsrc rcx = from(a.op.cx), rcy = from(a.op.cy), rcz = from(a.op.cz), rd = from(a.op.d), rr0 = from(a.r0),
                    rb0 = from(a.b), rx = from(a.x);
+        const Rsrc rcw = rsrc_of((const T*)a.cw + (int64_t)k0 * sp, (int64_t)nk * sp);
         auto at = [&](bool in, int p) { return valid && in ? (uint32_t)p * E : kNowhere; };
         uint32_t o = at(true, pos), ox = at(i > 0 || PER, i > 0 ? pos - 1 : pos + nx - 1),
                  oy = at(j > 0 || PER, j > 0 ? pos - nx : pos + (ny - 1) * nx);
         const uint32_t plane_bytes = (uint32_t)(sp * E);
 #pragma unroll
         for (int kk = 0; kk < NZ; ++kk) {
-            cx[kk] = bload<0>(rcx, o, T());
-            cy[kk] = bload<0>(rcy, o, T());
-            cz[kk] = bload<0>(rcz, o, T());
-            d[kk] = bload<0>(rd, o, T());
-            const T cxl = bload<0>(rcx, ox, T()), cyl = bload<0>(rcy, oy, T());
+            T cxl, cyl;
+            if (coded) {   // words at kNowhere read as 0, the code of 0
+                const uint32_t c = word_load(rcw, o);
+                cx[kk] = decode(c, 0);
+                cy[kk] = decode(c, 1);
+                cz[kk] = decode(c, 2);
+                d[kk] = decode(c, 3);
+                cxl = decode(word_load(rcw, ox), 0);
+                cyl = decode(word_load(rcw, oy), 1);
+            } else {
+                cx[kk] = bload<0>(rcx, o, T());
+                cy[kk] = bload<0>(rcy, o, T());
+                cz[kk] = bload<0>(rcz, o, T());
+                d[kk] = bload<0>(rd, o, T());
+                cxl = bload<0>(rcx, ox, T());
+                cyl = bload<0>(rcy, oy, T());
+            }
             if constexpr (LL) {
                 CL[2 * kk * BS] = cxl;
                 CL[(2 * kk + 1) * BS] = cyl;
@@ -253,14 +281,14 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
     T czb = T(0), rb = T(0), ib = T(0), pb_ = T(0), rt = T(0), it_ = T(0), pt = T(0);
     if (valid && has_b) {
         const int64_t g = (int64_t)kb * sp + pos;
-        czb = a.op.cz[g];
+        czb = coded ? decode(a.cw[g], 2) : a.op.cz[g];
         rb = a.r0[g];
-        ib = jacobi_inv(a.op.d[g]);
+        ib = jacobi_inv(diag_at(g));
     }
     if (valid && has_t) {
         const int64_t g = (int64_t)kt * sp + pos;
         rt = a.r0[g];
-        it_ = jacobi_inv(a.op.d[g]);
+        it_ = jacobi_inv(diag_at(g));
     }
     // ---- where the faces of this brick are published and the halo's are read
     // (byte offsets); kNowhere where no neighbour reads or is
@@ -316,7 +344,7 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
         if (in && kk < nk) {
             const int64_t g0 = (int64_t)(k0 + kk) * sp + (int64_t)hi_j * nx + hi_i;
             n.r = a.r0[g0];
-            n.inv = jacobi_inv(a.op.d[g0]);
+            n.inv = jacobi_inv(diag_at(g0));
             n.from = there;
         } else {
             n.p = kk;   // a corner column, whose p stays zero (1/d = 0)
@@ -368,7 +396,7 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
                 if (bad == 0) break;
                 const long long now = wall_clock64();
                 if (t0 == 0) t0 = now;
-                if (now - t0 > a.timeout_ticks) {
+                if (now - t0 > (b == 0 ? a.first_timeout_ticks : a.timeout_ticks)) {
                     s_flag[0] = 1;
                     break;
                 }
@@ -526,6 +554,43 @@ template <typename T, int BS, int NZ, bool PER>
 __global__ __launch_bounds__(BS) void k_jpcg_resident(RArgs<T> a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     resident_problem<T, BS, NZ, PER>(a, blockIdx.x, lds_raw);
+}
+
+// The bricks of a batch: 512 threads, these numbers of planes.
+template <typename T>
+__device__ __forceinline__ void resident_batch_problem(const RArgs<T>& a, int w, unsigned char* lds) {
+    if constexpr (sizeof(T) == 4) {
+        if (a.planes == 19) resident_problem<T, 512, 19, false>(a, w, lds);
+        else if (a.planes == 17) resident_problem<T, 512, 17, false>(a, w, lds);
+        else if (a.planes == 12) resident_problem<T, 512, 12, false>(a, w, lds);
+        else if (a.planes == 8) resident_problem<T, 512, 8, false>(a, w, lds);
+    } else {
+        if (a.planes == 8) resident_problem<T, 512, 8, false>(a, w, lds);
+        else if (a.planes == 4) resident_problem<T, 512, 4, false>(a, w, lds);
+    }
+}
+template <typename T>
+const std::vector<int>& batch_planes() {
+    static const std::vector<int> v = sizeof(T) == 4 ? std::vector<int>{8, 12, 17, 19} : std::vector<int>{4, 8};
+    return v;
+}
+
+// Many problems in one launch: workgroup g runs the jobs [off[g], off[g + 1]) of
+// its list one after the other, job (problem, its workgroup number there). Jobs
+// are listed in one global order, so a workgroup that waits in a problem's
+// first barrier waits only for workgroups whose earlier jobs come before that
+// problem in every list: no cycle.
+template <typename T>
+__global__ __launch_bounds__(512) void k_resident_batch(const RArgs<T>* __restrict__ probs, const int* __restrict__ off,
+                                                        const int2* __restrict__ jobs) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int end = off[blockIdx.x + 1];
+    for (int n = off[blockIdx.x]; n < end; ++n) {
+        const int2 job = jobs[n];
+        const RArgs<T> a = probs[job.x];
+        resident_batch_problem<T>(a, job.y, lds_raw);
+        __syncthreads();
+    }
 }
 
 }  // namespace

@@ -14,7 +14,5 @@ const std::vector<ResVariant>& res_variants<float>() {
     return v;
 }
 }  // namespace
-template pb_status resident_jpcg<float>(const Layout&, const SolveBufs<float>&, SyncState*, double*, double, int,
-                                        hipStream_t, SolveResult*, int, bool&);
-template bool resident_fits<float>(const Layout&, int);
+PB_RES_INSTANCES(float)
 }  // namespace pb

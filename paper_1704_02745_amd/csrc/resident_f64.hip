@@ -12,7 +12,5 @@ const std::vector<ResVariant>& res_variants<double>() {
     return v;
 }
 }  // namespace
-template pb_status resident_jpcg<double>(const Layout&, const SolveBufs<double>&, SyncState*, double*, double, int,
-                                         hipStream_t, SolveResult*, int, bool&);
-template bool resident_fits<double>(const Layout&, int);
+PB_RES_INSTANCES(double)
 }  // namespace pb

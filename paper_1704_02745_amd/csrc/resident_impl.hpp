@@ -6,7 +6,10 @@
 #include "resident_device.hpp"
 
 #include <algorithm>
+#include <cstring>
+#include <map>
 #include <mutex>
+#include <tuple>
 #include <vector>
 
 namespace pb {
@@ -23,11 +26,11 @@ struct ResPlan {
     int bs, nz, tx, ty, nxt, nyt, nzc, grid;
     size_t lds;
     const void* fn;
+    double us;   // modelled microseconds of a pass
 };
 
 struct ResDevice {
-    int cus = 0, wallclock_khz = 0;
-    size_t lds = 0;
+    int dev = -1, cus = 0, wallclock_khz = 0;
 };
 ResDevice res_device() {
     static std::mutex mu;
@@ -41,7 +44,7 @@ ResDevice res_device() {
         int v = 0;
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess) d.cus = v;
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeWallClockRate, dev) == hipSuccess) d.wallclock_khz = v;
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess) d.lds = (size_t)v;
+        d.dev = dev;
         cache[dev] = d;
     }
     return cache[dev];
@@ -50,50 +53,84 @@ ResDevice res_device() {
 template <typename T>
 const std::vector<ResVariant>& res_variants();
 
-// The bricks of a grid: the cheapest feasible (block, planes, tile) by a model
-// of one pass (see resident_cost); grid = 0 when the state does not fit.
+// Microseconds of one pass, fitted to sweeps of block, planes and tile at
+// 33^3-129^3: a fixed part (the barrier's two memory latencies), the planes of a
+// thread (0.15 each with 512 threads), the halo nodes, the slots every
+// workgroup polls, and the strided x-faces.
+double resident_pass_us(int bs, int nzb, int halo, int grid, bool split_x) {
+    return 2.4 + 0.149 * nzb * bs / 512 + 0.1 * halo / bs + 0.0107 * grid + (split_x ? 0.2 : 0.0);
+}
+
+// Every feasible way to cut a grid into bricks of `bs` threads and `nzb`
+// planes, the cheapest by `cost` kept in `best`.
+template <typename T, typename Cost>
+void resident_search(const Layout& L, int per, int bs, int nzb, int cap, int64_t face_room, const void* fn, Cost&& cost,
+                     double& best_cost, ResPlan& best) {
+    const int nzc = (L.nz + nzb - 1) / nzb;
+    if (nzc > cap) return;
+    for (int nxt = 1; nxt <= cap / nzc; ++nxt) {
+        if (nxt > 1 && L.nx / nxt < 2) break;   // a column is on one x-face at most
+        const int tx = (L.nx + nxt - 1) / nxt;
+        if (tx > bs) continue;
+        const int nyt = (L.ny + bs / tx - 1) / (bs / tx);
+        if (nyt > 1 && L.ny / nyt < 2) continue;
+        const int ty = (L.ny + nyt - 1) / nyt;
+        const int64_t grid = (int64_t)nxt * nyt * nzc;
+        if (grid > cap) continue;
+        const size_t lds = resident_lds_bytes<T>(bs, nzb, tx, ty);
+        if (lds > 160 * 1024) continue;
+        if ((grid > 1 || per) && grid * face_len(bs, nzb, tx, ty) > face_room) continue;
+        const int halo = (nxt > 1 ? 2 * ty * nzb : 0) + (nyt > 1 ? 2 * tx * nzb : 0);
+        const double us = resident_pass_us(bs, nzb, halo, (int)grid, nxt > 1), c = cost(us, (int)grid);
+        if (c < best_cost) {
+            best_cost = c;
+            best = ResPlan{bs, nzb, tx, ty, nxt, nyt, nzc, (int)grid, lds, fn, us};
+        }
+    }
+}
+
+// The bricks of a grid; grid = 0 when its state does not fit the device. For a
+// solve of its own the fastest pass counts; in a batch (batch = true, one
+// kernel for all) the device time a pass takes, workgroups times microseconds:
+// problems share the device, and each keeps its bricks in any mix. Plans are
+// kept per device and shape (a host-side search of a few microseconds).
 template <typename T>
-ResPlan resident_plan(const Layout& L, int per) {
+ResPlan resident_plan(const Layout& L, int per, bool batch) {
     ResPlan best{};
     const ResDevice di = res_device();
     const int cap = std::min(di.cus, kMaxResidentGroups);
     if (cap <= 0 || L.npad * (int64_t)sizeof(T) >= ((int64_t)1 << 31)) return best;
+    using Key = std::tuple<int, int, int, int, int, bool>;
+    static std::mutex mu;
+    static std::map<Key, ResPlan> kept;
+    const Key key(di.dev, L.nx, L.ny, L.nz, per, batch);
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        const auto it = kept.find(key);
+        if (it != kept.end()) return it->second;
+    }
     double best_cost = 1e300;
-    for (const ResVariant& v : res_variants<T>()) {
-        const int nzc = (L.nz + v.nz - 1) / v.nz;
-        if (nzc > cap) continue;
-        for (int nxt = 1; nxt <= cap / nzc; ++nxt) {
-            if (nxt > 1 && L.nx / nxt < 2) break;
-            const int tx = (L.nx + nxt - 1) / nxt;
-            if (tx > v.bs) continue;
-            const int nyt = (L.ny + v.bs / tx - 1) / (v.bs / tx);
-            if (nyt > 1 && L.ny / nyt < 2) continue;
-            const int ty = (L.ny + nyt - 1) / nyt;
-            const int64_t grid = (int64_t)nxt * nyt * nzc;
-            if (grid > cap) continue;
-            const size_t lds = resident_lds_bytes<T>(v.bs, v.nz, tx, ty);
-            if (lds > 160 * 1024) continue;
-            // published faces fit five of the six state arrays of the streaming
-            // form (a warm start's residual takes the sixth)
-            if ((grid > 1 || per) && 2 * grid * face_len(v.bs, v.nz, tx, ty) > 5 * L.npad) continue;
-            const int halo = (nxt > 1 ? 2 * ty * v.nz : 0) + (nyt > 1 ? 2 * tx * v.nz : 0);
-            // microseconds of one pass beyond its fixed part, fitted to sweeps of
-            // block, planes and tile at 33^3-129^3: the planes of a thread (0.15
-            // each with 512 threads), the halo nodes, the slots every workgroup
-            // polls, and the strided x-faces
-            const double cost = 0.149 * v.nz * v.bs / 512 + 0.1 * halo / v.bs + 0.0107 * grid + (nxt > 1 ? 0.2 : 0.0);
-            if (cost < best_cost) {
-                best_cost = cost;
-                best = ResPlan{v.bs, v.nz, tx, ty, nxt, nyt, nzc, (int)grid, lds, v.fn[per ? 1 : 0]};
-            }
-        }
+    if (batch) {
+        // faces in r and in r2, one parity each
+        for (int nzb : batch_planes<T>())
+            resident_search<T>(L, 0, 512, nzb, cap, L.npad, (const void*)k_resident_batch<T>,
+                               [](double us, int grid) { return us * grid; }, best_cost, best);
+    } else {
+        // both parities in five of the six state arrays of the streaming form (a
+        // warm start's residual takes the sixth)
+        for (const ResVariant& v : res_variants<T>())
+            resident_search<T>(L, per, v.bs, v.nz, cap, 5 * L.npad / 2, v.fn[per ? 1 : 0],
+                               [](double us, int) { return us; }, best_cost, best);
     }
     if (best.grid > 0) {
         int nb = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, best.fn, best.bs, best.lds) != hipSuccess ||
             nb * di.cus < best.grid)
-            return ResPlan{};
+            best = ResPlan{};
     }
+    std::lock_guard<std::mutex> lk(mu);
+    if (kept.size() >= 4096) kept.clear();
+    kept[key] = best;
     return best;
 }
 
@@ -127,22 +164,14 @@ __global__ void k_resident_start(Op<T> op, const T* __restrict__ b, const T* __r
 }
 
 template <typename T>
-pb_status resident_solve(const Layout& L, const SolveBufs<T>& s, SyncState* sync, double* partials, double tol,
-                         int maxiter, hipStream_t st, SolveResult* res, int periodic, bool& ran) {
-    ran = false;
-    // the state arrays of the streaming form, r to q2, hold the published faces
-    if (!s.r || !s.q2 || s.q2 - s.r != 5 * L.npad) return PB_OK;
-    const ResPlan p = resident_plan<T>(L, periodic);
-    if (p.grid <= 0) return PB_OK;
+RArgs<T> resident_args(const Layout& L, const SolveBufs<T>& s, const ResPlan& p, SyncState* sync,
+                       unsigned long long* slots, double tol, int maxiter) {
     const ResDevice di = res_device();
     RArgs<T> a{};
     a.op = s.op;
     a.b = s.b;
     a.r0 = s.b;
     a.x = s.x;
-    const int64_t half = (int64_t)p.grid * face_len(p.bs, p.nz, p.tx, p.ty);
-    a.faces[0] = s.r;
-    a.faces[1] = s.r + half;
     a.nx = L.nx; a.ny = L.ny; a.nz = L.nz;
     a.sp = L.sp;
     a.tx = p.tx; a.ty = p.ty;
@@ -151,13 +180,37 @@ pb_status resident_solve(const Layout& L, const SolveBufs<T>& s, SyncState* sync
     a.maxiter = maxiter;
     a.warm = s.warm;
     a.S = sync;
-    a.slots = (unsigned long long*)partials;
+    a.slots = slots;
+    a.planes = p.nz;
+    // every wait is bounded: 20 s of the constant-rate clock
     a.timeout_ticks = (long long)(di.wallclock_khz > 0 ? di.wallclock_khz : 100000) * 1000LL * 20LL;
+    a.first_timeout_ticks = a.timeout_ticks;
+    return a;
+}
+
+template <typename T>
+pb_status launch_resident_start(const Layout& L, const Op<T>& op, const T* b, const T* x, T* r, int periodic,
+                                hipStream_t st) {
+    const unsigned nb = (unsigned)std::min<int64_t>((L.npad + 255) / 256, 8192);
+    hipLaunchKernelGGL(k_resident_start<T>, dim3(nb), dim3(256), 0, st, op, b, x, r, L.nx, L.ny, L.nz, L.sp, periodic);
+    PB_HIP(hipGetLastError());
+    return PB_OK;
+}
+
+template <typename T>
+pb_status resident_solve(const Layout& L, const SolveBufs<T>& s, SyncState* sync, double* partials, double tol,
+                         int maxiter, hipStream_t st, SolveResult* res, int periodic, bool& ran) {
+    ran = false;
+    // the state arrays of the streaming form, r to q2, hold the published faces
+    if (!s.r || !s.q2 || s.q2 - s.r != 5 * L.npad) return PB_OK;
+    const ResPlan p = resident_plan<T>(L, periodic, false);
+    if (p.grid <= 0) return PB_OK;
+    RArgs<T> a = resident_args<T>(L, s, p, sync, (unsigned long long*)partials, tol, maxiter);
+    const int64_t half = (int64_t)p.grid * face_len(p.bs, p.nz, p.tx, p.ty);
+    a.faces[0] = s.r;
+    a.faces[1] = s.r + half;
     if (s.warm) {
-        const unsigned nb = (unsigned)std::min<int64_t>((L.npad + 255) / 256, 8192);
-        hipLaunchKernelGGL(k_resident_start<T>, dim3(nb), dim3(256), 0, st, s.op, s.b, (const T*)s.x, s.q2, L.nx, L.ny,
-                           L.nz, L.sp, periodic);
-        PB_HIP(hipGetLastError());
+        if (launch_resident_start<T>(L, s.op, s.b, s.x, s.q2, periodic, st) != PB_OK) return PB_ERR_HIP;
         a.r0 = s.q2;
     }
     if (launch_fill<int>((int*)sync, (int64_t)(sizeof(SyncState) / sizeof(int)), 0, st) != PB_OK) return PB_ERR_HIP;
@@ -211,7 +264,64 @@ pb_status resident_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync,
 }
 template <typename T>
 bool resident_fits(const Layout& L, int periodic) {
-    return resident_plan<T>(L, periodic).grid > 0;
+    return resident_plan<T>(L, periodic, false).grid > 0;
 }
+
+
+// ---- batch support (see solver.hpp)
+
+template <typename T>
+ResBatchPlan resident_batch_plan(const Layout& L) {
+    const ResPlan p = resident_plan<T>(L, 0, true);
+    return ResBatchPlan{p.grid, std::min(res_device().cus, kMaxResidentGroups), p.us, p.lds, (size_t)2 * p.grid * kSlotWords * sizeof(unsigned long long)};
+}
+template <typename T>
+size_t resident_batch_args_bytes() {
+    return sizeof(RArgs<T>);
+}
+template <typename T>
+pb_status resident_batch_fill(void* dst, const Layout& L, const SolveBufs<T>& s, SyncState* S, void* slots, double tol,
+                              int maxiter, int problems, const float* cw, const float* ctab, const int* fit) {
+    const ResPlan p = resident_plan<T>(L, 0, true);
+    RArgs<T> a = resident_args<T>(L, s, p, S, (unsigned long long*)slots, tol, maxiter);
+    a.faces[0] = s.r;
+    a.faces[1] = s.r2;
+    if (s.warm) a.r0 = s.p0;
+    a.first_timeout_ticks = a.timeout_ticks * (1 + (long long)problems);
+    a.cw = (const uint32_t*)cw;
+    a.ctab = ctab;
+    a.fit = fit;
+    std::memcpy(dst, &a, sizeof(a));
+    return PB_OK;
+}
+template <typename T>
+pb_status resident_batch_start(const Layout& L, const SolveBufs<T>& s, hipStream_t st) {
+    return s.warm ? launch_resident_start<T>(L, s.op, s.b, s.x, s.p0, 0, st) : PB_OK;
+}
+template <typename T>
+pb_status resident_batch_launch(const void* d_args, const int* d_off, const void* d_jobs, int grid, size_t lds,
+                                hipStream_t st, bool cooperative) {
+    const RArgs<T>* ap = (const RArgs<T>*)d_args;
+    const int2* jp = (const int2*)d_jobs;
+    void* args[] = {&ap, &d_off, &jp};
+    const void* fn = (const void*)k_resident_batch<T>;
+    const hipError_t e = cooperative ? hipLaunchCooperativeKernel(fn, dim3(grid), dim3(512), args, lds, st)
+                                     : hipLaunchKernel(fn, dim3(grid), dim3(512), args, lds, st);
+    if (e != hipSuccess) {
+        set_error("resident batch launch failed: %s (grid %d, lds %zu)", hipGetErrorString(e), grid, lds);
+        return PB_ERR_HIP;
+    }
+    return PB_OK;
+}
+#define PB_RES_INSTANCES(T)                                                                                       \
+    template pb_status resident_jpcg<T>(const Layout&, const SolveBufs<T>&, SyncState*, double*, double, int,     \
+                                        hipStream_t, SolveResult*, int, bool&);                                   \
+    template bool resident_fits<T>(const Layout&, int);                                                           \
+    template ResBatchPlan resident_batch_plan<T>(const Layout&);                                                  \
+    template size_t resident_batch_args_bytes<T>();                                                               \
+    template pb_status resident_batch_fill<T>(void*, const Layout&, const SolveBufs<T>&, SyncState*, void*, double, \
+                                              int, int, const float*, const float*, const int*);                  \
+    template pb_status resident_batch_start<T>(const Layout&, const SolveBufs<T>&, hipStream_t);                  \
+    template pb_status resident_batch_launch<T>(const void*, const int*, const void*, int, size_t, hipStream_t, bool);
 
 }  // namespace pb

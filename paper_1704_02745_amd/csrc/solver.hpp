@@ -128,6 +128,29 @@ pb_status resident_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync,
                         int maxiter, hipStream_t st, SolveResult* res, int periodic, bool& ran);
 template <typename T>
 bool resident_fits(const Layout& L, int periodic);
+// The same for many problems in one launch. A problem's bricks depend on its
+// shape only; every workgroup of the launch works through a list of jobs
+// (problem, workgroup number in it), all lists in one global order of problems.
+struct ResBatchPlan {
+    int grid;            // workgroups of the problem, 0 when it does not fit
+    int groups;          // workgroups of the launch (one per CU)
+    double us;           // modelled microseconds per iteration
+    size_t lds;
+    size_t slot_bytes;   // barrier words, cleared before every launch
+};
+template <typename T>
+ResBatchPlan resident_batch_plan(const Layout& L);
+template <typename T>
+size_t resident_batch_args_bytes();
+// `problems`: how many share the launch (bounds the wait of a first barrier).
+template <typename T>
+pb_status resident_batch_fill(void* dst, const Layout& L, const SolveBufs<T>& s, SyncState* S, void* slots, double tol,
+                              int maxiter, int problems, const float* cw, const float* ctab, const int* fit);
+template <typename T>
+pb_status resident_batch_start(const Layout& L, const SolveBufs<T>& s, hipStream_t st);   // warm starts: b - A x0
+template <typename T>
+pb_status resident_batch_launch(const void* d_args, const int* d_off, const void* d_jobs, int grid, size_t lds,
+                                hipStream_t st, bool cooperative);
 
 template <typename T>
 Tiling choose_tiling(const Layout& L);
