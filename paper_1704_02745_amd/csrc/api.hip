@@ -246,7 +246,7 @@ pb_status autotune_impl(const Layout& L, const SolveBufs<T>& s, const SolveWs& w
     // the resident form of the same solve, where the grid fits it
     Tiling rt = best_t;
     rt.resident = 1;
-    if (resident_fits<T>(L, 0)) {
+    if (resident_fits<T>(L, 0, false) || (sizeof(T) == 4 && resident_fits<T>(L, 0, true))) {
         double us = 0.0;
         pb_status e = time_tiling<T>(L, s, w, rt, iters, st, us);
         if (e != PB_OK) return e;

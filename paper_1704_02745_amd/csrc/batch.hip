@@ -36,17 +36,22 @@ struct Plan {
     SyncState* sync = nullptr;      // device: one per problem
     ProbRec* rec = nullptr;         // device: one per problem
     int* fit = nullptr;             // device: one per problem (coded coefficients fit the dictionary)
-    // problems whose state fits the device run in the resident form, the
-    // others in the streaming form, one launch each
-    std::vector<int> res, str;      // their indices
+    // problems whose state fits the device run in the resident form, full or
+    // compact, the others in the streaming form, one launch each (choose_forms)
+    struct Form {
+        std::vector<int> of;        // indices of its problems
+        size_t lds = 0;
+        char* table = nullptr;      // device: RArgs records
+        int* job_off = nullptr;     // device: job list offsets per workgroup
+        char* jobs = nullptr;       // device: (index in of, workgroup) pairs
+    };
+    Form res[2];                    // full, compact
+    std::vector<int> str;
     std::vector<ResBatchPlan> rp;   // per problem (grid 0: streaming)
     std::vector<char*> slots;       // device: barrier words per problem
     char* all_slots = nullptr;      // and the range that holds them all
-    size_t slot_bytes = 0, res_lds = 0;
-    char* res_table = nullptr;      // device: RArgs records of the problems in res
-    int* job_off = nullptr;         // device: job list offsets per workgroup
-    char* jobs = nullptr;           // device: (index in res, workgroup) pairs
-    int groups = 0;                 // workgroups of the resident launch
+    size_t slot_bytes = 0;
+    int groups = 0;                 // workgroups of a resident launch
     size_t str_lds = 0;             // LDS of the streaming form over every problem of the batch
     std::vector<Layout> L;
     std::vector<Tiling> t;
@@ -60,6 +65,33 @@ bool problem_ok(const pb_problem& p) {
     return p.nx >= 1 && p.ny >= 1 && p.nz >= 1 && (int64_t)p.nx * p.ny * p.nz < (int64_t(1) << 36) &&
            std::isfinite(p.h) && p.h > 0 && std::isfinite(p.tol) && p.tol > 0 && p.eps_x && p.eps_y &&
            p.eps_z && p.kappa2 && p.rhs && p.x;
+}
+
+// Which problems run in which form. coded 0: no code words, problems that only
+// the compact resident form takes run in the streaming one; 1: every problem
+// has code words; 2: its fit flag says so on the device, so those problems are
+// in both launches and one of the two skips them.
+template <typename T>
+void choose_forms(Plan<T>& P, int coded) {
+    for (auto& f : P.res) {
+        f.of.clear();
+        f.lds = 0;
+    }
+    P.str.clear();
+    P.lds = 0;
+    for (int i = 0; i < P.nprob; ++i) {
+        const ResBatchPlan& rp = P.rp[i];
+        const bool res = rp.grid > 0 && (!rp.compact || coded);
+        if (res) {
+            auto& f = P.res[rp.compact ? 1 : 0];
+            f.of.push_back(i);
+            f.lds = std::max(f.lds, rp.lds);
+        }
+        if (!res || (rp.compact && coded == 2)) {
+            P.str.push_back(i);
+            P.lds = std::max(P.lds, P.t[i].lds);
+        }
+    }
 }
 
 // Carve the workspace (base may be null to size it). Returns false with an
@@ -78,7 +110,7 @@ bool carve_batch(void* base, int nprob, const pb_problem* probs, Plan<T>& P, int
     P.sync = (SyncState*)take(sizeof(SyncState) * (size_t)nprob);
     P.rec = (ProbRec*)take(sizeof(ProbRec) * (size_t)nprob);
     P.fit = (int*)take(sizeof(int) * (size_t)nprob);
-    P.lds = 0;
+    size_t nres[2] = {0, 0}, njobs[2] = {0, 0};
     for (int i = 0; i < nprob; ++i) {
         const Layout L = make_layout(probs[i].nx, probs[i].ny, probs[i].nz);
         const Tiling t = batch_tiling<T>(L, zchunk);
@@ -90,12 +122,9 @@ bool carve_batch(void* base, int nprob, const pb_problem* probs, Plan<T>& P, int
         P.rp.push_back(rp);
         P.str_lds = std::max(P.str_lds, t.lds);
         if (rp.grid > 0) {
-            P.res.push_back(i);
-            P.res_lds = std::max(P.res_lds, rp.lds);
+            ++nres[rp.compact ? 1 : 0];
+            njobs[rp.compact ? 1 : 0] += (size_t)rp.grid;
             P.groups = rp.groups;
-        } else {
-            P.str.push_back(i);
-            P.lds = std::max(P.lds, t.lds);
         }
         const size_t n8 = sizeof(double) * (size_t)L.npad, nT = sizeof(T) * (size_t)L.npad;
         P.L.push_back(L);
@@ -126,20 +155,20 @@ bool carve_batch(void* base, int nprob, const pb_problem* probs, Plan<T>& P, int
         s.warm = probs[i].warm_start ? 1 : 0;
         P.s.push_back(s);
     }
-    size_t njobs = 0;
     P.all_slots = base ? (char*)base + off : nullptr;
     const size_t slots0 = off;
     for (int i = 0; i < nprob; ++i) {
         P.slots.push_back(P.rp[i].grid > 0 ? (char*)take(P.rp[i].slot_bytes) : nullptr);
-        njobs += (size_t)P.rp[i].grid;
     }
     P.slot_bytes = off - slots0;
-    if (!P.res.empty()) {
-        P.res_table = (char*)take(resident_batch_args_bytes<T>() * P.res.size());
-        P.job_off = (int*)take(sizeof(int) * (size_t)(P.groups + 1));
-        P.jobs = (char*)take(2 * sizeof(int) * njobs);
-    }
+    for (int c = 0; c < 2; ++c)
+        if (nres[c]) {
+            P.res[c].table = (char*)take(resident_batch_args_bytes<T>() * nres[c]);
+            P.res[c].job_off = (int*)take(sizeof(int) * (size_t)(P.groups + 1));
+            P.res[c].jobs = (char*)take(2 * sizeof(int) * njobs[c]);
+        }
     P.bytes = off;
+    choose_forms(P, 0);
     return true;
 }
 
@@ -149,16 +178,16 @@ double expected_iterations(const Layout& L) { return std::sqrt((double)std::max(
 
 // The job lists of the resident launch: problems in order of decreasing
 // expected duration (wider ones first among equals), each on the workgroups
-// that are free first. off: P.groups + 1 offsets; jobs: (index in P.res,
+// that are free first. off: P.groups + 1 offsets; jobs: (index in `of`,
 // workgroup of the problem) pairs.
 template <typename T>
-void resident_schedule(const Plan<T>& P, std::vector<int>& off, std::vector<int>& jobs) {
-    const int n = (int)P.res.size();
+void resident_schedule(const Plan<T>& P, const std::vector<int>& of, std::vector<int>& off, std::vector<int>& jobs) {
+    const int n = (int)of.size();
     std::vector<int> order(n);
     for (int k = 0; k < n; ++k) order[k] = k;
-    auto cost = [&](int k) { return P.rp[P.res[k]].us * expected_iterations(P.L[P.res[k]]); };
+    auto cost = [&](int k) { return P.rp[of[k]].us * expected_iterations(P.L[of[k]]); };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-        const int ga = P.rp[P.res[a]].grid, gb = P.rp[P.res[b]].grid;
+        const int ga = P.rp[of[a]].grid, gb = P.rp[of[b]].grid;
         return ga != gb ? ga > gb : cost(a) > cost(b);
     });
     std::vector<std::vector<int>> list(P.groups);
@@ -166,7 +195,7 @@ void resident_schedule(const Plan<T>& P, std::vector<int>& off, std::vector<int>
     std::vector<int> by(P.groups);
     for (int g = 0; g < P.groups; ++g) by[g] = g;
     for (int k : order) {
-        const int G = P.rp[P.res[k]].grid;
+        const int G = P.rp[of[k]].grid;
         std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return free_at[a] < free_at[b]; });
         const double end = free_at[by[G - 1]] + cost(k);
         std::vector<int> gang(by.begin(), by.begin() + G);
@@ -284,37 +313,51 @@ pb_status enqueue_batch(const Plan<T>& P, const pb_problem* probs, int grid, boo
 // dictionary when `coded`, and its fit flag when coded == 2).
 template <typename T>
 pb_status fill_table(const Plan<T>& P, const pb_problem* probs, int coded, hipStream_t st) {
-    std::vector<char> host(batch_kargs_bytes<T>() * P.str.size()), rhost(resident_batch_args_bytes<T>() * P.res.size());
-    size_t ns = 0, nr = 0;
-    for (int i = 0; i < P.nprob; ++i) {
+    auto args = [&](int i, auto&& fill) {
         const int maxiter = probs[i].maxiter > 0 ? probs[i].maxiter
                                                  : 10 * std::max(probs[i].nx, std::max(probs[i].ny, probs[i].nz));
-        const float* cw = coded ? (const float*)P.s[i].q2 : nullptr;
-        const float* tab = coded ? dictionary_table(P.s[i].q) : nullptr;
-        const int* fit = coded == 2 ? P.fit + i : nullptr;
-        if (P.rp[i].grid > 0)
-            resident_batch_fill<T>(rhost.data() + resident_batch_args_bytes<T>() * nr++, P.L[i], P.s[i], &P.sync[i],
-                                   P.slots[i], probs[i].tol, maxiter, (int)P.res.size(), cw, tab, fit);
-        else
-            batch_fill_kargs<T>(host.data() + batch_kargs_bytes<T>() * ns++, P.L[i], P.s[i], &P.sync[i], P.partials[i],
-                                P.t[i], probs[i].tol, maxiter, 0, 0, cw, tab, fit);
+        fill(maxiter, coded ? (const float*)P.s[i].q2 : nullptr, coded ? dictionary_table(P.s[i].q) : nullptr,
+             coded == 2 ? (const int*)(P.fit + i) : nullptr);
+    };
+    std::vector<char> host(batch_kargs_bytes<T>() * P.str.size()), rhost[2];
+    for (size_t k = 0; k < P.str.size(); ++k) {
+        const int i = P.str[k];
+        args(i, [&](int maxiter, const float* cw, const float* tab, const int* fit) {
+            batch_fill_kargs<T>(host.data() + batch_kargs_bytes<T>() * k, P.L[i], P.s[i], &P.sync[i], P.partials[i],
+                                P.t[i], probs[i].tol, maxiter, 0, 0, cw, tab, fit, P.rp[i].compact && coded == 2);
+        });
     }
-    if (ns) PB_HIP(hipMemcpyAsync(P.table, host.data(), host.size(), hipMemcpyHostToDevice, st));
-    if (nr) PB_HIP(hipMemcpyAsync(P.res_table, rhost.data(), rhost.size(), hipMemcpyHostToDevice, st));
+    for (int c = 0; c < 2; ++c) {
+        const auto& f = P.res[c];
+        rhost[c].resize(resident_batch_args_bytes<T>() * f.of.size());
+        for (size_t k = 0; k < f.of.size(); ++k) {
+            const int i = f.of[k];
+            args(i, [&](int maxiter, const float* cw, const float* tab, const int* fit) {
+                resident_batch_fill<T>(rhost[c].data() + resident_batch_args_bytes<T>() * k, P.L[i], P.s[i], &P.sync[i],
+                                       P.slots[i], probs[i].tol, maxiter, (int)f.of.size(), cw, tab, fit);
+            });
+        }
+        if (!f.of.empty())
+            PB_HIP(hipMemcpyAsync(f.table, rhost[c].data(), rhost[c].size(), hipMemcpyHostToDevice, st));
+    }
+    if (!host.empty()) PB_HIP(hipMemcpyAsync(P.table, host.data(), host.size(), hipMemcpyHostToDevice, st));
     PB_HIP(hipStreamSynchronize(st));
     return PB_OK;
 }
 
-// The solves: one resident launch, then one streaming launch, each over the
-// problems of its form. grid: workgroups of the streaming launch.
+// The solves: a launch of each resident form, then a streaming one, each over
+// the problems of its form. grid: workgroups of the streaming launch.
 template <typename T>
 pb_status launch_solves(const Plan<T>& P, int grid, hipStream_t st, bool cooperative, int coded) {
-    if (!P.res.empty()) {
-        pb_status e = launch_fill<int>((int*)P.all_slots, (int64_t)(P.slot_bytes / sizeof(int)), 0, st);
-        if (e != PB_OK) return e;
-        for (int i : P.res)
+    pb_status e = PB_OK;
+    if (P.slot_bytes > 0) e = launch_fill<int>((int*)P.all_slots, (int64_t)(P.slot_bytes / sizeof(int)), 0, st);
+    if (e != PB_OK) return e;
+    for (int c = 0; c < 2; ++c) {
+        const auto& f = P.res[c];
+        if (f.of.empty()) continue;
+        for (int i : f.of)
             if ((e = resident_batch_start<T>(P.L[i], P.s[i], st)) != PB_OK) return e;
-        e = resident_batch_launch<T>(P.res_table, P.job_off, P.jobs, P.groups, P.res_lds, st, cooperative);
+        e = resident_batch_launch<T>(f.table, f.job_off, f.jobs, P.groups, f.lds, c == 1, st, cooperative);
         if (e != PB_OK) return e;
     }
     if (P.str.empty()) return PB_OK;
@@ -322,11 +365,13 @@ pb_status launch_solves(const Plan<T>& P, int grid, hipStream_t st, bool coopera
                            cooperative, coded);
 }
 
-// Upload the per-problem kernel arguments and workgroup offsets.
+// Settle the forms for `coded` (choose_forms) and upload the per-problem kernel
+// arguments, the workgroup offsets and the job lists.
 template <typename T>
-pb_status upload_table(const Plan<T>& P, const pb_problem* probs, int& grid, hipStream_t st) {
+pb_status upload_table(Plan<T>& P, const pb_problem* probs, int& grid, int coded, hipStream_t st) {
     grid = 0;
-    std::vector<int> first, off, jobs;
+    choose_forms(P, coded);
+    std::vector<int> first;
     // a batch holds at most as many problems as the streaming form has
     // co-resident workgroups, whatever form its problems run in
     if (const int most = batch_capacity<T>(P.str_lds); most < P.nprob) {
@@ -334,7 +379,7 @@ pb_status upload_table(const Plan<T>& P, const pb_problem* probs, int& grid, hip
         return PB_ERR_ARG;
     }
     if (!P.str.empty()) {
-        const int cap = batch_capacity<T>(P.lds);
+        const int cap = batch_capacity<T>(P.lds, coded);
         std::vector<Layout> L;
         std::vector<Tiling> t;
         for (int i : P.str) {
@@ -345,12 +390,25 @@ pb_status upload_table(const Plan<T>& P, const pb_problem* probs, int& grid, hip
         grid = first.back();
         PB_HIP(hipMemcpyAsync(P.first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice, st));
     }
-    if (!P.res.empty()) {
-        resident_schedule<T>(P, off, jobs);
-        PB_HIP(hipMemcpyAsync(P.job_off, off.data(), sizeof(int) * off.size(), hipMemcpyHostToDevice, st));
-        PB_HIP(hipMemcpyAsync(P.jobs, jobs.data(), sizeof(int) * jobs.size(), hipMemcpyHostToDevice, st));
+    std::vector<int> off[2], jobs[2];
+    for (int c = 0; c < 2; ++c) {
+        const auto& f = P.res[c];
+        if (f.of.empty()) continue;
+        resident_schedule<T>(P, f.of, off[c], jobs[c]);
+        PB_HIP(hipMemcpyAsync(f.job_off, off[c].data(), sizeof(int) * off[c].size(), hipMemcpyHostToDevice, st));
+        PB_HIP(hipMemcpyAsync(f.jobs, jobs[c].data(), sizeof(int) * jobs[c].size(), hipMemcpyHostToDevice, st));
     }
-    return fill_table<T>(P, probs, 0, st);
+    return fill_table<T>(P, probs, coded, st);
+}
+
+// Whether every problem of the batch can have code words: the arrays that hold
+// them are large enough, and the coded streaming kernel takes as many problems.
+template <typename T>
+bool can_code(const Plan<T>& P, int coded) {
+    if (sizeof(T) != sizeof(float) || !coded_coefficients()) return false;
+    for (const Layout& L : P.L)
+        if (!coded_layout_ok(L)) return false;
+    return batch_capacity<T>(P.str_lds + kCodedLdsBytes, coded) >= P.nprob;
 }
 
 // The direct (not graph-recorded) batch: as enqueue_batch, with coded
@@ -360,7 +418,7 @@ pb_status upload_table(const Plan<T>& P, const pb_problem* probs, int& grid, hip
 // problem's q2 and the dictionary to its q (the batch's pass form uses
 // neither).
 template <typename T>
-pb_status enqueue_batch_direct(const Plan<T>& P, const pb_problem* probs, int grid, hipStream_t st, bool& coded) {
+pb_status enqueue_batch_direct(Plan<T>& P, const pb_problem* probs, hipStream_t st, bool& coded) {
     coded = false;
     pb_status e = launch_fill<int>((int*)P.rec, (int64_t)(sizeof(ProbRec) / sizeof(int)) * P.nprob, 0, st);
     if (e != PB_OK) return e;
@@ -369,8 +427,7 @@ pb_status enqueue_batch_direct(const Plan<T>& P, const pb_problem* probs, int gr
     e = enqueue_prepare<T>(P, probs, st);
     if (e != PB_OK) return e;
     if constexpr (sizeof(T) == sizeof(float)) {
-        bool can = coded_coefficients() != 0 && (P.str.empty() || batch_capacity<T>(P.lds + kCodedLdsBytes, true) >= grid);
-        for (int i = 0; i < P.nprob && can; ++i) can = coded_layout_ok(P.L[i]);
+        bool can = can_code(P, 1);
         if (can) {
             for (int i = 0; i < P.nprob; ++i) {
                 e = enqueue_dictionary(P.s[i].op, P.L[i].npad, (void*)P.s[i].q, P.fit + i, st);
@@ -386,11 +443,12 @@ pb_status enqueue_batch_direct(const Plan<T>& P, const pb_problem* probs, int gr
                 e = enqueue_encode(P.s[i].op, P.L[i].npad, P.s[i].q, (uint32_t*)P.s[i].q2, st);
                 if (e != PB_OK) return e;
             }
-            e = fill_table<T>(P, probs, 1, st);
-            if (e != PB_OK) return e;
             coded = true;
         }
     }
+    int grid = 0;
+    e = upload_table<T>(P, probs, grid, coded ? 1 : 0, st);
+    if (e != PB_OK) return e;
     e = launch_solves<T>(P, grid, st, true, coded);
     if (e != PB_OK) return e;
     return enqueue_finish<T>(P, probs, st);
@@ -436,15 +494,12 @@ pb_status solve_batch_impl(int nprob, const pb_problem* probs, void* ws, size_t 
         set_error("pb_solve_batch: workspace of %zu bytes, %zu needed", wsb, P.bytes);
         return PB_ERR_NOMEM;
     }
-    int grid = 0;
-    pb_status e = upload_table<T>(P, probs, grid, st);
-    if (e != PB_OK) return e;
     hipEvent_t ev[2];
     PB_HIP(hipEventCreate(&ev[0]));
     PB_HIP(hipEventCreate(&ev[1]));
     PB_HIP(hipEventRecord(ev[0], st));
     bool coded = false;
-    e = enqueue_batch_direct<T>(P, probs, grid, st, coded);
+    pb_status e = enqueue_batch_direct<T>(P, probs, st, coded);
     if (e != PB_OK) {
         (void)hipEventDestroy(ev[0]);
         (void)hipEventDestroy(ev[1]);
@@ -493,7 +548,7 @@ pb_status batch_autotune_impl(int nprob, const pb_problem* probs, int iters, voi
             break;
         }
         int grid = 0;
-        if ((e = upload_table<T>(P, trial.data(), grid, st)) != PB_OK) break;
+        if ((e = upload_table<T>(P, trial.data(), grid, 0, st)) != PB_OK) break;
         if ((e = launch_fill<int>((int*)P.rec, (int64_t)(sizeof(ProbRec) / sizeof(int)) * nprob, 0, st)) != PB_OK) break;
         if ((e = launch_fill<int>((int*)P.sync, (int64_t)(sizeof(SyncState) / sizeof(int)) * nprob, 0, st)) != PB_OK) break;
         if ((e = enqueue_prepare<T>(P, trial.data(), st)) != PB_OK) break;
@@ -634,22 +689,12 @@ pb_status graph_build(pb_batch_graph* G, Plan<T>& P, void* ws, size_t wsb, hipSt
         set_error("pb_batch_graph_create: workspace of %zu bytes, %zu needed", wsb, P.bytes);
         return PB_ERR_NOMEM;
     }
-    int grid = 0;
-    pb_status e = upload_table<T>(P, G->probs.data(), grid, st);
-    if (e != PB_OK) return e;
     // coded coefficients, decided on the device at every replay (the
     // coefficients may change between replays)
-    G->coded = 0;
-    if constexpr (sizeof(T) == sizeof(float)) {
-        bool can = coded_coefficients() != 0 &&
-                   (P.str.empty() || batch_capacity<T>(P.lds + kCodedLdsBytes, 2) >= grid);
-        for (int i = 0; i < P.nprob && can; ++i) can = coded_layout_ok(P.L[i]);
-        if (can) {
-            e = fill_table<T>(P, G->probs.data(), 2, st);
-            if (e != PB_OK) return e;
-            G->coded = 2;
-        }
-    }
+    G->coded = can_code(P, 2) ? 2 : 0;
+    int grid = 0;
+    pb_status e = upload_table<T>(P, G->probs.data(), grid, G->coded, st);
+    if (e != PB_OK) return e;
     hipStream_t cs;
     PB_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     for (int attempt = 0; attempt < 2; ++attempt) {

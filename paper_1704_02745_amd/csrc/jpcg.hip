@@ -86,6 +86,7 @@ struct KArgs {
     const float* cw;     // coded 40-byte pass: one word of coefficient codes per position (bit patterns)
     const float* ctab;   // and the dictionary (kCodedTableSize values)
     const int* fit;      // runtime-checked coded launches: 1 when this problem's dictionary holds its operator
+    int unless_fit;      // 1: nothing to do when it does (another launch solved the problem)
 };
 
 // LDS scratch of the reductions below, in doubles.
@@ -1765,6 +1766,7 @@ __global__ __launch_bounds__(BS) void k_jpcg_batch(const KArgs<T>* __restrict__ 
         if (first[mid] <= (int)blockIdx.x) lo = mid; else hi = mid;
     }
     const KArgs<T> a = probs[lo];
+    if (a.unless_fit && *a.fit == 1) return;
     // coded launches: every problem's arguments carry its code words and
     // dictionary (and, runtime-checked, its fit flag)
     run_problem<T, BS, MC, SCH, false, NT, CD, RT>(a, blockIdx.x - first[lo], first[lo + 1] - first[lo], false,
@@ -2173,8 +2175,19 @@ pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, do
                      int maxiter, hipStream_t st, SolveResult* res, const Tiling* force, int periodic) {
     if (force ? force->resident != 0 : !streaming_asked<T>(L, periodic)) {
         bool ran = false;
-        const pb_status e = resident_jpcg<T>(L, s, sync, partials, tol, maxiter, st, res, periodic, ran);
+        pb_status e = resident_jpcg<T>(L, s, sync, partials, tol, maxiter, st, res, periodic, nullptr, nullptr, ran);
         if (e != PB_OK || ran) return e;
+        if constexpr (sizeof(T) == 4) {
+            if (coded_coefficients() && s.q && s.q2 && coded_layout_ok(L) && resident_fits<T>(L, periodic, true)) {
+                bool fits = s.codes_valid != 0;
+                const float* tab = s.ctab;
+                if (!fits) e = build_codes(s.op, L.npad, (void*)s.q, (uint32_t*)s.q2, st, fits, &tab);
+                if (e == PB_OK && fits)
+                    e = resident_jpcg<T>(L, s, sync, partials, tol, maxiter, st, res, periodic,
+                                         (const uint32_t*)s.q2, tab, ran);
+                if (e != PB_OK || ran) return e;
+            }
+        }
     }
     const Tiling t = !periodic && force && force->grid > 0 ? *force : solve_tiling<T>(L, periodic);
     if (t.grid <= 0) {
@@ -2415,7 +2428,7 @@ template size_t batch_kargs_bytes<double>();
 template <typename T>
 void batch_fill_kargs(void* dst, const Layout& L, const SolveBufs<T>& s, SyncState* S, double* partials,
                       const Tiling& t, double tol, int maxiter, int resume, int chunk, const float* cw,
-                      const float* ctab, const int* fit) {
+                      const float* ctab, const int* fit, bool unless_fit) {
     const DevInfo di = dev_info();
     KArgs<T> a{};
     a.op = s.op;
@@ -2442,14 +2455,15 @@ void batch_fill_kargs(void* dst, const Layout& L, const SolveBufs<T>& s, SyncSta
     a.cw = cw;
     a.ctab = ctab;
     a.fit = fit;
+    a.unless_fit = unless_fit ? 1 : 0;
     std::memcpy(dst, &a, sizeof(a));
 }
 template void batch_fill_kargs<float>(void*, const Layout&, const SolveBufs<float>&, SyncState*, double*,
                                       const Tiling&, double, int, int, int, const float*, const float*,
-                                      const int*);
+                                      const int*, bool);
 template void batch_fill_kargs<double>(void*, const Layout&, const SolveBufs<double>&, SyncState*, double*,
                                        const Tiling&, double, int, int, int, const float*, const float*,
-                                       const int*);
+                                       const int*, bool);
 
 // Co-resident workgroups of the batch kernel with `lds` bytes of dynamic LDS.
 template <typename T>

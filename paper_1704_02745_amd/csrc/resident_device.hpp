@@ -52,7 +52,7 @@ struct RArgs {
     unsigned long long* slots;   // 2 x workgroups x kSlotWords, cleared before the launch
     long long timeout_ticks;
     long long first_timeout_ticks;   // of the first barrier (a batch's workgroups come to it from earlier problems)
-    int planes;           // batch: planes per brick (the kernel's NZ)
+    T* xs;                // forms with x in memory: x by brick (one value per thread and plane)
     // batch: the operator as code words and their dictionary, read instead of
     // its arrays when given and (fit given) *fit == 1
     const uint32_t* cw;
@@ -61,6 +61,9 @@ struct RArgs {
 };
 
 constexpr int kSlotWords = 16;            // two words per sum (low half, high half), 8 sums
+// Barrier words are reached through global-memory instructions also where the
+// compiler cannot see the pointer's origin (a batch's argument table).
+typedef __attribute__((address_space(1))) unsigned long long GlobalWord;
 constexpr int kMaxResidentGroups = 256;   // workgroups that the poll of one barrier covers
 
 // The value, unknown to the optimizer: keeps what is derived from it (1/d,
@@ -70,6 +73,7 @@ __device__ __forceinline__ int opaque_v(int v) {
     return v;
 }
 __device__ __forceinline__ int opaque_s(int v) {   // v uniform over the wave
+    v = __builtin_amdgcn_readfirstlane(v);
     asm volatile("" : "+s"(v));
     return v;
 }
@@ -78,7 +82,10 @@ __device__ __forceinline__ float opaque_v(float v) {
     asm volatile("" : "+v"(v));
     return v;
 }
-__device__ __forceinline__ double opaque_v(double v) { return v; }
+__device__ __forceinline__ double opaque_v(double v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
 
 constexpr int kDppRor4 = 0x124;   // lane i of 16 reads a lane 4 away (cyclic)
 
@@ -138,6 +145,19 @@ __device__ __forceinline__ uint32_t word_load(Rsrc r, uint32_t off) {
 __device__ __forceinline__ void agent_store(Rsrc r, uint32_t off, float v) {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, (int)off, 0, kAgentScope);
 }
+// x by brick: one address register per thread, the plane in the scalar offset.
+__device__ __forceinline__ float x_get(Rsrc r, uint32_t off, int plane, float) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, plane, 0));
+}
+__device__ __forceinline__ void x_put(Rsrc r, uint32_t off, int plane, float v) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), r, (int)off, plane, 0);
+}
+__device__ __forceinline__ double x_get(Rsrc r, uint32_t off, int plane, double) {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, plane, 0));
+}
+__device__ __forceinline__ void x_put(Rsrc r, uint32_t off, int plane, double v) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, plane, 0);
+}
 __device__ __forceinline__ void agent_store(Rsrc r, uint32_t off, double v) {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, kAgentScope);
 }
@@ -146,40 +166,46 @@ __device__ __forceinline__ void agent_store(Rsrc r, uint32_t off, double v) {
 // two y-faces of tx * NZ, two z-faces of one value per thread.
 __host__ __device__ constexpr int face_len(int bs, int nzb, int tx, int ty) { return 2 * (tx + ty) * nzb + 2 * bs; }
 
-// One in-plane halo node: its r and 1/d, where its q is published (byte offset
-// in the faces) and the LDS element of its p.
-template <typename T>
-struct HaloNode {
-    T r, inv;
-    uint32_t from;
-    int p;
-};
-
 // LDS of one workgroup, in bytes: the reduction scratch, p by columns (the NZ
 // values of a column together, at an odd stride, so that a lane's accesses
 // are one address plus constants and the lanes fall into different banks) over
-// the tile and its halo, and the halo nodes.
+// the tile and its halo, and r and 1/d of the halo.
 // Whether the couplings to the lower x and y neighbours sit in LDS (each thread
 // its own) instead of registers: from 17 planes of FP32 or 9 of FP64 on the
 // rest of the state fills the 256 registers of a thread and they would spill
 // (129^3, 19 planes: 13.1 us per iteration with the spills, 7.5 without).
 template <typename T>
-__host__ __device__ constexpr bool lower_in_lds(int bs, int nzb) { return nzb > (sizeof(T) == 4 ? 16 : 8); }
+__host__ __device__ constexpr bool lower_in_lds(int bs, int nzb) { return nzb > (sizeof(T) == 4 ? 14 : 6); }
+// Whether x goes to memory by brick instead of registers (each thread reads and
+// writes its own values once per pass; they stay in the XCD's L2): the compact
+// form, and FP64 from 7 planes on (97 x 105 x 89, 8 planes: 14.0 us per
+// iteration with x in registers and 36 of them spilled).
 template <typename T>
-__host__ __device__ constexpr size_t resident_lds_bytes(int bs, int nzb, int tx, int ty) {
-    return (lower_in_lds<T>(bs, nzb) ? sizeof(T) * 2 * (size_t)bs * nzb : 0) + sizeof(double) * (size_t)(bs / 64) * 4 * 8 * 2 + 256 +
-           (sizeof(T) * (size_t)(nzb | 1) * (tx + 2) * (ty + 2) + 15) / 16 * 16 +
-           sizeof(HaloNode<T>) * (size_t)nzb * 2 * (tx + ty);
+__host__ __device__ constexpr bool x_in_memory(int nzb, bool compact) {
+    return compact || (sizeof(T) == 8 && nzb > 6);
+}
+template <typename T>
+__host__ __device__ constexpr size_t resident_lds_bytes(int bs, int nzb, int tx, int ty, bool compact) {
+    return (!compact && lower_in_lds<T>(bs, nzb) ? sizeof(T) * 2 * (size_t)bs * nzb : 0) +
+           sizeof(double) * (size_t)(bs / 64) * 4 * 8 * 2 + 256 +
+           sizeof(T) * ((size_t)(nzb | 1) * (tx + 2) * (ty + 2) + (size_t)nzb * 4 * (tx + ty));
 }
 
 // The whole solve of one problem by workgroup `w` of its nxt * nyt * nzc.
-template <typename T, int BS, int NZ, bool PER>
+//
+// CP, the compact form (FP32, operator given as code words): for bricks whose
+// state does not fit the registers. A node keeps r, q and six bytes of codes
+// there, decoded through the dictionary in LDS where they are used; x goes to
+// memory (x_in_memory). The operations and their order are the same.
+template <typename T, int BS, int NZ, bool PER, bool CP = false>
 __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_raw) {
 #pragma clang fp contract(off)
     constexpr int ROWS = BS / 64 * 4;
     constexpr int E = (int)sizeof(T);
     // 1/d kept beside d where the registers allow
-    constexpr bool LL = lower_in_lds<T>(BS, NZ);
+    static_assert(!CP || E == 4, "code words are FP32");
+    constexpr bool LL = !CP && lower_in_lds<T>(BS, NZ);
+    constexpr bool XM = x_in_memory<T>(NZ, CP);
     constexpr bool KEEP = E == 8 || NZ <= (LL ? 17 : 12);
     constexpr int SZ = NZ | 1;   // LDS stride of a column
     const int G = a.nxt * a.nyt * a.nzc;
@@ -199,11 +225,25 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
     double* red = reinterpret_cast<double*>(lds_raw);
     double* red2 = red + ROWS * 8;
     int* s_flag = reinterpret_cast<int*>(red2 + ROWS * 8);
-    T* P = reinterpret_cast<T*>(lds_raw + sizeof(double) * ROWS * 16 + 256);
-    HaloNode<T>* HN = reinterpret_cast<HaloNode<T>*>(
-        lds_raw + sizeof(double) * ROWS * 16 + 256 + (sizeof(T) * (size_t)SZ * row * (a.ty + 2) + 15) / 16 * 16);
-
-    T* const CL = reinterpret_cast<T*>(HN + (size_t)NZ * 2 * (a.tx + a.ty)) + tid;   // LL: x and y of plane kk at 2kk, 2kk+1
+    T* const P = reinterpret_cast<T*>(lds_raw + sizeof(double) * ROWS * 16 + 256);
+    T* const RH = P + (size_t)SZ * row * (a.ty + 2);
+    T* const IH = RH + (size_t)NZ * 2 * (a.tx + a.ty);
+    T* const CL = IH + (size_t)NZ * 2 * (a.tx + a.ty) + tid;   // LL: x and y of plane kk at 2kk, 2kk+1
+    // CP: dictionary and 1/dictionary, at an address known to the compiler (a
+    // lookup is one shift of a code byte and one LDS read)
+    T *tv = nullptr, *ti = nullptr;
+    if constexpr (CP) {
+        __shared__ T s_dict[2 * kCodedTableSize];
+        tv = s_dict;
+        ti = s_dict + kCodedTableSize;
+        if (a.fit && *a.fit != 1) return;   // the operator does not fit the dictionary: the streaming form solves it
+        for (int n = tid; n < kCodedTableSize; n += BS) {
+            const T c = (T)a.ctab[n];
+            tv[n] = c;
+            ti[n] = c == T(0) ? T(0) : jacobi_inv(c);   // 0 is read for the diagonal where there is no node
+        }
+        __syncthreads();
+    }
 
     // p of this thread's column and of the four around it. With one brick
     // along a periodic axis the neighbour across the end is in the tile itself.
@@ -215,64 +255,79 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
     const T* const pU = !valid ? pl : wrap_y && j == ny - 1 ? pl - SZ * row * (ny - 1) : pl + SZ * row;
     const T* const pD = !valid ? pl : wrap_y && j == 0 ? pl + SZ * row * (ny - 1) : pl - SZ * row;
 
-    const bool coded = E == 4 && a.cw && (!a.fit || *a.fit == 1);
+    const bool coded = CP || (E == 4 && a.cw && (!a.fit || *a.fit == 1));
     auto decode = [&](uint32_t c, int byte) -> T { return (T)a.ctab[(c >> (8 * byte)) & 255u]; };
     auto diag_at = [&](int64_t g) -> T { return coded ? decode(a.cw[g], 3) : a.op.d[g]; };
     // ---- the operator and the state of the own nodes
-    T r[NZ], x[NZ], q[NZ], cx[NZ], cy[NZ], cz[NZ], d[NZ], iv[KEEP ? NZ : 1];
-    T cxm[LL ? 1 : NZ], cym[LL ? 1 : NZ];
+    constexpr int NR = CP ? 1 : NZ;   // held in registers by the full form alone
+    T r[NZ], q[NZ];
+    T x[XM ? 1 : NZ], cx[NR], cy[NR], cz[NR], d[NR], iv[KEEP && !CP ? NZ : 1], cxm[LL ? 1 : NR], cym[LL ? 1 : NR];
+    uint32_t w1[CP ? NZ : 1], w2[CP ? (NZ + 1) / 2 : 1];   // codes: x+, x-, y+, y-; z+, d of two planes
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    // XM: x of plane kk at xoff + kk * BS elements
+    const Rsrc xs = rsrc_of(XM ? a.xs + (size_t)w * NZ * BS : a.x, XM ? NZ * BS : 0);
+    const uint32_t xoff = (uint32_t)tid * E;
     {
         // positions without a node and planes past nk read as zero
-        auto from = [&](const T* p) { return rsrc_of(p + (int64_t)k0 * sp, (int64_t)nk * sp); };
+        auto from = [&](const void* p) { return rsrc_of((const T*)p + (int64_t)k0 * sp, (int64_t)nk * sp); };
         const Rsrc rcx = from(a.op.cx), rcy = from(a.op.cy), rcz = from(a.op.cz), rd = from(a.op.d), rr0 = from(a.r0),
-                   rb0 = from(a.b), rx = from(a.x);
-        const Rsrc rcw = rsrc_of((const T*)a.cw + (int64_t)k0 * sp, (int64_t)nk * sp);
+                   rb0 = from(a.b), rx = from(a.x), rcw = from(a.cw);
         auto at = [&](bool in, int p) { return valid && in ? (uint32_t)p * E : kNowhere; };
         uint32_t o = at(true, pos), ox = at(i > 0 || PER, i > 0 ? pos - 1 : pos + nx - 1),
                  oy = at(j > 0 || PER, j > 0 ? pos - nx : pos + (ny - 1) * nx);
         const uint32_t plane_bytes = (uint32_t)(sp * E);
 #pragma unroll
         for (int kk = 0; kk < NZ; ++kk) {
-            T cxl, cyl;
-            if (coded) {   // words at kNowhere read as 0, the code of 0
-                const uint32_t c = word_load(rcw, o);
-                cx[kk] = decode(c, 0);
-                cy[kk] = decode(c, 1);
-                cz[kk] = decode(c, 2);
-                d[kk] = decode(c, 3);
-                cxl = decode(word_load(rcw, ox), 0);
-                cyl = decode(word_load(rcw, oy), 1);
+            if constexpr (CP) {   // words at kNowhere read as 0, the code of 0
+                const uint32_t c = word_load(rcw, o), cl = word_load(rcw, ox), cd = word_load(rcw, oy);
+                w1[kk] = (c & 0xffu) | (cl & 0xffu) << 8 | (c & 0xff00u) << 8 | (cd & 0xff00u) << 16;
+                if (kk % 2 == 0) w2[kk / 2] = c >> 16;
+                else w2[kk / 2] |= c & 0xffff0000u;
             } else {
-                cx[kk] = bload<0>(rcx, o, T());
-                cy[kk] = bload<0>(rcy, o, T());
-                cz[kk] = bload<0>(rcz, o, T());
-                d[kk] = bload<0>(rd, o, T());
-                cxl = bload<0>(rcx, ox, T());
-                cyl = bload<0>(rcy, oy, T());
+                T cxl, cyl;
+                if (coded) {
+                    const uint32_t c = word_load(rcw, o);
+                    cx[kk] = decode(c, 0);
+                    cy[kk] = decode(c, 1);
+                    cz[kk] = decode(c, 2);
+                    d[kk] = decode(c, 3);
+                    cxl = decode(word_load(rcw, ox), 0);
+                    cyl = decode(word_load(rcw, oy), 1);
+                } else {
+                    cx[kk] = bload<0>(rcx, o, T());
+                    cy[kk] = bload<0>(rcy, o, T());
+                    cz[kk] = bload<0>(rcz, o, T());
+                    d[kk] = bload<0>(rd, o, T());
+                    cxl = bload<0>(rcx, ox, T());
+                    cyl = bload<0>(rcy, oy, T());
+                }
+                if constexpr (LL) {
+                    CL[2 * kk * BS] = cxl;
+                    CL[(2 * kk + 1) * BS] = cyl;
+                } else {
+                    cxm[kk] = cxl;
+                    cym[kk] = cyl;
+                }
+                if (d[kk] == T(0)) d[kk] = T(1);
+                if constexpr (KEEP) iv[kk] = jacobi_inv(d[kk]);
             }
-            if constexpr (LL) {
-                CL[2 * kk * BS] = cxl;
-                CL[(2 * kk + 1) * BS] = cyl;
-            } else {
-                cxm[kk] = cxl;
-                cym[kk] = cyl;
-            }
+            const T xv = bload<0>(rx, a.warm ? o : kNowhere, T());
+            if constexpr (XM) x_put(xs, xoff, kk * BS * E, xv);
+            else x[kk] = xv;
             r[kk] = bload<0>(rr0, o, T());
-            x[kk] = bload<0>(rx, a.warm ? o : kNowhere, T());
             q[kk] = T(0);
             const T bv = bload<0>(rb0, o, T());
-            if (d[kk] == T(0)) d[kk] = T(1);
             acc[0] = fma((double)r[kk], (double)r[kk], acc[0]);
             acc[1] = fma((double)bv, (double)bv, acc[1]);
-            if constexpr (KEEP) iv[kk] = jacobi_inv(d[kk]);
             o += plane_bytes;
             ox += plane_bytes;
             oy += plane_bytes;
+            if (kk % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
     }
     auto inv = [&](int kk) -> T {
-        if constexpr (KEEP) return iv[kk];
+        if constexpr (CP) return ti[(w2[kk / 2] >> (kk % 2 ? 24 : 8)) & 255u];
+        else if constexpr (KEEP) return iv[kk];
         else return jacobi_inv(opaque_v(d[kk]));
     };
     // planes below and above the brick, in this thread's column
@@ -316,41 +371,43 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
     const uint32_t off_b = valid && has_b ? brick(bx, by, bz - 1) + zhi : kNowhere;
     const uint32_t off_t = valid && has_t ? brick(bx, by, bz + 1) + zlo : kNowhere;
     const int64_t face_elems = (int64_t)G * face_len(BS, NZ, a.tx, a.ty);
-    // in-plane halo nodes, in the order of the faces they are read from
-    const int hx = face_x ? 2 * FX : 0, hn = hx + (face_y ? 2 * FY : 0);
-    for (int h = tid; h < SZ * row * (a.ty + 2); h += BS) P[h] = T(0);
-    for (int h = tid; h < hn; h += BS) {
-        HaloNode<T> n{T(0), T(0), kNowhere, 0};
-        const bool alongx = h < hx;
-        const int F = alongx ? FX : FY, g = alongx ? h : h - hx, hi = g >= F ? 1 : 0, l = g - hi * F;
-        const int stride = alongx ? a.ty : a.tx, kk = l / stride, c = l - kk * stride;
+    // in-plane halo: column c of hc (x-, x+, y-, y+ neighbours) is kept by the
+    // threads c + hc * m, planes m, m + hgroups, ... each
+    const int hxc = face_x ? 2 * a.ty : 0, hc = hxc + (face_y ? 2 * a.tx : 0);
+    const int hgroups = hc > 0 ? BS / hc : 0;   // at least 1 (host)
+    const int hk0 = hc > 0 ? tid / hc : 0, hcol = tid - hk0 * hc;
+    bool hon = hc > 0 && hk0 < hgroups;
+    uint32_t hfrom = kNowhere;   // byte offset of plane 0's value in the faces
+    int hpos = 0;                // plane position of the column's nodes
+    T* hP = P;
+    if (hon) {
+        const bool alongx = hcol < hxc;
+        const int side = alongx ? a.ty : a.tx, g = alongx ? hcol : hcol - hxc, hi = g >= side ? 1 : 0, c = g - hi * side;
         int hi_i, hi_j, col;
-        uint32_t there;
-        bool in;
         if (alongx) {
-            in = c < wy && (PER || (hi ? x1 < nx : x0 > 0));
+            hon = c < wy && (PER || (hi ? x1 < nx : x0 > 0));
             hi_i = hi ? (x1 < nx ? x1 : 0) : (x0 > 0 ? x0 - 1 : nx - 1);
             hi_j = y0 + c;
             col = (c + 1) * row + (hi ? wx + 1 : 0);
-            there = brick(bx + (hi ? 1 : -1), by, bz) + (uint32_t)((hi ? 0 : FX) + l) * E;
+            hfrom = brick(bx + (hi ? 1 : -1), by, bz) + (uint32_t)((hi ? 0 : FX) + c) * E;
         } else {
-            in = c < wx && (PER || (hi ? y1 < ny : y0 > 0));
+            hon = c < wx && (PER || (hi ? y1 < ny : y0 > 0));
             hi_j = hi ? (y1 < ny ? y1 : 0) : (y0 > 0 ? y0 - 1 : ny - 1);
             hi_i = x0 + c;
             col = (hi ? wy + 1 : 0) * row + c + 1;
-            there = brick(bx, by + (hi ? 1 : -1), bz) + (uint32_t)(2 * FX + (hi ? 0 : FY) + l) * E;
+            hfrom = brick(bx, by + (hi ? 1 : -1), bz) + (uint32_t)(2 * FX + (hi ? 0 : FY) + c) * E;
         }
-        n.p = SZ * col + kk;
-        if (in && kk < nk) {
-            const int64_t g0 = (int64_t)(k0 + kk) * sp + (int64_t)hi_j * nx + hi_i;
-            n.r = a.r0[g0];
-            n.inv = jacobi_inv(diag_at(g0));
-            n.from = there;
-        } else {
-            n.p = kk;   // a corner column, whose p stays zero (1/d = 0)
-        }
-        HN[h] = n;
+        hpos = hi_j * nx + hi_i;
+        hP = P + SZ * col;
     }
+    const uint32_t hstride = (uint32_t)((hcol < hxc ? a.ty : a.tx) * E);   // bytes from plane to plane
+    for (int h = tid; h < SZ * row * (a.ty + 2); h += BS) P[h] = T(0);
+    if (hon)
+        for (int kk = hk0; kk < nk; kk += hgroups) {
+            const int64_t g = (int64_t)(k0 + kk) * sp + hpos;
+            RH[kk * hc + hcol] = a.r0[g];
+            IH[kk * hc + hcol] = jacobi_inv(diag_at(g));
+        }
 
     // ---- grid barrier with the reduction of the sums in acc; the totals in
     // every thread
@@ -361,12 +418,12 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's face values have arrived
         __syncthreads();
         const unsigned tag = (unsigned)(b + 1);
-        unsigned long long* slots = a.slots + (size_t)(b & 1) * G * kSlotWords;
+        GlobalWord* slots = (GlobalWord*)(uintptr_t)a.slots + (size_t)(b & 1) * G * kSlotWords;
         if (wave == 0) {
             const double v = lds_rows_sum8(red, ROWS);
             if (lane < 8) {
                 const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-                unsigned long long* m = slots + (size_t)w * kSlotWords + 2 * lane;
+                GlobalWord* m = slots + (size_t)w * kSlotWords + 2 * lane;
                 __hip_atomic_store(m, (u << 32) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(m + 1, (u & 0xffffffff00000000ull) | tag, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
@@ -384,7 +441,7 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
                 for (int m = 0; m < M; ++m) {
                     if (m > 0 && m * (BS / 8) >= G) break;   // uniform
                     const int slot = min((tid >> 3) + m * (BS / 8), G - 1);
-                    const unsigned long long* p = slots + (size_t)slot * kSlotWords + 2 * (tid & 7);
+                    const GlobalWord* p = slots + (size_t)slot * kSlotWords + 2 * (tid & 7);
                     lo[m] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     hi[m] = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
@@ -432,6 +489,7 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
     else if (sqrt(rr) / sqrt_bb < a.tol) { done = 1; }
     else if (a.maxiter <= 0) { done = 1; status = PB_NOT_CONVERGED; }
 
+    T last = T(0);   // XM: step of the last x update
     for (int pass = 0; !done; ++pass) {
         const T al = (T)alpha, be = (T)beta;
         // ---- q of the halo, on its way while the own nodes are updated (the
@@ -442,34 +500,64 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
         const T qt = bload<kAgentScope>(qo, off_t | none, T());
         constexpr int U = E == 4 ? 4 : 2;   // halo nodes in flight per thread
         T qh[U];
-        auto fetch = [&](int h0) {
+        const uint32_t hbytes = (uint32_t)hgroups * hstride;
+        uint32_t hoff = hon ? (hfrom + (uint32_t)hk0 * hstride) | none : kNowhere;
+        int hk = hon ? hk0 : nk;
+        auto fetch = [&] {
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                qh[u] = bload<kAgentScope>(qo, (h0 + u * BS < hn ? HN[h0 + u * BS].from : kNowhere) | none, T());
+            for (int u = 0; u < U; ++u) qh[u] = bload<kAgentScope>(qo, hoff + (uint32_t)u * hbytes, T());
+            hoff += U * hbytes;
         };
-        fetch(tid);
+        fetch();
         // ---- r, p, x of the own nodes
+        if constexpr (XM) {
+            constexpr int C = 32 / E;   // x values in flight
+            T xv[C];
 #pragma unroll
-        for (int kk = 0; kk < NZ; ++kk) {
-            const T po = pl[kk];
-            r[kk] = fma(-al, q[kk], r[kk]);
-            x[kk] = fma(al, po, x[kk]);
-            pl[kk] = fma(be, po, r[kk] * inv(kk));
+            for (int u = 0; u < C && u < NZ; ++u) xv[u] = x_get(xs, xoff, u * BS * E, T());
+#pragma unroll
+            for (int k8 = 0; k8 < NZ; k8 += C) {
+                T xn[C];
+#pragma unroll
+                for (int u = 0; u < C; ++u)
+                    if (k8 + C + u < NZ) xn[u] = x_get(xs, xoff, (k8 + C + u) * BS * E, T());
+#pragma unroll
+                for (int u = 0; u < C; ++u) {
+                    const int kk = k8 + u < NZ ? k8 + u : 0;
+                    if (k8 + u >= NZ) continue;
+                    const T po = pl[kk];
+                    r[kk] = fma(-al, q[kk], r[kk]);
+                    if constexpr (CP)
+                        if (kk % 2 == 0) asm volatile("" : "+v"(w2[kk / 2]));
+                    x_put(xs, xoff, kk * BS * E, fma(al, po, xv[u]));
+                    pl[kk] = fma(be, po, r[kk] * inv(kk));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < C; ++u) xv[u] = xn[u];
+            }
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < NZ; ++kk) {
+                const T po = pl[kk];
+                r[kk] = fma(-al, q[kk], r[kk]);
+                x[kk] = fma(al, po, x[kk]);
+                pl[kk] = fma(be, po, r[kk] * inv(kk));
+            }
         }
         // ---- r and p of the halo
-        for (int h0 = tid; h0 < hn;) {
+        while (hk < nk) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int h = h0 + u * BS;
-                if (h < hn) {
-                    const T rh = fma(-al, qh[u], HN[h].r);
-                    HN[h].r = rh;
-                    T* pp = P + HN[h].p;
-                    *pp = fma(be, *pp, rh * HN[h].inv);
+                if (hk < nk) {
+                    const int h = hk * hc + hcol;
+                    const T rh = fma(-al, qh[u], RH[h]);
+                    RH[h] = rh;
+                    hP[hk] = fma(be, hP[hk], rh * IH[h]);
                 }
+                hk += hgroups;
             }
-            h0 += U * BS;
-            if (h0 < hn) fetch(h0);
+            if (hk < nk) fetch();
         }
         rb = fma(-al, qb, rb);
         pb_ = fma(be, pb_, rb * ib);
@@ -480,17 +568,57 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
 #pragma unroll
         for (int k = 0; k < 8; ++k) acc[k] = 0.0;
         const Rsrc qn = rsrc_of((pass & 1) ? a.faces[1] : a.faces[0], face_elems);
-        T pm = pb_, pc = pl[0];
+        T pm = pb_, pc = pl[0], cbelow = T(0);
         uint32_t ox = opaque_v(pub_x), oy = opaque_v(pub_y);
         const int nkv = opaque_s(nk);   // compared in place, not kept as NZ masks
+        // the operator and the neighbours' p of a plane, read from LDS one plane
+        // ahead of their use; the forms that fill the registers hold the scheduler
+        // to that with a barrier after each plane (it would pull the reads of many
+        // planes ahead and spill), the others leave it free: with two waves per
+        // SIMD they need the planes' chains interleaved
+        struct Ops {
+            T right, left, up, down, above, cr, cl, cu, cd, ca, d, iv;
+        };
+        auto ops_of = [&](int kk) -> Ops {
+            Ops o;
+            o.right = pR[kk];
+            o.left = pL[kk];
+            o.up = pU[kk];
+            o.down = pD[kk];
+            o.above = kk + 1 < NZ ? pl[kk + 1 < NZ ? kk + 1 : 0] : T(0);
+            if constexpr (CP) {
+                // (in place: no copy, and no address kept across iterations)
+                asm volatile("" : "+v"(w1[kk]), "+v"(w2[kk / 2]));
+                const uint32_t c1 = w1[kk], c2 = w2[kk / 2];
+                o.cr = tv[c1 & 255u];
+                o.cl = tv[c1 >> 8 & 255u];
+                o.cu = tv[c1 >> 16 & 255u];
+                o.cd = tv[c1 >> 24];
+                o.ca = tv[(kk % 2 ? c2 >> 16 : c2) & 255u];
+                o.d = tv[(kk % 2 ? c2 >> 24 : c2 >> 8) & 255u];
+                o.iv = ti[(kk % 2 ? c2 >> 24 : c2 >> 8) & 255u];
+            } else {
+                o.cr = cx[kk];
+                o.cl = LL ? CL[2 * kk * BS] : cxm[LL ? 0 : kk];
+                o.cu = cy[kk];
+                o.cd = LL ? CL[(2 * kk + 1) * BS] : cym[LL ? 0 : kk];
+                o.ca = cz[kk];
+                o.d = d[kk];
+                o.iv = E == 8 ? opaque_v(inv(kk)) : inv(kk);   // FP64: r/d is formed again, not kept
+            }
+            return o;
+        };
+        Ops cur = ops_of(0);
 #pragma unroll
         for (int kk = 0; kk < NZ; ++kk) {
-            const T up = kk + 1 < NZ ? pl[kk + 1 < NZ ? kk + 1 : 0] : T(0);
-            const T pu = kk + 1 == NZ || kk + 1 == nkv ? pt : up;
-            T cb = kk == 0 ? czb : cz[kk > 0 ? kk - 1 : 0];
+            Ops nxt;
+            if (kk + 1 < NZ) nxt = ops_of(kk + 1 < NZ ? kk + 1 : kk);
+            const T pu = kk + 1 == NZ || kk + 1 == nkv ? pt : cur.above;
+            T cb = kk == 0 ? czb : cbelow;
             if (PER && kk > 0) cb = kk < nkv ? cb : T(0);
-            const T cl = LL ? CL[2 * kk * BS] : cxm[LL ? 0 : kk], cd = LL ? CL[(2 * kk + 1) * BS] : cym[LL ? 0 : kk];
-            const T qq = apply_point(d[kk], pc, cx[kk], pR[kk], cl, pL[kk], cy[kk], pU[kk], cd, pD[kk], cz[kk], pu, cb, pm);
+            cbelow = cur.ca;
+            const T qq = apply_point(cur.d, pc, cur.cr, cur.right, cur.cl, cur.left, cur.cu, cur.up, cur.cd, cur.down,
+                                     cur.ca, pu, cb, pm);
             q[kk] = qq;
             agent_store(qn, ox, qq);   // dropped at kNowhere
             agent_store(qn, oy, qq);
@@ -498,7 +626,7 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
             if (kk + 1 == nkv) agent_store(qn, pub_zhi, qq);
             ox += (uint32_t)(a.ty * E);
             oy += (uint32_t)(a.tx * E);
-            const T ivk = inv(kk);
+            const T ivk = cur.iv;
             const double pd = (double)pc, qd = (double)qq, rd = (double)r[kk];
             const double zd = (double)(r[kk] * ivk), wd = (double)(qq * ivk);
             acc[0] = fma(pd, qd, acc[0]);
@@ -508,8 +636,16 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
             acc[4] = fma(rd, rd, acc[4]);
             acc[5] = fma(rd, qd, acc[5]);
             acc[6] = fma(qd, qd, acc[6]);
+            if constexpr (CP || (LL && E == 4)) {
+                // the sums are otherwise sunk below the loop, with p and 1/d of
+                // every plane kept until then
+#pragma unroll
+                for (int k = 0; k < 7; ++k) asm volatile("" : "+v"(acc[k]));
+                __builtin_amdgcn_sched_barrier(0);
+            }
             pm = pc;
-            pc = up;
+            pc = cur.above;
+            cur = nxt;
         }
         if (!reduce(v)) return timed_out();
         const double pq = v[0], rrd = v[1], rqd = v[2], qqd = v[3];
@@ -529,15 +665,22 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
             else if (iters >= a.maxiter) { done = 1; status = PB_NOT_CONVERGED; }
             if (done && status != PB_ERR_BREAKDOWN) {
                 // last x update with the final alpha and direction
+                if constexpr (!XM)
 #pragma unroll
-                for (int kk = 0; kk < NZ; ++kk) x[kk] = fma((T)alpha, pl[kk], x[kk]);
+                    for (int kk = 0; kk < NZ; ++kk) x[kk] = fma((T)alpha, pl[kk], x[kk]);
+                last = (T)alpha;
             }
         }
     }
     if (valid)
 #pragma unroll
         for (int kk = 0; kk < NZ; ++kk)
-            if (kk < nk) a.x[(int64_t)(k0 + kk) * sp + pos] = zero ? T(0) : x[kk];
+            if (kk < nk) {
+                T xk;
+                if constexpr (XM) xk = fma(last, pl[kk], x_get(xs, xoff, kk * BS * E, T()));
+                else xk = x[kk];
+                a.x[(int64_t)(k0 + kk) * sp + pos] = zero ? T(0) : xk;
+            }
     if (w == 0 && tid == 0) {
         a.S->rr = rr;
         a.S->bb = bb;
@@ -550,45 +693,44 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
     }
 }
 
-template <typename T, int BS, int NZ, bool PER>
+template <typename T, int BS, int NZ, bool PER, bool CP = false>
 __global__ __launch_bounds__(BS) void k_jpcg_resident(RArgs<T> a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    resident_problem<T, BS, NZ, PER>(a, blockIdx.x, lds_raw);
+    resident_problem<T, BS, NZ, PER, CP>(a, blockIdx.x, lds_raw);
 }
 
-// The bricks of a batch: 512 threads, these numbers of planes.
+constexpr int kCompactFrom = 24;   // planes per brick from which a kernel is the compact form's
+// Planes per brick of a batch: the largest that leave the registers unspilled,
+// so that a problem takes few workgroups and the barrier's latency is shared by
+// many nodes. One number per form: a kernel that chose between four inlined
+// forms spilled, and gave wrong potentials in the last bricks of one of them.
 template <typename T>
-__device__ __forceinline__ void resident_batch_problem(const RArgs<T>& a, int w, unsigned char* lds) {
-    if constexpr (sizeof(T) == 4) {
-        if (a.planes == 19) resident_problem<T, 512, 19, false>(a, w, lds);
-        else if (a.planes == 17) resident_problem<T, 512, 17, false>(a, w, lds);
-        else if (a.planes == 12) resident_problem<T, 512, 12, false>(a, w, lds);
-        else if (a.planes == 8) resident_problem<T, 512, 8, false>(a, w, lds);
-    } else {
-        if (a.planes == 8) resident_problem<T, 512, 8, false>(a, w, lds);
-        else if (a.planes == 4) resident_problem<T, 512, 4, false>(a, w, lds);
-    }
-}
-template <typename T>
-const std::vector<int>& batch_planes() {
-    static const std::vector<int> v = sizeof(T) == 4 ? std::vector<int>{8, 12, 17, 19} : std::vector<int>{4, 8};
-    return v;
-}
+constexpr int batch_planes(bool compact) { return sizeof(T) == 8 ? 8 : (compact ? 43 : 19); }
 
 // Many problems in one launch: workgroup g runs the jobs [off[g], off[g + 1]) of
 // its list one after the other, job (problem, its workgroup number there). Jobs
 // are listed in one global order, so a workgroup that waits in a problem's
 // first barrier waits only for workgroups whose earlier jobs come before that
 // problem in every list: no cycle.
-template <typename T>
+template <typename T, bool CP>
 __global__ __launch_bounds__(512) void k_resident_batch(const RArgs<T>* __restrict__ probs, const int* __restrict__ off,
                                                         const int2* __restrict__ jobs) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int end = off[blockIdx.x + 1];
     for (int n = off[blockIdx.x]; n < end; ++n) {
         const int2 job = jobs[n];
-        const RArgs<T> a = probs[job.x];
-        resident_batch_problem<T>(a, job.y, lds_raw);
+        // the arguments, word by word known uniform: the compiler otherwise
+        // takes the buffer descriptors made of them for divergent
+        union U {
+            RArgs<T> a;
+            int w[sizeof(RArgs<T>) / 4];
+            __device__ U() {}
+        } u;
+        const int* src = reinterpret_cast<const int*>(probs + __builtin_amdgcn_readfirstlane(job.x));
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(RArgs<T>) / 4); ++i) u.w[i] = __builtin_amdgcn_readfirstlane(src[i]);
+        const RArgs<T> a = u.a;
+        resident_problem<T, 512, batch_planes<T>(CP), false, CP>(a, __builtin_amdgcn_readfirstlane(job.y), lds_raw);
         __syncthreads();
     }
 }

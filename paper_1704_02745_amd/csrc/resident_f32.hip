@@ -8,8 +8,8 @@ const std::vector<ResVariant>& res_variants<float>() {
     static const std::vector<ResVariant> v = {
         PB_RES_VARIANT(float, 256, 2),  PB_RES_VARIANT(float, 256, 4),  PB_RES_VARIANT(float, 512, 4),
         PB_RES_VARIANT(float, 512, 6),  PB_RES_VARIANT(float, 512, 8),  PB_RES_VARIANT(float, 512, 10),
-        PB_RES_VARIANT(float, 512, 12), PB_RES_VARIANT(float, 512, 14), PB_RES_VARIANT(float, 512, 16),
-        PB_RES_VARIANT(float, 512, 17), PB_RES_VARIANT(float, 512, 19), PB_RES_VARIANT(float, 512, 22),
+        PB_RES_VARIANT(float, 512, 12), PB_RES_VARIANT(float, 512, 14), PB_RES_VARIANT(float, 512, 19),
+        PB_RES_COMPACT(24),             PB_RES_COMPACT(32),             PB_RES_COMPACT(43),
     };
     return v;
 }

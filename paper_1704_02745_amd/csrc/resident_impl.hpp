@@ -19,6 +19,14 @@ struct ResVariant {
     int bs, nz;
     const void* fn[2];   // free, periodic
 };
+// compact: free and periodic kernels of the compact form
+#define PB_RES_COMPACT(NZ)                                                     \
+    ResVariant {                                                               \
+        512, NZ, {                                                             \
+            (const void*)k_jpcg_resident<float, 512, NZ, false, true>,         \
+                (const void*)k_jpcg_resident<float, 512, NZ, true, true>       \
+        }                                                                      \
+    }
 #define PB_RES_VARIANT(T, BS, NZ) \
     ResVariant { BS, NZ, { (const void*)k_jpcg_resident<T, BS, NZ, false>, (const void*)k_jpcg_resident<T, BS, NZ, true> } }
 
@@ -53,21 +61,30 @@ ResDevice res_device() {
 template <typename T>
 const std::vector<ResVariant>& res_variants();
 
+template <typename T>
+const void* batch_kernel(bool compact) {
+    if constexpr (sizeof(T) == 4)
+        if (compact) return (const void*)k_resident_batch<T, true>;
+    return (const void*)k_resident_batch<T, false>;
+}
+
 // Microseconds of one pass, fitted to sweeps of block, planes and tile at
 // 33^3-129^3: a fixed part (the barrier's two memory latencies), the planes of a
 // thread (0.15 each with 512 threads), the halo nodes, the slots every
 // workgroup polls, and the strided x-faces.
-double resident_pass_us(int bs, int nzb, int halo, int grid, bool split_x) {
-    return 2.4 + 0.149 * nzb * bs / 512 + 0.1 * halo / bs + 0.0107 * grid + (split_x ? 0.2 : 0.0);
+double resident_pass_us(int bs, int nzb, int halo, int grid, bool split_x, bool compact) {
+    return 2.4 + (compact ? 0.19 : 0.149) * nzb * bs / 512 + 0.1 * halo / bs + 0.0107 * grid + (split_x ? 0.2 : 0.0);
 }
 
 // Every feasible way to cut a grid into bricks of `bs` threads and `nzb`
 // planes, the cheapest by `cost` kept in `best`.
 template <typename T, typename Cost>
-void resident_search(const Layout& L, int per, int bs, int nzb, int cap, int64_t face_room, const void* fn, Cost&& cost,
-                     double& best_cost, ResPlan& best) {
+void resident_search(const Layout& L, int per, int bs, int nzb, bool compact, int cap, int64_t face_room,
+                     const void* fn, Cost&& cost, double& best_cost, ResPlan& best) {
     const int nzc = (L.nz + nzb - 1) / nzb;
     if (nzc > cap) return;
+    // faces of one parity: both fit r where x takes p0 and p1 
+    if (x_in_memory<T>(nzb, compact)) face_room = L.npad / 2;
     for (int nxt = 1; nxt <= cap / nzc; ++nxt) {
         if (nxt > 1 && L.nx / nxt < 2) break;   // a column is on one x-face at most
         const int tx = (L.nx + nxt - 1) / nxt;
@@ -77,11 +94,14 @@ void resident_search(const Layout& L, int per, int bs, int nzb, int cap, int64_t
         const int ty = (L.ny + nyt - 1) / nyt;
         const int64_t grid = (int64_t)nxt * nyt * nzc;
         if (grid > cap) continue;
-        const size_t lds = resident_lds_bytes<T>(bs, nzb, tx, ty);
-        if (lds > 160 * 1024) continue;
+        // every halo column needs a thread; x by brick fits two state arrays
+        if ((nxt > 1 ? 2 * ty : 0) + (nyt > 1 ? 2 * tx : 0) > bs) continue;
+        if (x_in_memory<T>(nzb, compact) && grid * nzb * bs > 2 * L.npad) continue;
+        const size_t lds = resident_lds_bytes<T>(bs, nzb, tx, ty, compact);
+        if (lds + (compact ? sizeof(T) * 2 * kCodedTableSize : 0) > 160 * 1024) continue;
         if ((grid > 1 || per) && grid * face_len(bs, nzb, tx, ty) > face_room) continue;
         const int halo = (nxt > 1 ? 2 * ty * nzb : 0) + (nyt > 1 ? 2 * tx * nzb : 0);
-        const double us = resident_pass_us(bs, nzb, halo, (int)grid, nxt > 1), c = cost(us, (int)grid);
+        const double us = resident_pass_us(bs, nzb, halo, (int)grid, nxt > 1, compact), c = cost(us, (int)grid);
         if (c < best_cost) {
             best_cost = c;
             best = ResPlan{bs, nzb, tx, ty, nxt, nyt, nzc, (int)grid, lds, fn, us};
@@ -95,15 +115,15 @@ void resident_search(const Layout& L, int per, int bs, int nzb, int cap, int64_t
 // problems share the device, and each keeps its bricks in any mix. Plans are
 // kept per device and shape (a host-side search of a few microseconds).
 template <typename T>
-ResPlan resident_plan(const Layout& L, int per, bool batch) {
+ResPlan resident_plan(const Layout& L, int per, bool batch, bool compact) {
     ResPlan best{};
     const ResDevice di = res_device();
     const int cap = std::min(di.cus, kMaxResidentGroups);
     if (cap <= 0 || L.npad * (int64_t)sizeof(T) >= ((int64_t)1 << 31)) return best;
-    using Key = std::tuple<int, int, int, int, int, bool>;
+    using Key = std::tuple<int, int, int, int, int, bool, bool>;
     static std::mutex mu;
     static std::map<Key, ResPlan> kept;
-    const Key key(di.dev, L.nx, L.ny, L.nz, per, batch);
+    const Key key(di.dev, L.nx, L.ny, L.nz, per, batch, compact);
     {
         std::lock_guard<std::mutex> lk(mu);
         const auto it = kept.find(key);
@@ -111,16 +131,17 @@ ResPlan resident_plan(const Layout& L, int per, bool batch) {
     }
     double best_cost = 1e300;
     if (batch) {
-        // faces in r and in r2, one parity each
-        for (int nzb : batch_planes<T>())
-            resident_search<T>(L, 0, 512, nzb, cap, L.npad, (const void*)k_resident_batch<T>,
+        // the faces of one parity in r, of the other in r2
+        if (sizeof(T) == 4 || !compact)
+            resident_search<T>(L, 0, 512, batch_planes<T>(compact), compact, cap, L.npad, batch_kernel<T>(compact),
                                [](double us, int grid) { return us * grid; }, best_cost, best);
     } else {
         // both parities in five of the six state arrays of the streaming form (a
         // warm start's residual takes the sixth)
         for (const ResVariant& v : res_variants<T>())
-            resident_search<T>(L, per, v.bs, v.nz, cap, 5 * L.npad / 2, v.fn[per ? 1 : 0],
-                               [](double us, int) { return us; }, best_cost, best);
+            if (compact == (v.nz >= kCompactFrom))
+                resident_search<T>(L, per, v.bs, v.nz, compact, cap, 5 * L.npad / 2,
+                                   v.fn[per ? 1 : 0], [](double us, int) { return us; }, best_cost, best);
     }
     if (best.grid > 0) {
         int nb = 0;
@@ -181,7 +202,6 @@ RArgs<T> resident_args(const Layout& L, const SolveBufs<T>& s, const ResPlan& p,
     a.warm = s.warm;
     a.S = sync;
     a.slots = slots;
-    a.planes = p.nz;
     // every wait is bounded: 20 s of the constant-rate clock
     a.timeout_ticks = (long long)(di.wallclock_khz > 0 ? di.wallclock_khz : 100000) * 1000LL * 20LL;
     a.first_timeout_ticks = a.timeout_ticks;
@@ -197,21 +217,27 @@ pb_status launch_resident_start(const Layout& L, const Op<T>& op, const T* b, co
     return PB_OK;
 }
 
+// cw, ctab: the compact form on these code words (null: the full form).
 template <typename T>
 pb_status resident_solve(const Layout& L, const SolveBufs<T>& s, SyncState* sync, double* partials, double tol,
-                         int maxiter, hipStream_t st, SolveResult* res, int periodic, bool& ran) {
+                         int maxiter, hipStream_t st, SolveResult* res, int periodic, const uint32_t* cw,
+                         const float* ctab, bool& ran) {
     ran = false;
     // the state arrays of the streaming form, r to q2, hold the published faces
-    if (!s.r || !s.q2 || s.q2 - s.r != 5 * L.npad) return PB_OK;
-    const ResPlan p = resident_plan<T>(L, periodic, false);
+    if (!s.r || !s.q2 || s.q2 - s.r != 5 * L.npad || s.p1 - s.p0 != L.npad) return PB_OK;
+    const ResPlan p = resident_plan<T>(L, periodic, false, cw != nullptr);
     if (p.grid <= 0) return PB_OK;
     RArgs<T> a = resident_args<T>(L, s, p, sync, (unsigned long long*)partials, tol, maxiter);
     const int64_t half = (int64_t)p.grid * face_len(p.bs, p.nz, p.tx, p.ty);
     a.faces[0] = s.r;
     a.faces[1] = s.r + half;
+    a.cw = cw;
+    a.ctab = ctab;
+    a.xs = s.p0;
     if (s.warm) {
-        if (launch_resident_start<T>(L, s.op, s.b, s.x, s.q2, periodic, st) != PB_OK) return PB_ERR_HIP;
-        a.r0 = s.q2;
+        T* r0 = x_in_memory<T>(p.nz, cw != nullptr) ? s.r2 : s.q2;   // q2 holds the code words
+        if (launch_resident_start<T>(L, s.op, s.b, s.x, r0, periodic, st) != PB_OK) return PB_ERR_HIP;
+        a.r0 = r0;
     }
     if (launch_fill<int>((int*)sync, (int64_t)(sizeof(SyncState) / sizeof(int)), 0, st) != PB_OK) return PB_ERR_HIP;
     if (launch_fill<int>((int*)partials, (int64_t)2 * p.grid * kSlotWords * 2, 0, st) != PB_OK) return PB_ERR_HIP;
@@ -249,8 +275,8 @@ pb_status resident_solve(const Layout& L, const SolveBufs<T>& s, SyncState* sync
         res->bb = h.bb;
         res->kernel_seconds = 1e-3 * ms;
         res->tiling = Tiling{};
-        res->coded = 0;
-        res->ctab = nullptr;
+        res->coded = cw ? 1 : 0;
+        res->ctab = ctab;
     }
     return PB_OK;
 }
@@ -259,21 +285,30 @@ pb_status resident_solve(const Layout& L, const SolveBufs<T>& s, SyncState* sync
 
 template <typename T>
 pb_status resident_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, double* partials, double tol,
-                        int maxiter, hipStream_t st, SolveResult* res, int periodic, bool& ran) {
-    return resident_solve<T>(L, s, sync, partials, tol, maxiter, st, res, periodic, ran);
+                        int maxiter, hipStream_t st, SolveResult* res, int periodic, const uint32_t* cw,
+                        const float* ctab, bool& ran) {
+    return resident_solve<T>(L, s, sync, partials, tol, maxiter, st, res, periodic, cw, ctab, ran);
 }
 template <typename T>
-bool resident_fits(const Layout& L, int periodic) {
-    return resident_plan<T>(L, periodic, false).grid > 0;
+bool resident_fits(const Layout& L, int periodic, bool compact) {
+    return resident_plan<T>(L, periodic, false, compact).grid > 0;
 }
-
 
 // ---- batch support (see solver.hpp)
 
 template <typename T>
 ResBatchPlan resident_batch_plan(const Layout& L) {
-    const ResPlan p = resident_plan<T>(L, 0, true);
-    return ResBatchPlan{p.grid, std::min(res_device().cus, kMaxResidentGroups), p.us, p.lds, (size_t)2 * p.grid * kSlotWords * sizeof(unsigned long long)};
+    ResPlan p = resident_plan<T>(L, 0, true, false);
+    const bool compact = p.grid <= 0;
+    if (compact) p = resident_plan<T>(L, 0, true, true);
+    ResBatchPlan b{};
+    b.grid = p.grid;
+    b.compact = compact && p.grid > 0;
+    b.groups = std::min(res_device().cus, kMaxResidentGroups);
+    b.us = p.us;
+    b.lds = p.lds;
+    b.slot_bytes = (size_t)2 * p.grid * kSlotWords * sizeof(unsigned long long);
+    return b;
 }
 template <typename T>
 size_t resident_batch_args_bytes() {
@@ -282,11 +317,15 @@ size_t resident_batch_args_bytes() {
 template <typename T>
 pb_status resident_batch_fill(void* dst, const Layout& L, const SolveBufs<T>& s, SyncState* S, void* slots, double tol,
                               int maxiter, int problems, const float* cw, const float* ctab, const int* fit) {
-    const ResPlan p = resident_plan<T>(L, 0, true);
+    ResPlan p = resident_plan<T>(L, 0, true, false);
+    const bool compact = p.grid <= 0;
+    if (compact) p = resident_plan<T>(L, 0, true, true);
     RArgs<T> a = resident_args<T>(L, s, p, S, (unsigned long long*)slots, tol, maxiter);
     a.faces[0] = s.r;
-    a.faces[1] = s.r2;
-    if (s.warm) a.r0 = s.p0;
+    const bool xmem = x_in_memory<T>(p.nz, compact);
+    a.faces[1] = xmem ? s.r + (int64_t)p.grid * face_len(p.bs, p.nz, p.tx, p.ty) : s.r2;
+    a.xs = s.p0;
+    if (s.warm) a.r0 = xmem ? s.r2 : s.p0;
     a.first_timeout_ticks = a.timeout_ticks * (1 + (long long)problems);
     a.cw = (const uint32_t*)cw;
     a.ctab = ctab;
@@ -296,15 +335,19 @@ pb_status resident_batch_fill(void* dst, const Layout& L, const SolveBufs<T>& s,
 }
 template <typename T>
 pb_status resident_batch_start(const Layout& L, const SolveBufs<T>& s, hipStream_t st) {
-    return s.warm ? launch_resident_start<T>(L, s.op, s.b, s.x, s.p0, 0, st) : PB_OK;
+    ResPlan p = resident_plan<T>(L, 0, true, false);
+    const bool compact = p.grid <= 0;
+    if (compact) p = resident_plan<T>(L, 0, true, true);
+    T* r0 = x_in_memory<T>(p.nz, compact) ? s.r2 : s.p0;
+    return s.warm ? launch_resident_start<T>(L, s.op, s.b, s.x, r0, 0, st) : PB_OK;
 }
 template <typename T>
 pb_status resident_batch_launch(const void* d_args, const int* d_off, const void* d_jobs, int grid, size_t lds,
-                                hipStream_t st, bool cooperative) {
+                                bool compact, hipStream_t st, bool cooperative) {
     const RArgs<T>* ap = (const RArgs<T>*)d_args;
     const int2* jp = (const int2*)d_jobs;
     void* args[] = {&ap, &d_off, &jp};
-    const void* fn = (const void*)k_resident_batch<T>;
+    const void* fn = batch_kernel<T>(compact);
     const hipError_t e = cooperative ? hipLaunchCooperativeKernel(fn, dim3(grid), dim3(512), args, lds, st)
                                      : hipLaunchKernel(fn, dim3(grid), dim3(512), args, lds, st);
     if (e != hipSuccess) {
@@ -315,13 +358,14 @@ pb_status resident_batch_launch(const void* d_args, const int* d_off, const void
 }
 #define PB_RES_INSTANCES(T)                                                                                       \
     template pb_status resident_jpcg<T>(const Layout&, const SolveBufs<T>&, SyncState*, double*, double, int,     \
-                                        hipStream_t, SolveResult*, int, bool&);                                   \
-    template bool resident_fits<T>(const Layout&, int);                                                           \
+                                        hipStream_t, SolveResult*, int, const uint32_t*, const float*, bool&);    \
+    template bool resident_fits<T>(const Layout&, int, bool);                                                     \
     template ResBatchPlan resident_batch_plan<T>(const Layout&);                                                  \
     template size_t resident_batch_args_bytes<T>();                                                               \
     template pb_status resident_batch_fill<T>(void*, const Layout&, const SolveBufs<T>&, SyncState*, void*, double, \
                                               int, int, const float*, const float*, const int*);                  \
     template pb_status resident_batch_start<T>(const Layout&, const SolveBufs<T>&, hipStream_t);                  \
-    template pb_status resident_batch_launch<T>(const void*, const int*, const void*, int, size_t, hipStream_t, bool);
+    template pb_status resident_batch_launch<T>(const void*, const int*, const void*, int, size_t, bool, hipStream_t, \
+                                                bool);
 
 }  // namespace pb

@@ -121,18 +121,21 @@ pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, do
                      int periodic = 0);
 
 // resident_f32.hip, resident_f64.hip: the same solve with the whole iteration
-// state in registers and LDS. ran = false: the grid does not fit, nothing was
-// enqueued.
+// state in registers and LDS; with cw and ctab (FP32: the operator's code words
+// and dictionary) in the compact form, which takes larger grids. ran = false: the
+// grid does not fit, nothing was enqueued.
 template <typename T>
 pb_status resident_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, double* partials, double tol,
-                        int maxiter, hipStream_t st, SolveResult* res, int periodic, bool& ran);
+                        int maxiter, hipStream_t st, SolveResult* res, int periodic, const uint32_t* cw,
+                        const float* ctab, bool& ran);
 template <typename T>
-bool resident_fits(const Layout& L, int periodic);
+bool resident_fits(const Layout& L, int periodic, bool compact);
 // The same for many problems in one launch. A problem's bricks depend on its
 // shape only; every workgroup of the launch works through a list of jobs
 // (problem, workgroup number in it), all lists in one global order of problems.
 struct ResBatchPlan {
     int grid;            // workgroups of the problem, 0 when it does not fit
+    bool compact;        // in the compact form: needs the operator's code words
     int groups;          // workgroups of the launch (one per CU)
     double us;           // modelled microseconds per iteration
     size_t lds;
@@ -150,7 +153,7 @@ template <typename T>
 pb_status resident_batch_start(const Layout& L, const SolveBufs<T>& s, hipStream_t st);   // warm starts: b - A x0
 template <typename T>
 pb_status resident_batch_launch(const void* d_args, const int* d_off, const void* d_jobs, int grid, size_t lds,
-                                hipStream_t st, bool cooperative);
+                                bool compact, hipStream_t st, bool cooperative);
 
 template <typename T>
 Tiling choose_tiling(const Layout& L);
@@ -231,7 +234,7 @@ size_t batch_kargs_bytes();
 template <typename T>
 void batch_fill_kargs(void* dst, const Layout& L, const SolveBufs<T>& s, SyncState* S, double* partials,
                       const Tiling& t, double tol, int maxiter, int resume, int chunk, const float* cw = nullptr,
-                      const float* ctab = nullptr, const int* fit = nullptr);
+                      const float* ctab = nullptr, const int* fit = nullptr, bool unless_fit = false);
 // Co-resident workgroups of the batch kernel. coded: 0 uncoded, 1 coded (every
 // problem's operator fits), 2 coded per problem as its fit flag says; for 1
 // and 2, lds includes kCodedLdsBytes.

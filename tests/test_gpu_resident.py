@@ -102,3 +102,84 @@ def test_resident_against_streaming(pb, prec, bound):
     assert float((x1 - x0).abs().max()) <= bound * float(x0.abs().max())
     assert il["status"] == im["status"] == pb.PB_NOT_CONVERGED and il["iters"] == im["iters"] == 7
     assert float((xl - xm).abs().max()) <= bound * float(xm.abs().max())
+
+
+def molecule_system(pb, dims, natoms, seed, boundary="free"):
+    import synth
+    p = synth.small_problem(*dims, natoms, seed=seed, precision="f32")
+    return pb.setup(p.grid, p.mol.xyz, p.mol.radius, p.mol.charge, p.eps_in, p.eps_out, p.kappa_d2, device=DEV,
+                    boundary=boundary)
+
+
+def streaming(pb, sysm, **kw):
+    """The solve in the streaming form, the shape's choice of form left as it was."""
+    dims = sysm.dims
+    if sysm.grid.boundary:
+        pb.set_periodic_pass(1)
+        try:
+            return pb.solve(sysm, **kw)
+        finally:
+            pb.set_periodic_pass(-1)
+    c = [c for c in pb.tiling_candidates(*dims, "f32") if c["scheme"] == 1][0]
+    pb.set_tuning(*dims, "f32", c["block"], c["groups"], c["zchunk"], c["grid"], c["scheme"], c["streaming"],
+                  c["segments"])
+    try:
+        return pb.solve(sysm, **kw)
+    finally:
+        pb.autotune(sysm, precision="f32", iters_per_trial=2)
+
+
+# every number of planes per brick of the FP32 kernels, full (2 to 19) and compact (24 to 43), is the
+# default of some of these
+@pytest.mark.parametrize("dims", [(33, 29, 31), (45, 41, 47), (65, 57, 61), (81, 77, 83), (97, 105, 89),
+                                  (117, 117, 113), (133, 129, 133), (139, 141, 137), (153, 150, 155), (169, 171, 165)])
+@pytest.mark.parametrize("boundary", ["free", "periodic"])
+def test_resident_sizes(pb, dims, boundary):
+    sysm = molecule_system(pb, dims, max(20, int(1e-3 * dims[0] ** 3) // 8), sum(dims), boundary)
+    print(f"resident sizes {dims} {boundary}", flush=True)
+    x1, i1 = pb.solve(sysm, tol=1e-6, precision="f32")
+    xw, iw = pb.solve(sysm, tol=1e-6, precision="f32", x0=0.9 * x1)
+    xr, ir = pb.solve(sysm, tol=1e-9, precision="f32_refine64")
+    x0, i0 = streaming(pb, sysm, tol=1e-6, precision="f32")
+    scale = float(x0.abs().max())
+    assert i1["status"] == iw["status"] == ir["status"] == pb.PB_OK
+    assert abs(i1["iters"] - i0["iters"]) <= max(2, 0.02 * i0["iters"]) and iw["iters"] < i1["iters"]
+    assert float((x1 - x0).abs().max()) <= 1e-5 * scale
+    assert float((xw - x0).abs().max()) <= 1e-5 * scale
+    assert float((xr - x0).abs().max()) <= 1e-5 * scale and ir["relres_true"] < 1e-9
+
+
+def test_batch_of_every_form(pb):
+    """Full and compact resident problems and one that only streams, in one batch:
+    each bitwise as alone; recorded, a compact problem whose operator stops
+    fitting the dictionary runs uncoded and the others as before."""
+    shapes = [(139, 141, 137), (49, 45, 41), (96, 97, 95), (201, 193, 189)]
+    systems = [molecule_system(pb, s, 200, 900 + i) for i, s in enumerate(shapes)]
+    xs, infos = pb.solve_batch(systems, tol=1e-6, precision="f32")
+    assert all(i["status"] == pb.PB_OK and i["coded_launches"] == 1 for i in infos), infos
+    for k, s in enumerate(systems):
+        x, i = pb.solve_batch([s], tol=1e-6, precision="f32")
+        assert torch.equal(x[0], xs[k]) and i[0]["iters"] == infos[k]["iters"], k
+        y, _ = pb.solve(s, tol=1e-6, precision="f32")
+        assert float((y - xs[k]).abs().max()) <= 1e-5 * float(y.abs().max()), k
+    g = pb.BatchGraph(systems, tol=1e-6, precision="f32")
+    try:
+        for _ in range(3):
+            g.launch()
+            i1 = g.results()
+            assert [i["coded_launches"] for i in i1] == [1] * 4
+            assert all(torch.equal(g.outs[j], xs[j]) for j in range(4))
+            torch.zeros(1 << 20, device=DEV).add_(1.0)
+        saved = systems[0].eps_x.clone()
+        systems[0].eps_x.copy_(torch.as_tensor(np.random.default_rng(5).uniform(1, 80, tuple(saved.shape)), device=DEV))
+        g.launch()
+        i2 = g.results()
+        assert [i["coded_launches"] for i in i2] == [0, 1, 1, 1] and all(i["status"] == pb.PB_OK for i in i2)
+        xd, _ = pb.solve_batch(systems, tol=1e-6, precision="f32")
+        assert torch.equal(g.outs[0], xd[0]) and all(torch.equal(g.outs[j], xs[j]) for j in range(1, 4))
+        systems[0].eps_x.copy_(saved)
+        g.launch()
+        g.results()
+        assert all(torch.equal(g.outs[j], xs[j]) for j in range(4))
+    finally:
+        g.close()
