@@ -262,6 +262,7 @@ struct SetupWs {
     double* qgrid;
     uint8_t* mask;
     double* ghost;
+    double* dh;        // sums at the Chebyshev points of the faces' tiles
     int* cell_start;   // fractional edges: atom ranges per cell
     int* cell_end;
     size_t bytes;
