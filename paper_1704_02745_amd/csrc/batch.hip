@@ -17,6 +17,41 @@
 #include <vector>
 
 namespace pb {
+
+// Problems in order of decreasing expected duration (wider ones first among
+// equals), each on the workgroups that are free first.
+void resident_schedule(const std::vector<int>& grid, const std::vector<double>& cost, int groups,
+                       std::vector<int>& off, std::vector<int>& jobs) {
+    const int n = (int)grid.size();
+    std::vector<int> order(n);
+    for (int k = 0; k < n; ++k) order[k] = k;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+        return grid[a] != grid[b] ? grid[a] > grid[b] : cost[a] > cost[b];
+    });
+    std::vector<std::vector<int>> list(groups);
+    std::vector<double> free_at(groups, 0.0);
+    std::vector<int> by(groups);
+    for (int g = 0; g < groups; ++g) by[g] = g;
+    for (int k : order) {
+        const int G = grid[k];
+        std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return free_at[a] < free_at[b]; });
+        const double end = free_at[by[G - 1]] + cost[k];
+        std::vector<int> gang(by.begin(), by.begin() + G);
+        std::sort(gang.begin(), gang.end());
+        for (int w = 0; w < G; ++w) {
+            list[gang[w]].push_back(k);
+            list[gang[w]].push_back(w);
+            free_at[gang[w]] = end;
+        }
+    }
+    off.assign(1, 0);
+    jobs.clear();
+    for (int g = 0; g < groups; ++g) {
+        jobs.insert(jobs.end(), list[g].begin(), list[g].end());
+        off.push_back((int)jobs.size() / 2);
+    }
+}
+
 namespace {
 
 struct ProbRec {            // per-problem host-visible results in the workspace
@@ -175,44 +210,6 @@ bool carve_batch(void* base, int nprob, const pb_problem* probs, Plan<T>& P, int
 // Jacobi-CG iterations of a problem relative to others (the count grows about
 // with the root of the edge once the salt screens the long waves).
 double expected_iterations(const Layout& L) { return std::sqrt((double)std::max(L.nx, std::max(L.ny, L.nz))); }
-
-// The job lists of the resident launch: problems in order of decreasing
-// expected duration (wider ones first among equals), each on the workgroups
-// that are free first. off: P.groups + 1 offsets; jobs: (index in `of`,
-// workgroup of the problem) pairs.
-template <typename T>
-void resident_schedule(const Plan<T>& P, const std::vector<int>& of, std::vector<int>& off, std::vector<int>& jobs) {
-    const int n = (int)of.size();
-    std::vector<int> order(n);
-    for (int k = 0; k < n; ++k) order[k] = k;
-    auto cost = [&](int k) { return P.rp[of[k]].us * expected_iterations(P.L[of[k]]); };
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-        const int ga = P.rp[of[a]].grid, gb = P.rp[of[b]].grid;
-        return ga != gb ? ga > gb : cost(a) > cost(b);
-    });
-    std::vector<std::vector<int>> list(P.groups);
-    std::vector<double> free_at(P.groups, 0.0);
-    std::vector<int> by(P.groups);
-    for (int g = 0; g < P.groups; ++g) by[g] = g;
-    for (int k : order) {
-        const int G = P.rp[of[k]].grid;
-        std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return free_at[a] < free_at[b]; });
-        const double end = free_at[by[G - 1]] + cost(k);
-        std::vector<int> gang(by.begin(), by.begin() + G);
-        std::sort(gang.begin(), gang.end());
-        for (int w = 0; w < G; ++w) {
-            list[gang[w]].push_back(k);
-            list[gang[w]].push_back(w);
-            free_at[gang[w]] = end;
-        }
-    }
-    off.assign(1, 0);
-    jobs.clear();
-    for (int g = 0; g < P.groups; ++g) {
-        jobs.insert(jobs.end(), list[g].begin(), list[g].end());
-        off.push_back((int)jobs.size() / 2);
-    }
-}
 
 // Workgroups per problem, proportional to nodes x max edge, at least one,
 // at most the problem's tile count; returns the offsets (size nprob + 1).
@@ -394,7 +391,13 @@ pb_status upload_table(Plan<T>& P, const pb_problem* probs, int& grid, int coded
     for (int c = 0; c < 2; ++c) {
         const auto& f = P.res[c];
         if (f.of.empty()) continue;
-        resident_schedule<T>(P, f.of, off[c], jobs[c]);
+        std::vector<int> grids;
+        std::vector<double> cost;
+        for (int i : f.of) {
+            grids.push_back(P.rp[i].grid);
+            cost.push_back(P.rp[i].us * expected_iterations(P.L[i]));
+        }
+        resident_schedule(grids, cost, P.groups, off[c], jobs[c]);
         PB_HIP(hipMemcpyAsync(f.job_off, off[c].data(), sizeof(int) * off[c].size(), hipMemcpyHostToDevice, st));
         PB_HIP(hipMemcpyAsync(f.jobs, jobs[c].data(), sizeof(int) * jobs[c].size(), hipMemcpyHostToDevice, st));
     }

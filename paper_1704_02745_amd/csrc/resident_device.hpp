@@ -58,6 +58,10 @@ struct RArgs {
     const uint32_t* cw;
     const float* ctab;
     const int* fit;
+    // a solve in chunks (KEEPS): r, q and p between launches, the iterations of this
+    // launch, and whether it goes on from them
+    T *keep_r, *keep_q, *keep_p;
+    int chunk, resume;
 };
 
 constexpr int kSlotWords = 16;            // two words per sum (low half, high half), 8 sums
@@ -197,7 +201,13 @@ __host__ __device__ constexpr size_t resident_lds_bytes(int bs, int nzb, int tx,
 // state does not fit the registers. A node keeps r, q and six bytes of codes
 // there, decoded through the dictionary in LDS where they are used; x goes to
 // memory (x_in_memory). The operations and their order are the same.
-template <typename T, int BS, int NZ, bool PER, bool CP = false>
+//
+// KEEPS: the launch ends after a.chunk iterations of an unfinished solve, with r,
+// q, p, x and the scalars in memory as the next pass expects them, and the next
+// launch goes on with that pass, so the iterates are those of one launch, bit for
+// bit. The last pass stores them before its barrier, from inside the loop: with
+// r and q alive past it the compiler spilled 74 (compact: 170) registers.
+template <typename T, int BS, int NZ, bool PER, bool CP = false, bool KEEPS = false>
 __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_raw) {
 #pragma clang fp contract(off)
     constexpr int ROWS = BS / 64 * 4;
@@ -267,11 +277,13 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
     // XM: x of plane kk at xoff + kk * BS elements
     const Rsrc xs = rsrc_of(XM ? a.xs + (size_t)w * NZ * BS : a.x, XM ? NZ * BS : 0);
     const uint32_t xoff = (uint32_t)tid * E;
+    const bool resume = KEEPS && a.resume;
     {
         // positions without a node and planes past nk read as zero
         auto from = [&](const void* p) { return rsrc_of((const T*)p + (int64_t)k0 * sp, (int64_t)nk * sp); };
         const Rsrc rcx = from(a.op.cx), rcy = from(a.op.cy), rcz = from(a.op.cz), rd = from(a.op.d), rr0 = from(a.r0),
-                   rb0 = from(a.b), rx = from(a.x), rcw = from(a.cw);
+                   rb0 = from(a.b), rx = from(a.x), rcw = from(a.cw), rkq = from(KEEPS ? a.keep_q : a.x);
+        const bool keeps_x = resume;   // by brick, from the launch before
         auto at = [&](bool in, int p) { return valid && in ? (uint32_t)p * E : kNowhere; };
         uint32_t o = at(true, pos), ox = at(i > 0 || PER, i > 0 ? pos - 1 : pos + nx - 1),
                  oy = at(j > 0 || PER, j > 0 ? pos - nx : pos + (ny - 1) * nx);
@@ -312,10 +324,10 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
                 if constexpr (KEEP) iv[kk] = jacobi_inv(d[kk]);
             }
             const T xv = bload<0>(rx, a.warm ? o : kNowhere, T());
-            if constexpr (XM) x_put(xs, xoff, kk * BS * E, xv);
+            if constexpr (XM) x_put(xs, keeps_x ? kNowhere : xoff, kk * BS * E, xv);
             else x[kk] = xv;
             r[kk] = bload<0>(rr0, o, T());
-            q[kk] = T(0);
+            q[kk] = KEEPS ? bload<0>(rkq, resume ? o : kNowhere, T()) : T(0);
             const T bv = bload<0>(rb0, o, T());
             acc[0] = fma((double)r[kk], (double)r[kk], acc[0]);
             acc[1] = fma((double)bv, (double)bv, acc[1]);
@@ -408,6 +420,18 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
             RH[kk * hc + hcol] = a.r0[g];
             IH[kk * hc + hcol] = jacobi_inv(diag_at(g));
         }
+    if constexpr (KEEPS) {
+        if (resume) {
+            __syncthreads();   // p is cleared
+            const T* const kp = a.keep_p;
+            if (valid)
+                for (int kk = 0; kk < nk; ++kk) pl[kk] = kp[(int64_t)(k0 + kk) * sp + pos];
+            if (hon)
+                for (int kk = hk0; kk < nk; kk += hgroups) hP[kk] = kp[(int64_t)(k0 + kk) * sp + hpos];
+            if (valid && has_b) pb_ = kp[(int64_t)kb * sp + pos];
+            if (valid && has_t) pt = kp[(int64_t)kt * sp + pos];
+        }
+    }
 
     // ---- grid barrier with the reduction of the sums in acc; the totals in
     // every thread
@@ -475,22 +499,35 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
     };
     auto timed_out = [&] {
         if (tid == 0) __hip_atomic_store(&a.S->status, (int)PB_ERR_TIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (KEEPS && tid == 0) __hip_atomic_store(&a.S->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
 
     if (tid == 0) s_flag[0] = 0;
     __syncthreads();
     double v[8];
-    if (!reduce(v)) return timed_out();
-    double alpha = 0.0, beta = 0.0, rr = v[0];
-    const double bb = v[1], sqrt_bb = sqrt(bb);
+    double alpha = 0.0, beta = 0.0, rr, bb;
     int done = 0, status = PB_OK, zero = 0, iters = 0;
-    if (!(bb - bb == 0.0) || !(rr - rr == 0.0)) { done = 1; status = PB_ERR_NONFINITE; }
+    if (!reduce(v)) return timed_out();   // also: every halo is read before any state is stored
+    if (resume) {
+        rr = a.S->rr;
+        bb = a.S->bb;
+        alpha = a.S->alpha;
+        beta = a.S->beta;
+        iters = a.S->iters;
+    } else {
+        rr = v[0];
+        bb = v[1];
+    }
+    const double sqrt_bb = sqrt(bb);
+    const int stop_at = KEEPS ? iters + a.chunk : 0;
+    if (resume) {
+    } else if (!(bb - bb == 0.0) || !(rr - rr == 0.0)) { done = 1; status = PB_ERR_NONFINITE; }
     else if (bb == 0.0) { done = 1; zero = 1; }
     else if (sqrt(rr) / sqrt_bb < a.tol) { done = 1; }
     else if (a.maxiter <= 0) { done = 1; status = PB_NOT_CONVERGED; }
 
     T last = T(0);   // XM: step of the last x update
-    for (int pass = 0; !done; ++pass) {
+    for (int pass = KEEPS ? iters : 0; !done && !(KEEPS && iters >= stop_at); ++pass) {
         const T al = (T)alpha, be = (T)beta;
         // ---- q of the halo, on its way while the own nodes are updated (the
         // first pass has alpha = 0 and reads nothing)
@@ -647,6 +684,21 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
             pc = cur.above;
             cur = nxt;
         }
+        if constexpr (KEEPS) {
+            if (iters + 1 >= stop_at) {   // the launch's last pass
+                const Rsrc kr = rsrc_of(a.keep_r + (int64_t)k0 * sp, (int64_t)nk * sp),
+                           kq = rsrc_of(a.keep_q + (int64_t)k0 * sp, (int64_t)nk * sp),
+                           kp = rsrc_of(a.keep_p + (int64_t)k0 * sp, (int64_t)nk * sp);
+                uint32_t o = opaque_v(valid ? (uint32_t)pos * E : kNowhere);
+#pragma unroll
+                for (int kk = 0; kk < NZ; ++kk) {
+                    x_put(kr, o, 0, r[kk]);
+                    x_put(kq, o, 0, q[kk]);
+                    x_put(kp, o, 0, pl[kk]);
+                    o += (uint32_t)(sp * E);
+                }
+            }
+        }
         if (!reduce(v)) return timed_out();
         const double pq = v[0], rrd = v[1], rqd = v[2], qqd = v[3];
         if (!(pq > 0.0) || !(pq - pq == 0.0) || !(rrd > 0.0)) {
@@ -672,7 +724,7 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
             }
         }
     }
-    if (valid)
+    if (valid && !(KEEPS && XM && !done))   // (x by brick stays there)
 #pragma unroll
         for (int kk = 0; kk < NZ; ++kk)
             if (kk < nk) {
@@ -712,7 +764,7 @@ constexpr int batch_planes(bool compact) { return sizeof(T) == 8 ? 8 : (compact 
 // are listed in one global order, so a workgroup that waits in a problem's
 // first barrier waits only for workgroups whose earlier jobs come before that
 // problem in every list: no cycle.
-template <typename T, bool CP>
+template <typename T, bool CP, bool KEEPS>
 __global__ __launch_bounds__(512) void k_resident_batch(const RArgs<T>* __restrict__ probs, const int* __restrict__ off,
                                                         const int2* __restrict__ jobs) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -730,7 +782,7 @@ __global__ __launch_bounds__(512) void k_resident_batch(const RArgs<T>* __restri
 #pragma unroll
         for (int i = 0; i < (int)(sizeof(RArgs<T>) / 4); ++i) u.w[i] = __builtin_amdgcn_readfirstlane(src[i]);
         const RArgs<T> a = u.a;
-        resident_problem<T, 512, batch_planes<T>(CP), false, CP>(a, __builtin_amdgcn_readfirstlane(job.y), lds_raw);
+        resident_problem<T, 512, batch_planes<T>(CP), false, CP, KEEPS>(a, __builtin_amdgcn_readfirstlane(job.y), lds_raw);
         __syncthreads();
     }
 }

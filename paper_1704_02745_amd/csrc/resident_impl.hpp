@@ -64,8 +64,8 @@ const std::vector<ResVariant>& res_variants();
 template <typename T>
 const void* batch_kernel(bool compact) {
     if constexpr (sizeof(T) == 4)
-        if (compact) return (const void*)k_resident_batch<T, true>;
-    return (const void*)k_resident_batch<T, false>;
+        if (compact) return (const void*)k_resident_batch<T, true, false>;
+    return (const void*)k_resident_batch<T, false, false>;
 }
 
 // Microseconds of one pass, fitted to sweeps of block, planes and tile at

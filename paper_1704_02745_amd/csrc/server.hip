@@ -3,12 +3,12 @@
 // Requests (systems of any supported size and tolerance) are queued by
 // pb_server_submit. Each pb_server_step admits queued requests in arrival
 // order while slots and the caller's HBM arena allow, advances every active
-// request by up to `chunk` Jacobi-PCG iterations in ONE persistent batch
-// launch (the requests' work overlaps on the device), retires requests that
-// converged or failed, and frees their memory for the next admissions. The
-// CG state of an unfinished request stays resident between steps and the
-// next launch resumes it exactly, so chunking and the mix of co-running
-// requests do not change any request's arithmetic.
+// request by some chunks of Jacobi-PCG iterations in one persistent launch per
+// form (full resident, compact resident, pass; the requests' work overlaps on
+// the device), retires requests that converged or failed, and frees their memory
+// for the next admissions. The CG state of an unfinished request stays in its
+// memory between steps and the next launch resumes it exactly, so chunking and
+// the mix of co-running requests do not change any request's arithmetic.
 //
 // PB_F32 requests run FP32 JPCG to their tolerance. PB_F32_REFINE64 requests
 // cycle: FP64 residual -> FP32 JPCG correction to a relative 1e-4 -> FP64
@@ -60,6 +60,7 @@ Tiling serve_tiling(const Layout& L) {
 // request's grid barrier and reductions, about 5.5 us, which the fused pass
 // at 257^3 spends on about 3,500 node updates per workgroup (1.6 ns each).
 constexpr double kBarrierNodes = 3500.0;
+constexpr int kServeGroups = 256;   // workgroups of a resident launch at most
 // A request advances by at most this many times the caller's chunk per launch.
 constexpr int kMaxChunkScale = 16;
 
@@ -108,6 +109,24 @@ void share_launch(const std::vector<Tiling>& Ts, int cap, int chunk, std::vector
     }
 }
 
+// Iterations of one launch over the resident requests, whose workgroups are
+// fixed by their shapes: as many as take the slowest one's kResidentChunks
+// chunks, at most kMaxChunkScale. A launch loads and stores a request's state,
+// 0.05 to 0.1 ms where 32 iterations take 0.15 to 0.55 (a burst of 12 requests of
+// 67 to 171 nodes an edge: 34.4 ms of launches with one chunk each, 31.5 with four,
+// and 0.4 ms of host time less for each launch saved).
+constexpr double kResidentChunks = 4.0;
+std::vector<int> resident_chunks(const std::vector<ResBatchPlan>& P, int chunk) {
+    double most = 0.0;
+    for (const ResBatchPlan& p : P) most = std::max(most, p.us);
+    std::vector<int> c;
+    for (const ResBatchPlan& p : P) {
+        const double scale = std::min<double>(kMaxChunkScale, kResidentChunks * most / p.us);
+        c.push_back((int)std::min<double>(1e9, std::floor((double)chunk * scale)));
+    }
+    return c;
+}
+
 struct SlotRec {   // per-slot results written by kernels and read by the host
     int flags;
     int fit;       // 1: the FP32 operator fits the coded-coefficient dictionary
@@ -118,16 +137,20 @@ struct SlotRec {   // per-slot results written by kernels and read by the host
     double pad2[3];
 };
 
+enum Form { kFull, kCompact, kPassForm };   // resident, full or compact; pass
+
 struct Slot {
     int64_t id = 0;
     pb_problem req{};
     int precision = PB_F32;
     Layout L{};
     Tiling t{};
+    ResBatchPlan rp{};               // the resident form's share, where the grid fits it
+    int form = kPassForm;
     size_t off = 0, bytes = 0;       // arena range
     SyncState* S = nullptr;
     SlotRec* rec = nullptr;
-    double* partials = nullptr;
+    double* partials = nullptr;      // tile sums, or the resident form's barrier words
     double* resp = nullptr;
     Op<double> op64{};
     double* b64 = nullptr;
@@ -158,6 +181,17 @@ struct Slot {
     bool energy_enqueued = false;
 };
 
+// Tilings of both forms, by the grid alone. The request runs in the full
+// resident form where its state fits the device so, in the compact one where that
+// fits and it has code words (settled when it is admitted), else in passes; its
+// arithmetic is the same whatever else is in flight.
+void plan_slot(Slot& s) {
+    s.t = serve_tiling(s.L);
+    if (s.t.ntiles <= 0) return;
+    s.rp = resident_batch_plan<float>(s.L);
+    if (s.rp.grid > 0 && !s.rp.compact) s.form = kFull;
+}
+
 // Carve one slot's device memory at `base` (null to size it).
 size_t carve_slot(char* base, Slot& s) {
     size_t off = 0;
@@ -168,7 +202,8 @@ size_t carve_slot(char* base, Slot& s) {
     };
     const size_t n8 = sizeof(double) * (size_t)s.L.npad, n4 = sizeof(float) * (size_t)s.L.npad;
     s.S = (SyncState*)take(sizeof(SyncState));
-    s.partials = (double*)take(2 * sizeof(double) * kMaxPartials * (size_t)s.t.ntiles);
+    s.partials = (double*)take(
+        std::max(2 * sizeof(double) * kMaxPartials * (size_t)s.t.ntiles, s.rp.grid > 0 ? s.rp.slot_bytes : (size_t)0));
     s.resp = (double*)take(sizeof(double) * 2 * (size_t)residual_blocks(s.L));
     s.op64.cx = (double*)take(n8);
     s.op64.cy = (double*)take(n8);
@@ -214,6 +249,9 @@ struct Server {
     size_t arena_bytes = 0;
     int max_slots = 0;
     char* table = nullptr;        // device: kernel-argument records for max_slots
+    char* rtable = nullptr;       // device: the same of the resident form
+    int* job_off = nullptr;       // device: its job lists (resident_schedule)
+    int* jobs = nullptr;
     int* first = nullptr;         // device: workgroup offsets
     StateDigest* digests = nullptr;   // device: each running request's scalars after a launch
     SlotRec* recs = nullptr;      // device: one record per admitted slot (max_slots)
@@ -228,7 +266,7 @@ struct Server {
     hipEvent_t ev[2] = {nullptr, nullptr};
     hipEvent_t ev_in = nullptr;      // the caller's stream at the start of a step
     hipStream_t adm = nullptr;       // admissions (setup, preparation), overlapping the running launch
-    std::vector<char> host_table;
+    std::vector<char> host_table, host_rtable;
     std::vector<int> host_first;
     std::vector<StateDigest> host_digests;
     std::vector<SlotRec> host_recs;
@@ -303,7 +341,7 @@ extern "C" size_t pb_server_request_bytes(const pb_problem* req) {
     if (!req || req->nx < 1 || req->ny < 1 || req->nz < 1) return 0;
     Slot s;
     s.L = make_layout(req->nx, req->ny, req->nz);
-    s.t = serve_tiling(s.L);
+    plan_slot(s);
     if (s.t.ntiles <= 0) return 0;
     return carve_slot(nullptr, s);
 }
@@ -321,17 +359,24 @@ extern "C" pb_status pb_server_create(void* arena, size_t arena_bytes, int32_t m
     const size_t fb = align_up(sizeof(int) * (size_t)(max_slots + 1), 256);
     const size_t db = align_up(sizeof(StateDigest) * (size_t)max_slots, 256);
     const size_t rb = align_up(sizeof(SlotRec) * (size_t)max_slots, 256);
-    PB_ARG(arena_bytes > tb + fb + db + rb, "pb_server_create: arena too small");
+    const size_t ab = align_up(resident_batch_args_bytes<float>() * (size_t)max_slots, 256);
+    const size_t ob = align_up(2 * sizeof(int) * (kServeGroups + 1), 256);
+    const size_t jb = align_up(2 * sizeof(int) * kServeGroups * (size_t)max_slots, 256);
+    PB_ARG(arena_bytes > tb + fb + db + rb + ab + ob + jb, "pb_server_create: arena too small");
     S->table = S->arena;
     S->first = (int*)(S->arena + tb);
     S->digests = (StateDigest*)(S->arena + tb + fb);
     S->recs = (SlotRec*)(S->arena + tb + fb + db);
-    S->reserved = tb + fb + db + rb;
+    S->rtable = S->arena + tb + fb + db + rb;
+    S->job_off = (int*)(S->rtable + ab);
+    S->jobs = (int*)(S->rtable + ab + ob);
+    S->reserved = tb + fb + db + rb + ab + ob + jb;
     S->host_digests.resize(max_slots);
     S->host_recs.resize(max_slots);
     for (int i = max_slots - 1; i >= 0; --i) S->free_recs.push_back(i);
     S->free_list.push_back({S->reserved, arena_bytes - S->reserved});
     S->host_table.resize(batch_kargs_bytes<float>() * (size_t)max_slots);
+    S->host_rtable.resize(resident_batch_args_bytes<float>() * (size_t)max_slots);
     S->host_first.resize(max_slots + 1);
     PB_HIP(hipEventCreate(&S->ev[0]));
     PB_HIP(hipEventCreate(&S->ev[1]));
@@ -352,7 +397,7 @@ extern "C" pb_status pb_server_submit(pb_server* S, const pb_problem* req, int32
     s->req = *req;
     s->precision = precision;
     s->L = make_layout(req->nx, req->ny, req->nz);
-    s->t = serve_tiling(s->L);
+    plan_slot(*s);
     PB_ARG(s->t.ntiles > 0, "pb_server_submit: grid too wide for the batch kernel (nx <= 512)");
     s->bytes = carve_slot(nullptr, *s);
     PB_ARG(s->bytes <= S->arena_bytes - S->reserved, "pb_server_submit: request larger than the whole arena");
@@ -370,7 +415,7 @@ extern "C" size_t pb_server_request_bytes_atoms(const pb_grid* grid, int64_t nat
     s.from_atoms = true;
     s.natoms = natoms;
     s.L = make_layout(grid->nx, grid->ny, grid->nz);
-    s.t = serve_tiling(s.L);
+    plan_slot(s);
     if (s.t.ntiles <= 0) return 0;
     return carve_slot(nullptr, s);
 }
@@ -413,7 +458,7 @@ extern "C" pb_status pb_server_submit_atoms(pb_server* S, const pb_grid* grid, i
     s->req.x = x;
     s->precision = precision;
     s->L = make_layout(grid->nx, grid->ny, grid->nz);
-    s->t = serve_tiling(s->L);
+    plan_slot(*s);
     PB_ARG(s->t.ntiles > 0, "pb_server_submit_atoms: grid too wide for the batch kernel (nx <= 512)");
     s->bytes = carve_slot(nullptr, *s);
     PB_ARG(s->bytes <= S->arena_bytes - S->reserved, "pb_server_submit_atoms: request larger than the whole arena");
@@ -517,6 +562,7 @@ extern "C" pb_status pb_server_step(pb_server* S, int32_t chunk, void* stream, i
                 e = enqueue_encode(s.s.op, s.L.npad, s.s.q, (uint32_t*)s.s.q2, st);
                 if (e != PB_OK) return e;
                 s.coded = true;
+                if (s.rp.grid > 0 && s.rp.compact) s.form = kCompact;
             }
             if (r.flags & (FLAG_BAD_RHS | FLAG_BAD_GUESS)) {
                 e = finish_slot(s, PB_ERR_NONFINITE, st);
@@ -554,51 +600,105 @@ extern "C" pb_status pb_server_step(pb_server* S, int32_t chunk, void* stream, i
     for (auto& up : S->active)
         if (up->solving && up->ready) run.push_back(up.get());
     if (!run.empty()) {
-        std::vector<Layout> Ls;
+        // the requests by form: a launch of each resident one, then the pass form's
+        std::stable_sort(run.begin(), run.end(), [](const Slot* a, const Slot* b) { return a->form < b->form; });
+        int count[3] = {0, 0, 0};
+        size_t lds = 0, all_lds = 0, rlds[2] = {0, 0};
         std::vector<Tiling> Ts;
-        size_t lds = 0;
+        std::vector<ResBatchPlan> Rs[2];
         for (Slot* sp : run) {
-            Ls.push_back(sp->L);
-            Ts.push_back(sp->t);
-            lds = std::max(lds, sp->t.lds);
+            ++count[sp->form];
+            all_lds = std::max(all_lds, sp->t.lds);
+            if (sp->form != kPassForm) {
+                Rs[sp->form].push_back(sp->rp);
+                rlds[sp->form] = std::max(rlds[sp->form], sp->rp.lds);
+            } else {
+                Ts.push_back(sp->t);
+                lds = std::max(lds, sp->t.lds);
+            }
         }
+        const int nres = count[kFull] + count[kCompact], npass = count[kPassForm];
         // the coded kernel when every running request has its code words
         bool coded = coded_coefficients() != 0;
         for (Slot* sp : run) coded = coded && sp->coded;
         int cap = coded ? batch_capacity<float>(lds + kCodedLdsBytes, true) : 0;
-        if (coded && cap >= (int)run.size()) lds += kCodedLdsBytes;
+        if (coded && cap >= npass) lds += kCodedLdsBytes;
         else {
             coded = false;
             cap = batch_capacity<float>(lds);
         }
-        if (cap < (int)run.size()) {
-            set_error("pb_server_step: %zu active solves exceed %d co-resident workgroups", run.size(), cap);
+        // a step takes as many active solves as the pass form has co-resident
+        // workgroups, whatever form they run in
+        if (batch_capacity<float>(all_lds) < (int)run.size()) {
+            set_error("pb_server_step: %zu active solves exceed %d co-resident workgroups", run.size(),
+                      batch_capacity<float>(all_lds));
             return PB_ERR_ARG;
         }
-        std::vector<int> first(run.size() + 1, 0), chunks(run.size(), chunk);
-        share_launch(Ts, cap, chunk, first, chunks);
-        const size_t kb = batch_kargs_bytes<float>();
-        for (size_t i = 0; i < run.size(); ++i) {
-            Slot& s = *run[i];
-            const double tol = s.precision == PB_F32 ? s.req.tol : kInnerTol;
-            batch_fill_kargs<float>(S->host_table.data() + kb * i, s.L, s.s, s.S, s.partials, s.t, tol, s.maxiter,
-                                    s.resume ? 1 : 0, chunks[i], coded ? (const float*)s.s.q2 : nullptr,
-                                    coded ? dictionary_table(s.s.q) : nullptr);
+        auto reads_codes = [&](const Slot& s) { return coded || s.form == kCompact; };
+        auto code_words = [&](const Slot& s) { return reads_codes(s) ? (const float*)s.s.q2 : nullptr; };
+        auto code_table = [&](const Slot& s) { return reads_codes(s) ? dictionary_table(s.s.q) : nullptr; };
+        auto tol_of = [](const Slot& s) { return s.precision == PB_F32 ? s.req.tol : kInnerTol; };
+        std::vector<int> joff[2], jobs[2], first(npass + 1, 0), chunks(npass, chunk);
+        int rgroups[2] = {0, 0}, job0[2] = {0, 0};
+        const size_t rkb = resident_batch_args_bytes<float>();
+        for (int c = 0, i = 0; c < 2; ++c) {
+            if (Rs[c].empty()) continue;
+            const std::vector<int> rchunk = resident_chunks(Rs[c], chunk);
+            std::vector<int> grids;
+            std::vector<double> cost;
+            int sum = 0;
+            for (size_t k = 0; k < Rs[c].size(); ++k, ++i) {
+                Slot& s = *run[i];
+                e = resident_serve_fill(S->host_rtable.data() + rkb * i, s.L, s.s, s.S, s.partials, tol_of(s), s.maxiter,
+                                        nres, code_words(s), code_table(s), rchunk[k], s.resume);
+                if (e != PB_OK) return e;
+                e = launch_fill<int>((int*)s.partials, (int64_t)(s.rp.slot_bytes / sizeof(int)), 0, st);
+                if (e != PB_OK) return e;
+                if (!s.resume && (e = resident_batch_start<float>(s.L, s.s, st)) != PB_OK) return e;
+                grids.push_back(s.rp.grid);
+                cost.push_back(s.rp.us * rchunk[k]);
+                sum += s.rp.grid;
+            }
+            rgroups[c] = std::min({sum, Rs[c][0].groups, kServeGroups});
+            resident_schedule(grids, cost, rgroups[c], joff[c], jobs[c]);
+            job0[c] = c == 0 ? 0 : (int)jobs[0].size();
+            PB_HIP(hipMemcpyAsync(S->job_off + c * (kServeGroups + 1), joff[c].data(), sizeof(int) * joff[c].size(),
+                                  hipMemcpyHostToDevice, st));
+            PB_HIP(hipMemcpyAsync(S->jobs + job0[c], jobs[c].data(), sizeof(int) * jobs[c].size(),
+                                  hipMemcpyHostToDevice, st));
         }
-        PB_HIP(hipMemcpyAsync(S->table, S->host_table.data(), kb * run.size(), hipMemcpyHostToDevice, st));
-        PB_HIP(hipMemcpyAsync(S->first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice, st));
-        e = batch_reset_arrivals<float>(S->table, (int)run.size(), st);
-        if (e != PB_OK) return e;
+        if (nres > 0) PB_HIP(hipMemcpyAsync(S->rtable, S->host_rtable.data(), rkb * nres, hipMemcpyHostToDevice, st));
+        if (npass > 0) {
+            share_launch(Ts, cap, chunk, first, chunks);
+            const size_t kb = batch_kargs_bytes<float>();
+            for (int i = 0; i < npass; ++i) {
+                Slot& s = *run[nres + i];
+                batch_fill_kargs<float>(S->host_table.data() + kb * i, s.L, s.s, s.S, s.partials, s.t, tol_of(s),
+                                        s.maxiter, s.resume ? 1 : 0, chunks[i], code_words(s), code_table(s));
+            }
+            PB_HIP(hipMemcpyAsync(S->table, S->host_table.data(), kb * npass, hipMemcpyHostToDevice, st));
+            PB_HIP(hipMemcpyAsync(S->first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice, st));
+            e = batch_reset_arrivals<float>(S->table, npass, st);
+            if (e != PB_OK) return e;
+        }
         PB_HIP(hipEventRecord(S->ev[0], st));
-        // a plain launch sized to co-residency (a cooperative launch would
+        // plain launches sized to co-residency (a cooperative launch would
         // keep the admissions from running beside it): workgroups still
         // waiting for a slot get one as the admissions' kernels finish
-        e = batch_launch<float>(S->table, S->first, (int)run.size(), first.back(), lds, st, false, coded);
-        if (e != PB_OK) return e;
+        for (int c = 0; c < 2; ++c) {
+            if (Rs[c].empty()) continue;
+            e = resident_serve_launch(S->rtable + (c == 0 ? 0 : rkb * count[kFull]), S->job_off + c * (kServeGroups + 1),
+                                      S->jobs + job0[c], rgroups[c], rlds[c], c == kCompact, st);
+            if (e != PB_OK) return e;
+        }
+        if (npass > 0) {
+            e = batch_launch<float>(S->table, S->first, npass, first.back(), lds, st, false, coded);
+            if (e != PB_OK) return e;
+        }
         PB_HIP(hipEventRecord(S->ev[1], st));
         // every running request's scalars in one read-back
-        e = batch_state_digests<float>(S->table, (int)run.size(), S->digests, st);
-        if (e != PB_OK) return e;
+        if (nres > 0 && (e = resident_serve_digests(S->rtable, nres, S->digests, st)) != PB_OK) return e;
+        if (npass > 0 && (e = batch_state_digests<float>(S->table, npass, S->digests + nres, st)) != PB_OK) return e;
         PB_HIP(hipMemcpyAsync(S->host_digests.data(), S->digests, sizeof(StateDigest) * run.size(),
                               hipMemcpyDeviceToHost, st));
         // this step's admissions, while the launch runs

@@ -250,6 +250,20 @@ struct StateDigest {
 };
 template <typename T>
 pb_status batch_state_digests(const void* d_kargs, int nprob, StateDigest* out, hipStream_t st);
+// resident_f32.hip: the solve server's requests in the resident form, each launch
+// advancing a request by up to `chunk` iterations. Between launches the state
+// arrays hold r and p; in the compact form p takes the place of b.
+pb_status resident_serve_fill(void* dst, const Layout& L, const SolveBufs<float>& s, SyncState* S, void* slots,
+                              double tol, int maxiter, int problems, const float* cw, const float* ctab, int chunk,
+                              bool resume);
+pb_status resident_serve_launch(const void* d_args, const int* d_off, const void* d_jobs, int grid, size_t lds,
+                                bool compact, hipStream_t st);
+pb_status resident_serve_digests(const void* d_args, int n, StateDigest* out, hipStream_t st);
+// batch.hip: the job lists of a resident launch of `groups` workgroups over
+// problems of `grid` workgroups and `cost` (any unit) each. off: groups + 1
+// offsets; jobs: (problem, workgroup of the problem) pairs.
+void resident_schedule(const std::vector<int>& grid, const std::vector<double>& cost, int groups,
+                       std::vector<int>& off, std::vector<int>& jobs);
 template <typename T>
 pb_status batch_launch(const void* d_kargs, const int* d_first, int nprob, int grid, size_t lds, hipStream_t st,
                        bool cooperative, int coded = 0);

@@ -183,3 +183,37 @@ def test_batch_of_every_form(pb):
         assert all(torch.equal(g.outs[j], xs[j]) for j in range(4))
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("chunk", [1, 7, 100000])
+def test_served_chunks(pb, chunk):
+    """Served requests of the full and the compact form and one in passes, warm starts among them,
+    stopped and resumed after `chunk` iterations (or a few times as many): each bitwise the batch of
+    that request alone, which runs through in one launch."""
+    shapes = [(45, 41, 47), (97, 89, 93), (139, 141, 137), (141, 131, 149)]
+    systems = [molecule_system(pb, s, 150, 700 + i) for i, s in enumerate(shapes)]
+    if chunk > 1:
+        systems.append(molecule_system(pb, (201, 193, 189), 200, 711))
+    want = [pb.solve_batch([s], tol=1e-5, precision="f32")[0][0] for s in systems]
+    guess = [0.9 * w if k % 2 else None for k, w in enumerate(want)]
+    batch = [pb.solve_batch([s], tol=1e-5, precision="f32", x0s=[g] if g is not None else None)
+             for s, g in zip(systems, guess)]
+    srv = pb.Server(sum(pb.Server.request_bytes(s) for s in systems) + (64 << 20), max_slots=8, device=DEV)
+    try:
+        ids = {srv.submit(s, tol=1e-5, precision="f32", x0=g): k for k, (s, g) in enumerate(zip(systems, guess))}
+        out = {}
+        for _ in range(5000):
+            for rid, info in srv.step(chunk=chunk):
+                out[ids[rid]] = (srv.outputs[rid].clone(), info)
+            if len(out) == len(systems):
+                break
+    finally:
+        srv.close()
+    assert len(out) == len(systems)
+    for k, (x, info) in out.items():
+        xb, ib = batch[k]
+        assert info["status"] == pb.PB_OK, k
+        if shapes[k:k + 1]:   # (the pass form's tiles differ between server and batch)
+            assert info["iters"] == ib[0]["iters"] and torch.equal(x, xb[0]), k
+        else:
+            assert float((x - xb[0]).abs().max()) <= 1e-5 * float(x.abs().max()), k
