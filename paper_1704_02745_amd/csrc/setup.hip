@@ -22,11 +22,6 @@ __global__ void k_fill_u8(uint8_t* p, int64_t n, uint8_t v) {
     for (; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-__global__ void k_fill_f64(double* p, int64_t n, double v) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
-}
-
 __global__ void k_fill_i32(int* p, int64_t n, int v) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;
@@ -37,14 +32,24 @@ __global__ void k_fill_u64(uint64_t* p, int64_t n, uint64_t v) {
     for (; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
+// What the setup accumulates into, cleared in one launch: the flags word's 256
+// bytes, the padded mask and the charge grid.
+__global__ void k_setup_clear(int* __restrict__ flags, uint8_t* __restrict__ mask, int64_t nmask,
+                              double* __restrict__ q, int64_t nn) {
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    if (t0 < 64) flags[t0] = 0;
+    const int64_t words = ((uintptr_t)mask & 7) == 0 ? nmask / 8 : 0;   // a caller's mask may lie anywhere
+    for (int64_t t = t0; t < words; t += step) reinterpret_cast<uint64_t*>(mask)[t] = 0;
+    for (int64_t t = 8 * words + t0; t < nmask; t += step) mask[t] = 0;
+    for (int64_t t = t0; t < nn; t += step) q[t] = 0.0;
+}
+
 // Node classification: one workgroup per atom walks the atom's bounding
 // window of padded nodes and marks the ones strictly inside the sphere.
 // Concurrent writers only ever store 1, so the result is order independent.
-__global__ void k_classify(const double* __restrict__ xyz, const double* __restrict__ radius,
-                           int64_t natoms, int nx, int ny, int nz, double h,
-                           double ox, double oy, double oz, int per, uint8_t* __restrict__ mask) {
-    const int64_t a = blockIdx.x;
-    if (a >= natoms) return;
+__device__ __forceinline__ void classify_atom(int64_t a, const double* __restrict__ xyz,
+                                              const double* __restrict__ radius, int nx, int ny, int nz, double h,
+                                              double ox, double oy, double oz, int per, uint8_t* __restrict__ mask) {
     const double cx = xyz[3 * a], cy = xyz[3 * a + 1], cz = xyz[3 * a + 2];
     const double r = radius[a];
     const double rr = r * r;
@@ -90,6 +95,12 @@ __global__ void k_classify(const double* __restrict__ xyz, const double* __restr
     }
 }
 
+__global__ void k_classify(const double* __restrict__ xyz, const double* __restrict__ radius, int64_t natoms, int nx,
+                           int ny, int nz, double h, double ox, double oy, double oz, int per,
+                           uint8_t* __restrict__ mask) {
+    if (blockIdx.x < natoms) classify_atom(blockIdx.x, xyz, radius, nx, ny, nz, h, ox, oy, oz, per, mask);
+}
+
 // Periodic: fill the ghost layer of the padded mask with the wrapped nodes,
 // one axis at a time (x, then y over whole padded rows, then z over whole
 // padded planes) so edges and corners wrap too.
@@ -125,47 +136,56 @@ __device__ __forceinline__ double harmonic(double a, double b) {
     return 2.0 * a * b / (a + b);
 }
 
-// Staggered edge dielectrics and the salt term, one thread per element.
-__global__ void k_edges(const uint8_t* __restrict__ mask, int nx, int ny, int nz,
-                        double ein, double eout, double kbar2,
-                        double* __restrict__ ex, double* __restrict__ ey,
-                        double* __restrict__ ez, double* __restrict__ k2) {
-    const int64_t px = nx + 2, py = ny + 2;
-    const int64_t nex = (int64_t)(nx + 1) * ny * nz;
-    const int64_t ney = (int64_t)nx * (ny + 1) * nz;
-    const int64_t nez = (int64_t)nx * ny * (nz + 1);
-    const int64_t nn = (int64_t)nx * ny * nz;
-    const int64_t total = nex + ney + nez + nn;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        if (t < nex) {
-            const int64_t e = t % (nx + 1);
-            const int64_t j = (t / (nx + 1)) % ny;
-            const int64_t k = t / ((int64_t)(nx + 1) * ny);
-            const int64_t base = px * ((j + 1) + py * (k + 1));
-            ex[t] = harmonic(node_eps(mask[base + e], ein, eout), node_eps(mask[base + e + 1], ein, eout));
-        } else if (t < nex + ney) {
-            const int64_t u = t - nex;
-            const int64_t i = u % nx;
-            const int64_t e = (u / nx) % (ny + 1);
-            const int64_t k = u / ((int64_t)nx * (ny + 1));
-            const int64_t a = (i + 1) + px * (e + py * (k + 1));
-            ey[u] = harmonic(node_eps(mask[a], ein, eout), node_eps(mask[a + px], ein, eout));
-        } else if (t < nex + ney + nez) {
-            const int64_t u = t - nex - ney;
-            const int64_t i = u % nx;
-            const int64_t j = (u / nx) % ny;
-            const int64_t e = u / ((int64_t)nx * ny);
-            const int64_t a = (i + 1) + px * ((j + 1) + py * e);
-            ez[u] = harmonic(node_eps(mask[a], ein, eout), node_eps(mask[a + px * py], ein, eout));
-        } else {
-            const int64_t u = t - nex - ney - nez;
-            const int64_t i = u % nx;
-            const int64_t j = (u / nx) % ny;
-            const int64_t k = u / ((int64_t)nx * ny);
-            const uint8_t m = mask[(i + 1) + px * ((j + 1) + py * (k + 1))];
-            k2[u] = m ? 0.0 : kbar2;
+// Staggered edge dielectrics, the salt term and (b given) the right-hand side
+// 4*pi*q/h^3 plus, for nodes on the box faces, the ghost potential times the
+// ghost-side edge dielectric over h^2 (x-, x+, y-, y+, z-, z+ in that order; none
+// in a periodic box, which repeats). One thread per node and its three lower
+// edges, and one past the last node of each axis for the upper ones. Bound by the
+// writes: 257^3 in 0.25 ms, where a thread per element with 64-bit divisions and
+// a pass of its own for the right-hand side took 0.32. An edge takes one of three
+// values, so their divisions are done once per thread. I: an integer type that
+// holds the thread count.
+template <typename I>
+__global__ void k_fields(const uint8_t* __restrict__ mask, int nx, int ny, int nz, double ein, double eout,
+                         double kbar2, const double* __restrict__ q, const double* __restrict__ ghost, double h3,
+                         double ih2, int per, double* __restrict__ ex, double* __restrict__ ey,
+                         double* __restrict__ ez, double* __restrict__ k2, double* __restrict__ b) {
+    const double hoo = harmonic(eout, eout), hio = harmonic(ein, eout), hii = harmonic(ein, ein);
+    auto edge = [&](uint8_t m, uint8_t n) { return m && n ? hii : (m || n ? hio : hoo); };
+    const int64_t px = nx + 2, pxy = px * (ny + 2);
+    const I mx = (I)(nx + 1), my = (I)(ny + 1), total = mx * my * (I)(nz + 1);
+    for (int64_t tt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; tt < (int64_t)total;
+         tt += (int64_t)gridDim.x * blockDim.x) {
+        const I t = (I)tt, row = t / mx, pk = row / my;
+        const int i = (int)(t - row * mx), j = (int)(row - pk * my), k = (int)pk;
+        const uint8_t* at = mask + (i + 1) + px * (j + 1) + pxy * (k + 1);
+        const uint8_t m = at[0];
+        const double exm = edge(at[-1], m), eym = edge(at[-px], m), ezm = edge(at[-pxy], m);
+        const bool ix = i < nx, jy = j < ny, kz = k < nz;
+        const int64_t yz = j + (int64_t)ny * k;
+        if (jy && kz) ex[i + (nx + 1) * yz] = exm;
+        if (ix && kz) ey[i + (int64_t)nx * (j + (int64_t)(ny + 1) * k)] = eym;
+        if (ix && jy) ez[i + (int64_t)nx * yz] = ezm;
+        if (!(ix && jy && kz)) continue;
+        const int64_t n = i + (int64_t)nx * yz;
+        k2[n] = m ? 0.0 : kbar2;
+        if (!b) continue;
+        const double charge = kFourPi * q[n] / h3;
+        if (per) {
+            b[n] = charge;
+            continue;
         }
+        const int64_t fx = (int64_t)ny * nz, fy = (int64_t)nx * nz, fz = (int64_t)nx * ny;
+        const double* gy = ghost + 2 * fx;
+        const double* gz = gy + 2 * fy;
+        double fold = 0.0;
+        if (i == 0) fold = fold + exm * ih2 * ghost[yz];
+        if (i == nx - 1) fold = fold + edge(m, at[1]) * ih2 * ghost[fx + yz];
+        if (j == 0) fold = fold + eym * ih2 * gy[i + (int64_t)nx * k];
+        if (j == ny - 1) fold = fold + edge(m, at[px]) * ih2 * gy[fy + i + (int64_t)nx * k];
+        if (k == 0) fold = fold + ezm * ih2 * gz[i + (int64_t)nx * j];
+        if (k == nz - 1) fold = fold + edge(m, at[pxy]) * ih2 * gz[fz + i + (int64_t)nx * j];
+        b[n] = charge + fold;
     }
 }
 
@@ -356,12 +376,12 @@ __device__ __forceinline__ int64_t corner_node(int i0, int j0, int k0, int c, in
 
 // Charge spreading, step 1: one sort key per (atom, corner) pair,
 // key = node_index << 24 | (8*atom + corner). Sorting the keys groups the
-// contributions of each node in increasing atom order.
-__global__ void k_spread_keys(const double* __restrict__ xyz, int64_t natoms, int nx, int ny, int nz,
-                              double h, double ox, double oy, double oz, int per,
-                              uint64_t* __restrict__ keys, int* __restrict__ flags) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= 8 * natoms) return;
+// contributions of each node in increasing atom order. Past the pairs, and for
+// an atom outside the box: all ones.
+__device__ __forceinline__ uint64_t spread_key(int64_t p, const double* __restrict__ xyz, int64_t natoms, int nx,
+                                               int ny, int nz, double h, double ox, double oy, double oz, int per,
+                                               int* __restrict__ flags) {
+    if (p >= 8 * natoms) return ~0ull;
     const int64_t a = p >> 3;
     const int c = (int)(p & 7);
     int i0, j0, k0;
@@ -371,11 +391,15 @@ __global__ void k_spread_keys(const double* __restrict__ xyz, int64_t natoms, in
     ok = cell_axis(xyz[3 * a + 2], oz, h, nz, per, k0, fz) && ok;
     if (!ok) {
         atomicOr(flags, 1);
-        keys[p] = ~0ull;
-        return;
+        return ~0ull;
     }
-    const int64_t node = corner_node(i0, j0, k0, c, nx, ny, nz);
-    keys[p] = ((uint64_t)node << 24) | (uint64_t)p;
+    return ((uint64_t)corner_node(i0, j0, k0, c, nx, ny, nz) << 24) | (uint64_t)p;
+}
+__global__ void k_spread_keys(const double* __restrict__ xyz, int64_t natoms, int nx, int ny, int nz,
+                              double h, double ox, double oy, double oz, int per,
+                              uint64_t* __restrict__ keys, int64_t n, int* __restrict__ flags) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < n) keys[p] = spread_key(p, xyz, natoms, nx, ny, nz, h, ox, oy, oz, per, flags);
 }
 
 // One compare-exchange step of a bitonic sorting network (ascending).
@@ -426,12 +450,10 @@ __global__ __launch_bounds__(1024) void k_bitonic_local(uint64_t* __restrict__ a
 
 // Charge spreading, step 2: the first key of each node's run sums the run in
 // key order (increasing atom index), starting from zero, and stores q_node.
-__global__ void k_spread_sum(const uint64_t* __restrict__ keys, int64_t npairs,
-                             const double* __restrict__ xyz, const double* __restrict__ charge,
-                             int nx, int ny, int nz, double h, double ox, double oy, double oz, int per,
-                             double* __restrict__ q) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= npairs) return;
+__device__ __forceinline__ void spread_run(const uint64_t* keys, int64_t i, int64_t npairs,
+                                           const double* __restrict__ xyz, const double* __restrict__ charge, int nx,
+                                           int ny, int nz, double h, double ox, double oy, double oz, int per,
+                                           double* __restrict__ q) {
     const uint64_t key = keys[i];
     if (key == ~0ull) return;
     const uint64_t node = key >> 24;
@@ -454,6 +476,37 @@ __global__ void k_spread_sum(const uint64_t* __restrict__ keys, int64_t npairs,
         s = s + charge[a] * wx * wy * wz;
     }
     q[node] = s;
+}
+__global__ void k_spread_sum(const uint64_t* __restrict__ keys, int64_t npairs,
+                             const double* __restrict__ xyz, const double* __restrict__ charge,
+                             int nx, int ny, int nz, double h, double ox, double oy, double oz, int per,
+                             double* __restrict__ q) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < npairs) spread_run(keys, i, npairs, xyz, charge, nx, ny, nz, h, ox, oy, oz, per, q);
+}
+// Both steps for up to kSortChunk keys by one workgroup, the keys in LDS: n keys
+// (a power of two >= 2), the same network with one pair per thread and turn.
+__device__ __forceinline__ void spread_small(uint64_t* s, int n, const double* __restrict__ xyz,
+                                             const double* __restrict__ charge, int64_t natoms, int nx, int ny, int nz,
+                                             double h, double ox, double oy, double oz, int per,
+                                             double* __restrict__ q, int* __restrict__ flags) {
+    for (int p = threadIdx.x; p < n; p += blockDim.x)
+        s[p] = spread_key(p, xyz, natoms, nx, ny, nz, h, ox, oy, oz, per, flags);
+    for (int k = 2; k <= n; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            __syncthreads();
+            for (int t = threadIdx.x; t < n / 2; t += blockDim.x) {
+                const int e = ((t & ~(j - 1)) << 1) | (t & (j - 1));
+                const uint64_t x = s[e], y = s[e + j];
+                if ((x > y) == ((e & k) == 0)) {
+                    s[e] = y;
+                    s[e + j] = x;
+                }
+            }
+        }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 8 * (int)natoms; i += blockDim.x)
+        spread_run(s, i, 8 * natoms, xyz, charge, nx, ny, nz, h, ox, oy, oz, per, q);
 }
 
 // Ghost point `t` of the six faces (x-, x+, y-, y+, z-, z+), in that order;
@@ -550,14 +603,14 @@ __device__ __forceinline__ double exp_nonpos(double x, const double* tab) {
 // Screened Coulomb sum of every atom at each ghost-face point, atoms in
 // index order through LDS records (x, y, z, q): phi = (1/eps_out) sum q e^(-kd)/d.
 // Ghost points lie one node outside the box and atoms inside it, so d >= h > 0.
-__global__ __launch_bounds__(kDhBlock) void k_dh_faces(
-        const double* __restrict__ xyz, const double* __restrict__ charge, int64_t natoms,
+__device__ __forceinline__ void dh_direct_block(
+        int64_t block, const double* __restrict__ xyz, const double* __restrict__ charge, int64_t natoms,
         int nx, int ny, int nz, double h, double ox, double oy, double oz,
         double kd, double eout, double* __restrict__ ghost, int64_t nghost) {
     __shared__ double4 sa[kDhBlock];
     __shared__ double s_tab[kExpTab];
     if (threadIdx.x < kExpTab) s_tab[threadIdx.x] = kExp2Frac[threadIdx.x];
-    const int64_t t = (int64_t)blockIdx.x * kDhBlock + threadIdx.x;
+    const int64_t t = block * kDhBlock + threadIdx.x;
     double px = 0, py = 0, pz = 0;
     if (t < nghost) ghost_point(t, nx, ny, nz, h, ox, oy, oz, px, py, pz);
     double s = 0.0;
@@ -587,6 +640,30 @@ __global__ __launch_bounds__(kDhBlock) void k_dh_faces(
         }
     }
     if (t < nghost) ghost[t] = s / eout;
+}
+
+__global__ __launch_bounds__(kDhBlock) void k_dh_faces(
+        const double* __restrict__ xyz, const double* __restrict__ charge, int64_t natoms,
+        int nx, int ny, int nz, double h, double ox, double oy, double oz,
+        double kd, double eout, double* __restrict__ ghost, int64_t nghost) {
+    dh_direct_block(blockIdx.x, xyz, charge, natoms, nx, ny, nz, h, ox, oy, oz, kd, eout, ghost, nghost);
+}
+
+// The parts of a small molecule's setup that need nothing of one another, in
+// one launch: workgroup 0 spreads the charges (up to kSortChunk keys), one per
+// atom classifies nodes, the rest take the boundary sum. Each is a chain of
+// latencies that leaves the device idle: 33^3 with 50 atoms, 11 launches and
+// 118 us in all before, 61 with this (3 launches).
+__global__ __launch_bounds__(kDhBlock) void k_setup_small(
+        const double* __restrict__ xyz, const double* __restrict__ radius, const double* __restrict__ charge,
+        int natoms, int nkeys, int nx, int ny, int nz, double h, double ox, double oy, double oz, int per, double kd,
+        double eout, uint8_t* __restrict__ mask, double* __restrict__ q, int* __restrict__ flags,
+        double* __restrict__ ghost, int64_t nghost) {
+    __shared__ uint64_t s_keys[kSortChunk];
+    const int block = (int)blockIdx.x;
+    if (block == 0) spread_small(s_keys, nkeys, xyz, charge, natoms, nx, ny, nz, h, ox, oy, oz, per, q, flags);
+    else if (block <= natoms) classify_atom(block - 1, xyz, radius, nx, ny, nz, h, ox, oy, oz, per, mask);
+    else dh_direct_block(block - 1 - natoms, xyz, charge, natoms, nx, ny, nz, h, ox, oy, oz, kd, eout, ghost, nghost);
 }
 
 // ---- the same sum with interpolated far fields
@@ -981,13 +1058,11 @@ pb_status dh_faces(const double* xyz, const double* charge, int64_t natoms, int 
     return PB_OK;
 }
 
-// Right-hand side: 4*pi*q/h^3 plus, for nodes on the box faces, the ghost
-// potential times the ghost-side edge dielectric over h^2 (x-, x+, y-, y+,
-// z-, z+ in that order).
+// The right-hand side of k_fields from edge arrays (fractional edges).
 __global__ void k_rhs(const double* __restrict__ q, const double* __restrict__ ex,
                       const double* __restrict__ ey, const double* __restrict__ ez,
                       const double* __restrict__ ghost, int nx, int ny, int nz,
-                      double h3, double ih2, int per, double* __restrict__ b) {
+                      double h3, double ih2, double* __restrict__ b) {
     const int64_t nn = (int64_t)nx * ny * nz;
     const int64_t fx = (int64_t)ny * nz, fy = (int64_t)nx * nz, fz = (int64_t)nx * ny;
     const double* gxm = ghost;
@@ -1000,10 +1075,6 @@ __global__ void k_rhs(const double* __restrict__ q, const double* __restrict__ e
          n += (int64_t)gridDim.x * blockDim.x) {
         const int64_t i = n % nx, j = (n / nx) % ny, k = n / fz;
         double fold = 0.0;
-        if (per) {   // no boundary values: the box repeats
-            b[n] = kFourPi * q[n] / h3;
-            continue;
-        }
         if (i == 0) fold = fold + ex[(nx + 1) * (j + ny * k)] * ih2 * gxm[j + ny * k];
         if (i == nx - 1) fold = fold + ex[nx + (nx + 1) * (j + ny * k)] * ih2 * gxp[j + ny * k];
         if (j == 0) fold = fold + ey[i + (int64_t)nx * ((ny + 1) * k)] * ih2 * gym[i + nx * k];
@@ -1173,9 +1244,18 @@ pb_status setup_enqueue(const pb_grid* g, int64_t natoms, const double* xyz, con
     double* q = qgrid ? qgrid : w.qgrid;
     const int per = g->boundary == PB_BOUNDARY_PERIODIC ? 1 : 0;
 
-    hipLaunchKernelGGL(k_fill_u8, dim3(1), dim3(64), 0, st, (uint8_t*)w.flags, (int64_t)256, (uint8_t)0);
-    hipLaunchKernelGGL(k_fill_u8, dim3(blocks_for(nmask, 256)), dim3(256), 0, st, m, nmask, (uint8_t)0);
-    if (natoms > 0)
+    const int64_t P = next_pow2(std::max<int64_t>(2, 8 * natoms));
+    const double kd = std::sqrt(kappa_d2);
+    // one launch where the keys fit a workgroup's LDS and the boundary sum is direct
+    const bool small = P <= kSortChunk && (per || dh_direct(dh_plan(nx, ny, nz, natoms, h, ox, oy, oz, kd), natoms));
+    hipLaunchKernelGGL(k_setup_clear, dim3(blocks_for(std::max(nmask / 8, nn), 256)), dim3(256), 0, st, w.flags, m,
+                       nmask, q, nn);
+    if (small)
+        hipLaunchKernelGGL(k_setup_small,
+                           dim3((unsigned)(1 + natoms + (per ? 0 : (ngh + kDhBlock - 1) / kDhBlock))), dim3(kDhBlock),
+                           0, st, xyz, radius, charge, (int)natoms, (int)P, nx, ny, nz, h, ox, oy, oz, per, kd, eps_out,
+                           m, q, w.flags, w.ghost, ngh);
+    else if (natoms > 0)
         hipLaunchKernelGGL(k_classify, dim3((unsigned)natoms), dim3(256), 0, st, xyz, radius, natoms,
                            nx, ny, nz, h, ox, oy, oz, per, m);
     if (per) {
@@ -1186,13 +1266,36 @@ pb_status setup_enqueue(const pb_grid* g, int64_t natoms, const double* xyz, con
         hipLaunchKernelGGL(k_wrap_ghosts, dim3(blocks_for((int64_t)(nx + 2) * (ny + 2), 256)), dim3(256), 0, st,
                            m, nx, ny, nz, 2);
     }
-    const int64_t nedge = (int64_t)(nx + 1) * ny * nz + (int64_t)nx * (ny + 1) * nz +
-                          (int64_t)nx * ny * (nz + 1) + nn;
-    hipLaunchKernelGGL(k_edges, dim3(blocks_for(nedge, 256)), dim3(256), 0, st, m, nx, ny, nz,
-                       eps_in, eps_out, eps_out * kappa_d2, eps_x, eps_y, eps_z, kappa2);
+    if (!small) {
+        // charges: keys, sort, per-node run sums
+        if (natoms > 0) {
+            hipLaunchKernelGGL(k_spread_keys, dim3(blocks_for(P, 256, 1 << 30)), dim3(256), 0, st, xyz, natoms, nx, ny,
+                               nz, h, ox, oy, oz, per, w.keys, P, w.flags);
+            const pb_status es = bitonic_sort(w.keys, P, st);
+            if (es != PB_OK) return es;
+            hipLaunchKernelGGL(k_spread_sum, dim3(blocks_for(8 * natoms, 256, 1 << 30)), dim3(256), 0, st, w.keys,
+                               8 * natoms, xyz, charge, nx, ny, nz, h, ox, oy, oz, per, q);
+        }
+        // boundary potential on the face ghosts (free space only)
+        if (!per) {
+            const pb_status es = dh_faces(xyz, charge, natoms, nx, ny, nz, h, ox, oy, oz, kd, eps_out, w.ghost, ngh,
+                                          w.dh, st);
+            if (es != PB_OK) return es;
+        }
+    }
+    const int64_t fields = (int64_t)(nx + 1) * (ny + 1) * (nz + 1);
+    const double h3 = std::pow(h, 3.0), ih2 = 1.0 / (h * h);
+    const bool two_point = !(frac && natoms > 0);   // the fractional edges come before the right-hand side
+    auto launch_fields = [&](auto index) {
+        hipLaunchKernelGGL(k_fields<decltype(index)>, dim3(blocks_for(fields, 256)), dim3(256), 0, st, m, nx, ny, nz,
+                           eps_in, eps_out, eps_out * kappa_d2, (const double*)q, (const double*)w.ghost, h3, ih2, per,
+                           eps_x, eps_y, eps_z, kappa2, two_point ? rhs : nullptr);
+    };
+    if (fields < (int64_t(1) << 31)) launch_fields((unsigned)0);
+    else launch_fields((int64_t)0);
     if (frac && natoms > 0) {
         // cell list of the atoms, then the fractional edges over the two-point ones
-        double* rmax_d = (double*)w.ghost;   // the boundary buffer is free until the face sums
+        double* rmax_d = (double*)w.keys;   // the keys are done with
         hipLaunchKernelGGL(k_max_radius, dim3(1), dim3(1024), 0, st, radius, natoms, rmax_d);
         double rmax = 0.0;
         PB_HIP(hipMemcpyAsync(&rmax, rmax_d, sizeof(double), hipMemcpyDeviceToHost, st));
@@ -1201,45 +1304,25 @@ pb_status setup_enqueue(const pb_grid* g, int64_t natoms, const double* xyz, con
         const int mcell = std::max(1, (int)std::ceil(rmax / h));
         const int ncx = (nx + 2 + mcell - 1) / mcell, ncy = (ny + 2 + mcell - 1) / mcell, ncz = (nz + 2 + mcell - 1) / mcell;
         const int64_t ncells = (int64_t)ncx * ncy * ncz;
-        const int64_t P = next_pow2(std::max<int64_t>(2, natoms));
-        hipLaunchKernelGGL(k_fill_u64, dim3(blocks_for(P, 256)), dim3(256), 0, st, w.keys, P, ~0ull);
+        const int64_t Pc = next_pow2(std::max<int64_t>(2, natoms));
+        hipLaunchKernelGGL(k_fill_u64, dim3(blocks_for(Pc, 256)), dim3(256), 0, st, w.keys, Pc, ~0ull);
         hipLaunchKernelGGL(k_cell_keys, dim3(blocks_for(natoms, 256, 1 << 30)), dim3(256), 0, st, xyz, natoms, nx, ny,
                            nz, h, ox, oy, oz, mcell, ncx, ncy, w.keys);
-        for (int64_t k = 2; k <= P; k <<= 1)
+        for (int64_t k = 2; k <= Pc; k <<= 1)
             for (int64_t j = k >> 1; j > 0; j >>= 1)
-                hipLaunchKernelGGL(k_bitonic_step, dim3(blocks_for(P, 256, 1 << 30)), dim3(256), 0, st, w.keys, P,
+                hipLaunchKernelGGL(k_bitonic_step, dim3(blocks_for(Pc, 256, 1 << 30)), dim3(256), 0, st, w.keys, Pc,
                                    j, k);
         hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(ncells, 256)), dim3(256), 0, st, w.cell_start, ncells, 0);
         hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for(ncells, 256)), dim3(256), 0, st, w.cell_end, ncells, 0);
         hipLaunchKernelGGL(k_cell_bounds, dim3(blocks_for(natoms, 256, 1 << 30)), dim3(256), 0, st,
                            (const uint64_t*)w.keys, natoms, w.cell_start, w.cell_end);
-        const int64_t nedge3 = nedge - nn;
+        const int64_t nedge3 = (int64_t)(nx + 1) * ny * nz + (int64_t)nx * (ny + 1) * nz + (int64_t)nx * ny * (nz + 1);
         hipLaunchKernelGGL(k_edges_fraction, dim3(blocks_for(nedge3, 256)), dim3(256), 0, st, xyz, radius,
                            (const uint64_t*)w.keys, (const int*)w.cell_start, (const int*)w.cell_end, nx, ny, nz, h,
                            ox, oy, oz, rmax, mcell, ncx, ncy, ncz, eps_in, eps_out, eps_x, eps_y, eps_z, w.flags);
+        hipLaunchKernelGGL(k_rhs, dim3(blocks_for(nn, 256)), dim3(256), 0, st, q, eps_x, eps_y, eps_z, w.ghost, nx, ny,
+                           nz, h3, ih2, rhs);
     }
-
-    // charges: keys, sort, per-node run sums
-    hipLaunchKernelGGL(k_fill_f64, dim3(blocks_for(nn, 256)), dim3(256), 0, st, q, nn, 0.0);
-    if (natoms > 0) {
-        const int64_t np = 8 * natoms;
-        const int64_t P = next_pow2(std::max<int64_t>(2, np));
-        hipLaunchKernelGGL(k_fill_u64, dim3(blocks_for(P, 256)), dim3(256), 0, st, w.keys, P, ~0ull);
-        hipLaunchKernelGGL(k_spread_keys, dim3(blocks_for(np, 256, 1 << 30)), dim3(256), 0, st, xyz,
-                           natoms, nx, ny, nz, h, ox, oy, oz, per, w.keys, w.flags);
-        const pb_status es = bitonic_sort(w.keys, P, st);
-        if (es != PB_OK) return es;
-        hipLaunchKernelGGL(k_spread_sum, dim3(blocks_for(np, 256, 1 << 30)), dim3(256), 0, st, w.keys,
-                           np, xyz, charge, nx, ny, nz, h, ox, oy, oz, per, q);
-    }
-    // boundary potential on the face ghosts (free space only)
-    if (!per) {
-        const pb_status es = dh_faces(xyz, charge, natoms, nx, ny, nz, h, ox, oy, oz, std::sqrt(kappa_d2), eps_out,
-                                      w.ghost, ngh, w.dh, st);
-        if (es != PB_OK) return es;
-    }
-    hipLaunchKernelGGL(k_rhs, dim3(blocks_for(nn, 256)), dim3(256), 0, st, q, eps_x, eps_y, eps_z,
-                       w.ghost, nx, ny, nz, std::pow(h, 3.0), 1.0 / (h * h), per, rhs);
     if (per) {   // sums of b and kbar^2 (fixed order) into the unused ghost buffer, then the background
         hipLaunchKernelGGL(k_sum_fixed, dim3(1), dim3(1024), 0, st, (const double*)rhs, nn, w.ghost);
         hipLaunchKernelGGL(k_sum_fixed, dim3(1), dim3(1024), 0, st, (const double*)kappa2, nn, w.ghost + 1);
