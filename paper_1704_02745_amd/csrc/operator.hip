@@ -238,15 +238,37 @@ __global__ void k_add_correction(double* __restrict__ x, const float* __restrict
 }
 
 // Padded (T) -> caller's unpadded FP64 array.
+// refuse: nothing is written when *refuse has one of the bits of a refused system.
+constexpr int kRefused = FLAG_BAD_COEF | FLAG_BAD_RHS | FLAG_BAD_GUESS;
 template <typename T>
 __global__ void k_unpad(const T* __restrict__ xp, int nx, int ny, int nz, int64_t sp,
-                        double* __restrict__ out) {
+                        double* __restrict__ out, const int* __restrict__ refuse) {
+    if (refuse && (*refuse & kRefused)) return;
     const int64_t plane = (int64_t)nx * ny;
     const int64_t n = plane * nz;
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n;
          t += (int64_t)gridDim.x * blockDim.x) {
         const int64_t k = t / plane;
         out[t] = (double)xp[t - k * plane + k * sp];
+    }
+}
+
+// The FP32 potential in FP64, padded for the residual and unpadded for the caller.
+__global__ void k_hand_back(const float* __restrict__ x, double* __restrict__ x64, int64_t plane, int64_t sp,
+                            int64_t npad, double* __restrict__ out, const int* __restrict__ refuse) {
+    const bool write = !(refuse && (*refuse & kRefused));
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < npad; t += (int64_t)gridDim.x * blockDim.x) {
+        const double v = (double)x[t];
+        x64[t] = v;
+        const int64_t k = npad < ((int64_t)1 << 31) ? (int64_t)((unsigned)t / (unsigned)sp) : t / sp, p = t - k * sp;
+        if (write && p < plane) out[k * plane + p] = v;
+    }
+}
+
+__global__ void k_clear2(int* __restrict__ a, int64_t na, int* __restrict__ b, int64_t nb) {
+    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < na + nb; t += (int64_t)gridDim.x * blockDim.x) {
+        if (t < na) a[t] = 0;
+        else b[t - na] = 0;
     }
 }
 
@@ -408,13 +430,25 @@ pb_status launch_f32_to_f64(const float* a, double* b, int64_t n, hipStream_t st
 }
 
 template <typename T>
-pb_status launch_unpad(const T* xp, const Layout& L, double* out, hipStream_t st) {
-    hipLaunchKernelGGL(k_unpad<T>, dim3(grid_for(L.n)), dim3(256), 0, st, xp, L.nx, L.ny, L.nz, L.sp, out);
+pb_status launch_unpad(const T* xp, const Layout& L, double* out, hipStream_t st, const int* refuse) {
+    hipLaunchKernelGGL(k_unpad<T>, dim3(grid_for(L.n)), dim3(256), 0, st, xp, L.nx, L.ny, L.nz, L.sp, out, refuse);
     PB_HIP(hipGetLastError());
     return PB_OK;
 }
-template pb_status launch_unpad<float>(const float*, const Layout&, double*, hipStream_t);
-template pb_status launch_unpad<double>(const double*, const Layout&, double*, hipStream_t);
+template pb_status launch_unpad<float>(const float*, const Layout&, double*, hipStream_t, const int*);
+template pb_status launch_unpad<double>(const double*, const Layout&, double*, hipStream_t, const int*);
+
+pb_status launch_hand_back(const float* x, double* x64, const Layout& L, double* out, const int* refuse,
+                           hipStream_t st) {
+    hipLaunchKernelGGL(k_hand_back, dim3(grid_for(L.npad)), dim3(256), 0, st, x, x64, L.plane, L.sp, L.npad, out, refuse);
+    PB_HIP(hipGetLastError());
+    return PB_OK;
+}
+pb_status launch_clear2(int* a, int64_t na, int* b, int64_t nb, hipStream_t st) {
+    hipLaunchKernelGGL(k_clear2, dim3(grid_for(na + nb)), dim3(256), 0, st, a, na, b, nb);
+    PB_HIP(hipGetLastError());
+    return PB_OK;
+}
 
 template <typename T>
 pb_status launch_fill(T* p, int64_t n, T v, hipStream_t st) {

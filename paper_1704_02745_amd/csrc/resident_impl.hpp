@@ -239,8 +239,9 @@ pb_status resident_solve(const Layout& L, const SolveBufs<T>& s, SyncState* sync
         if (launch_resident_start<T>(L, s.op, s.b, s.x, r0, periodic, st) != PB_OK) return PB_ERR_HIP;
         a.r0 = r0;
     }
-    if (launch_fill<int>((int*)sync, (int64_t)(sizeof(SyncState) / sizeof(int)), 0, st) != PB_OK) return PB_ERR_HIP;
-    if (launch_fill<int>((int*)partials, (int64_t)2 * p.grid * kSlotWords * 2, 0, st) != PB_OK) return PB_ERR_HIP;
+    if (launch_clear2((int*)sync, (int64_t)(sizeof(SyncState) / sizeof(int)), (int*)partials,
+                      (int64_t)2 * p.grid * kSlotWords * 2, st) != PB_OK)
+        return PB_ERR_HIP;
     hipEvent_t ev[2] = {nullptr, nullptr};
     const bool timed = res && !res->untimed;
     if (timed) {

@@ -23,7 +23,12 @@ pb_status launch_remove_mean(double* v, const Layout& L, double* partials, doubl
 pb_status launch_add_correction(double* x, const float* dx, int64_t npad, hipStream_t st);
 pb_status launch_f32_to_f64(const float* a, double* b, int64_t n, hipStream_t st);
 template <typename T>
-pb_status launch_unpad(const T* xp, const Layout& L, double* out, hipStream_t st);
+pb_status launch_unpad(const T* xp, const Layout& L, double* out, hipStream_t st, const int* refuse = nullptr);
+// x in FP64, padded into x64 and unpadded into out; `out` stays as it is when
+// *refuse (nullable) tells of a refused system, here and above.
+pb_status launch_hand_back(const float* x, double* x64, const Layout& L, double* out, const int* refuse,
+                           hipStream_t st);
+pb_status launch_clear2(int* a, int64_t na, int* b, int64_t nb, hipStream_t st);
 template <typename T>
 pb_status launch_fill(T* p, int64_t n, T v, hipStream_t st);
 
