@@ -19,7 +19,9 @@
 //
 // Barrier: every workgroup stores its sums into its own slot as 8-byte words
 // (half of a double, barrier tag), and every workgroup polls all slots until
-// the tags match, then adds them in one fixed order. A word carries its own
+// the tags match, then adds them in one fixed order; with many workgroups
+// (slot_groups) the first of every 16 polls these and stores their sums into a
+// group slot, and all poll the group slots. A word carries its own
 // tag, so there is no arrival counter, no second round trip for the data and no
 // order to keep between words. The face values of q, stored before, are waited
 // for (vmcnt) before the slot is written. All cross-workgroup accesses go past
@@ -49,7 +51,7 @@ struct RArgs {
     int maxiter;
     int warm;
     SyncState* S;
-    unsigned long long* slots;   // 2 x workgroups x kSlotWords, cleared before the launch
+    unsigned long long* slots;   // slot_words, cleared before the launch
     long long timeout_ticks;
     long long first_timeout_ticks;   // of the first barrier (a batch's workgroups come to it from earlier problems)
     T* xs;                // forms with x in memory: x by brick (one value per thread and plane)
@@ -68,7 +70,23 @@ constexpr int kSlotWords = 16;            // two words per sum (low half, high h
 // Barrier words are reached through global-memory instructions also where the
 // compiler cannot see the pointer's origin (a batch's argument table).
 typedef __attribute__((address_space(1))) unsigned long long GlobalWord;
-constexpr int kMaxResidentGroups = 256;   // workgroups that the poll of one barrier covers
+constexpr int kMaxResidentGroups = 256;   // workgroups of a problem at most
+constexpr int kSlotGroup = 16;            // slots that one wave polls
+static_assert(kMaxResidentGroups <= kSlotGroup * kSlotGroup, "two rounds of polling");
+// Group slots of a barrier over G workgroups, 0 where each polls all the slots.
+// One round costs a latency less, two rounds a fraction of the traffic: with 99
+// workgroups (65 x 57 x 61) 4.24 us a pass against 4.66, with 143 (81 x 77 x 85) 5.27
+// against 5.04, with 200 (97^3) 6.30 against 5.51, with 210 (97 x 105 x 89 FP64) 7.61
+// against 6.43, with 252 (141^3) 12.2 against 10.4. Where the passes are long the
+// workgroups come to the barrier one by one and the traffic is hidden: 19 planes
+// 6.96 against 7.0 to 7.3 (129^3), 43 planes 15.1 against 15.6 (161^3). The kernels of
+// up to 6 planes, whose plans have fewer workgroups, go without the choice (0.09 us
+// a pass).
+__host__ __device__ constexpr int slot_groups(int nzb, int G) {
+    return nzb > 6 && (nzb <= 14 || nzb == 24) && G > 128 ? (G + kSlotGroup - 1) / kSlotGroup : 0;
+}
+// Barrier words of a problem, both parities.
+__host__ __device__ constexpr int slot_words(int nzb, int G) { return 2 * (G + slot_groups(nzb, G)) * kSlotWords; }
 
 // The value, unknown to the optimizer: keeps what is derived from it (1/d,
 // offsets) from being hoisted out of the iteration into registers of its own.
@@ -442,56 +460,100 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's face values have arrived
         __syncthreads();
         const unsigned tag = (unsigned)(b + 1);
-        GlobalWord* slots = (GlobalWord*)(uintptr_t)a.slots + (size_t)(b & 1) * G * kSlotWords;
-        if (wave == 0) {
-            const double v = lds_rows_sum8(red, ROWS);
+        GlobalWord* slots = (GlobalWord*)(uintptr_t)a.slots + (size_t)(b & 1) * (G + slot_groups(NZ, G)) * kSlotWords;
+        auto put = [&](int slot, double v) {   // lane n's sum n
             if (lane < 8) {
                 const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-                GlobalWord* m = slots + (size_t)w * kSlotWords + 2 * lane;
+                GlobalWord* m = slots + (size_t)slot * kSlotWords + 2 * lane;
                 __hip_atomic_store(m, (u << 32) | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(m + 1, (u & 0xffffffff00000000ull) | tag, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
             }
-        }
-        // thread n polls the sum n & 7 of slots n/8, n/8 + BS/8, ...
-        constexpr int M = (kMaxResidentGroups * 8 + BS - 1) / BS;
-        double part = 0.0;
-        if (opaque_v(tid >> 3) < G) {
-            unsigned long long lo[M], hi[M];
-            long long t0 = 0;
-            while (true) {
-                unsigned bad = 0;
-#pragma unroll
-                for (int m = 0; m < M; ++m) {
-                    if (m > 0 && m * (BS / 8) >= G) break;   // uniform
-                    const int slot = min((tid >> 3) + m * (BS / 8), G - 1);
-                    const GlobalWord* p = slots + (size_t)slot * kSlotWords + 2 * (tid & 7);
-                    lo[m] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    hi[m] = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-#pragma unroll
-                for (int m = 0; m < M; ++m) {
-                    if (m > 0 && m * (BS / 8) >= G) break;
-                    bad |= ((unsigned)lo[m] ^ tag) | ((unsigned)hi[m] ^ tag);
-                }
-                if (bad == 0) break;
-                const long long now = wall_clock64();
-                if (t0 == 0) t0 = now;
-                if (now - t0 > (b == 0 ? a.first_timeout_ticks : a.timeout_ticks)) {
-                    s_flag[0] = 1;
-                    break;
-                }
+        };
+        double tot;
+        if (slot_groups(NZ, G) > 0) {
+            if (wave == 0) {
+                // the sums of up to kSlotGroup slots: lane n polls sum n & 7 of slots n / 8 and
+                // n / 8 + 8, and gets the total of that sum
+                auto get = [&](int first, int count) -> double {
+                    const int s0 = opaque_v(lane >> 3);
+                    const bool on0 = s0 < count, on1 = s0 + 8 < count;
+                    const GlobalWord* p0 = slots + (size_t)(first + (on0 ? s0 : 0)) * kSlotWords + 2 * (lane & 7);
+                    const GlobalWord* p1 = slots + (size_t)(first + (on1 ? s0 + 8 : 0)) * kSlotWords + 2 * (lane & 7);
+                    unsigned long long l0, h0, l1, h1;
+                    long long t0 = 0;
+                    while (true) {
+                        l0 = __hip_atomic_load(p0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        h0 = __hip_atomic_load(p0 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        l1 = __hip_atomic_load(p1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        h1 = __hip_atomic_load(p1 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if ((((unsigned)l0 ^ tag) | ((unsigned)h0 ^ tag) | ((unsigned)l1 ^ tag) | ((unsigned)h1 ^ tag)) == 0)
+                            break;
+                        const long long now = wall_clock64();
+                        if (t0 == 0) t0 = now;
+                        if (now - t0 > (b == 0 ? a.first_timeout_ticks : a.timeout_ticks)) {
+                            s_flag[0] = 1;
+                            break;
+                        }
+                    }
+                    const double v0 = __longlong_as_double((long long)((h0 & 0xffffffff00000000ull) | (l0 >> 32)));
+                    const double v1 = __longlong_as_double((long long)((h1 & 0xffffffff00000000ull) | (l1 >> 32)));
+                    double t = on0 ? v0 : 0.0;
+                    t += on1 ? v1 : 0.0;
+                    t += dpp_d<kDppRor8>(t);
+                    t += __shfl_xor(t, 16);
+                    t += __shfl_xor(t, 32);
+                    return t;
+                };
+                put(w, lds_rows_sum8(red, ROWS));
+                if (w % kSlotGroup == 0) put(G + w / kSlotGroup, get(w, min(kSlotGroup, G - w)));
+                const double t = get(G, slot_groups(NZ, G));
+                if (lane < 8) red2[lane] = t;
             }
+            __syncthreads();
+            tot = red2[lane & 7];
+        } else {
+            if (wave == 0) put(w, lds_rows_sum8(red, ROWS));
+            // thread n polls the sum n & 7 of slots n/8, n/8 + BS/8, ...
+            constexpr int M = (kMaxResidentGroups * 8 + BS - 1) / BS;
+            double part = 0.0;
+            if (opaque_v(tid >> 3) < G) {
+                unsigned long long lo[M], hi[M];
+                long long t0 = 0;
+                while (true) {
+                    unsigned bad = 0;
 #pragma unroll
-            for (int m = 0; m < M; ++m)
-                if ((tid >> 3) + m * (BS / 8) < G)
-                    part += __longlong_as_double((long long)((hi[m] & 0xffffffff00000000ull) | (lo[m] >> 32)));
+                    for (int m = 0; m < M; ++m) {
+                        if (m > 0 && m * (BS / 8) >= G) break;   // uniform
+                        const int slot = min((tid >> 3) + m * (BS / 8), G - 1);
+                        const GlobalWord* p = slots + (size_t)slot * kSlotWords + 2 * (tid & 7);
+                        lo[m] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        hi[m] = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+#pragma unroll
+                    for (int m = 0; m < M; ++m) {
+                        if (m > 0 && m * (BS / 8) >= G) break;
+                        bad |= ((unsigned)lo[m] ^ tag) | ((unsigned)hi[m] ^ tag);
+                    }
+                    if (bad == 0) break;
+                    const long long now = wall_clock64();
+                    if (t0 == 0) t0 = now;
+                    if (now - t0 > (b == 0 ? a.first_timeout_ticks : a.timeout_ticks)) {
+                        s_flag[0] = 1;
+                        break;
+                    }
+                }
+#pragma unroll
+                for (int m = 0; m < M; ++m)
+                    if ((tid >> 3) + m * (BS / 8) < G)
+                        part += __longlong_as_double((long long)((hi[m] & 0xffffffff00000000ull) | (lo[m] >> 32)));
+            }
+            asm volatile("" ::: "memory");
+            part += dpp_d<kDppRor8>(part);
+            if ((lane & 15) < 8) red2[(wave * 4 + (lane >> 4)) * 8 + (lane & 7)] = part;
+            __syncthreads();
+            tot = lds_rows_sum8(red2, ROWS);
         }
-        asm volatile("" ::: "memory");
-        part += dpp_d<kDppRor8>(part);
-        if ((lane & 15) < 8) red2[(wave * 4 + (lane >> 4)) * 8 + (lane & 7)] = part;
-        __syncthreads();
-        const double tot = lds_rows_sum8(red2, ROWS);
 #pragma unroll
         for (int k = 0; k < 8; ++k) out[k] = readlane_d(tot, k);
         ++b;
