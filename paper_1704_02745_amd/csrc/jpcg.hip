@@ -36,6 +36,15 @@
 // once). Its coded form reads the operator as one word of dictionary codes
 // per node instead (28 bytes per node; coded.hip builds the words).
 //
+// The 40-byte form and its coded form take x every second pass where they can:
+// with p_{l-1} = z + beta p_{l-2}, the pass that has p_{l-1} and z = r/d at hand
+// also has p_{l-2} = (p_{l-1} - z) / beta, so a pass may leave x alone and the next
+// adds both steps, 8 bytes per node in two passes less (36 and 24 bytes on
+// average; 257^3 coded, default tiling, 123 -> 117 us a pass). beta must be at least 1/8: the
+// division then enlarges the rounding of p_{l-1} in one step's share of x eight
+// times at most, against one rounding of x itself that is saved. Whether a pass
+// takes x follows from beta alone, so it is the same in both forms.
+//
 // Reductions and the grid barrier: each tile reduces its sums in a fixed
 // order into its own slot; workgroups arrive on counters spread over eight
 // cache lines, and after the barrier every workgroup sums all tile slots in
@@ -846,6 +855,14 @@ __device__ __forceinline__ void ghost_of(const KArgs<T>& a, int64_t q0, int nv, 
     }
 }
 
+// What a pass of the 40-byte form does with x: nothing, x += a p_old, or also
+// x += c (p_old - r_old/d), the step of the direction before p_old.
+template <typename T>
+struct XStep {
+    int mode;   // 0, 1, 2
+    T a, c;
+};
+
 // One pass on one tile, 40-byte form: the same iteration as pass_tile, but
 // q_{l-1} = A p_{l-2} is recomputed from the stored p_{l-2} instead of being
 // stored by the previous pass. Per node the pass reads r, p_old, d, cx, cy,
@@ -861,7 +878,7 @@ __device__ __forceinline__ void ghost_of(const KArgs<T>& a, int64_t q0, int nv, 
 // inner ring groups on the first 2*halo/VEC threads, outer ring groups on the
 // last 2*halo/VEC threads (the tiling guarantees 2*halo/VEC <= BS).
 template <typename T, int BS, bool NT, bool PER>
-__device__ void pass_tile40(const KArgs<T>& a, int tile, int o, int n, T alpha, T beta, T* lds,
+__device__ void pass_tile40(const KArgs<T>& a, int tile, int o, int n, T alpha, T beta, XStep<T> xs, T* lds,
                             double (&acc)[NPART]) {
 #pragma clang fp contract(off)
     constexpr int W = Vec<T>::n;
@@ -888,7 +905,7 @@ __device__ void pass_tile40(const KArgs<T>& a, int tile, int o, int n, T alpha, 
     const T* __restrict__ CY = a.op.cy;
     const T* __restrict__ CZ = a.op.cz;
     const T* __restrict__ DD = a.op.d;
-    const bool do_x = alpha != T(0);
+    const bool do_x = xs.mode != 0;
     const V z0 = vzero<T>();
 
     const int tid = threadIdx.x;
@@ -1062,7 +1079,11 @@ __device__ void pass_tile40(const KArgs<T>& a, int tile, int o, int n, T alpha, 
                 const T r = fma(-alpha, qo, vget(r_o, u));
                 vget(rn_n, u) = r;
                 vget(pn_n, u) = fma(beta, vget(po_c, u), r * jacobi_inv(vget(d_n, u)));
-                if (xu) vget(x_n, u) = fma(alpha, vget(po_c, u), vget(x_n, u));
+                if (xu) {
+                    vget(x_n, u) = fma(xs.a, vget(po_c, u), vget(x_n, u));
+                    if (xs.mode == 2)
+                        vget(x_n, u) = fma(xs.c, vget(po_c, u) - vget(r_o, u) * jacobi_inv(vget(d_n, u)), vget(x_n, u));
+                }
             }
             vstore(PNn + (pos - nbase), pn_n);
             if (own1) {
@@ -1234,8 +1255,8 @@ __device__ __forceinline__ void lds4(float* p, const float4& v) { *reinterpret_c
 // Threads past the segment's end work on a copy of the last group (their
 // loads stay in bounds) and store nothing and add nothing to the sums.
 template <int BS, bool NT, bool PER>
-__device__ void pass_tile_coded(const KArgs<float>& a, int tile, int o, int n, float alpha, float beta, float* lds,
-                                const float* tv, double (&acc)[NPART]) {
+__device__ void pass_tile_coded(const KArgs<float>& a, int tile, int o, int n, float alpha, float beta,
+                                XStep<float> xs, float* lds, const float* tv, double (&acc)[NPART]) {
 #pragma clang fp contract(off)
     constexpr int W = 4;
     using V = float4;
@@ -1259,7 +1280,7 @@ __device__ void pass_tile_coded(const KArgs<float>& a, int tile, int o, int n, f
     float* rnew = n ? a.r[1] : a.r[0];
     float* pnew = n ? a.p[1] : a.p[0];
     const float* CW = a.cw;
-    const bool do_x = alpha != 0.0f;
+    const bool do_x = xs.mode != 0;
     const V z0 = make_float4(0.f, 0.f, 0.f, 0.f);
 
     const int tid = threadIdx.x;
@@ -1449,7 +1470,11 @@ __device__ void pass_tile_coded(const KArgs<float>& a, int tile, int o, int n, f
                 const float r = fmaf(-alpha, qo, vget(cur.r, u));
                 vget(rn_n, u) = r;
                 vget(pn_n, u) = fmaf(beta, vget(po_c, u), r * vget(iv_n, u));
-                if (xu) vget(xv, u) = fmaf(alpha, vget(po_c, u), vget(xv, u));
+                if (xu) {
+                    vget(xv, u) = fmaf(xs.a, vget(po_c, u), vget(xv, u));
+                    if (xs.mode == 2)
+                        vget(xv, u) = fmaf(xs.c, vget(po_c, u) - vget(cur.r, u) * vget(iv_n, u), vget(xv, u));
+                }
             }
             if (valid) lds4(PNn + ln, pn_n);
         }
@@ -1574,8 +1599,9 @@ __device__ void pass_tile_coded(const KArgs<float>& a, int tile, int o, int n, f
     }
 }
 
+// x += alpha p (+ c p2 where c is not zero), or x = 0.
 template <typename T, int BS>
-__device__ void final_tile(const KArgs<T>& a, int tile, T alpha, const T* p, bool zero) {
+__device__ void final_tile(const KArgs<T>& a, int tile, T alpha, const T* p, T c, const T* p2, bool zero) {
     constexpr int W = Vec<T>::n;
     using V = typename Vec<T>::type;
     const TileBox tb = tile_box(a, tile);
@@ -1589,6 +1615,11 @@ __device__ void final_tile(const KArgs<T>& a, int tile, T alpha, const T* p, boo
                 const V pv = vload(p + g);
 #pragma unroll
                 for (int u = 0; u < Vec<T>::n; ++u) vget(xv, u) = vget(xv, u) + alpha * vget(pv, u);
+                if (c != T(0)) {
+                    const V p2v = vload(p2 + g);
+#pragma unroll
+                    for (int u = 0; u < Vec<T>::n; ++u) vget(xv, u) = vget(xv, u) + c * vget(p2v, u);
+                }
             }
             vstore(a.x + g, xv);
         }
@@ -1598,7 +1629,7 @@ __device__ void final_tile(const KArgs<T>& a, int tile, T alpha, const T* p, boo
 // ------------------------------------------------------------------ kernel
 
 struct Scal {
-    double alpha, beta, rr, bb;
+    double alpha, beta, rr, bb, x_pending, x_beta;
     int iters, done, status, zero;
 };
 
@@ -1666,7 +1697,9 @@ __device__ void run_problem(const KArgs<T>& a, int w, int G, bool xcd_map, unsig
             else if (a.maxiter <= 0) { done = 1; status = PB_NOT_CONVERGED; }
             sc.alpha = 0.0; sc.beta = 0.0; sc.rr = rr; sc.bb = bb;
             sc.iters = 0; sc.done = done; sc.status = status; sc.zero = zero;
+            sc.x_pending = 0.0; sc.x_beta = 0.0;
             if (lead) {
+                S->x_pending = 0.0; S->x_beta = 0.0;
                 S->rr = rr; S->bb = bb; S->alpha = 0.0; S->beta = 0.0; S->iters = 0;
                 S->done = done; S->status = status; S->zero_rhs = zero;
             }
@@ -1676,6 +1709,7 @@ __device__ void run_problem(const KArgs<T>& a, int w, int G, bool xcd_map, unsig
         if (threadIdx.x == 0) {
             sc.alpha = ld_agent_d(&S->alpha); sc.beta = ld_agent_d(&S->beta);
             sc.rr = ld_agent_d(&S->rr); sc.bb = ld_agent_d(&S->bb);
+            sc.x_pending = ld_agent_d(&S->x_pending); sc.x_beta = ld_agent_d(&S->x_beta);
             sc.iters = ld_agent_i(&S->iters); sc.done = ld_agent_i(&S->done);
             sc.status = ld_agent_i(&S->status); sc.zero = ld_agent_i(&S->zero_rhs);
         }
@@ -1687,15 +1721,27 @@ __device__ void run_problem(const KArgs<T>& a, int w, int G, bool xcd_map, unsig
     while (!sc.done && (a.chunk <= 0 || this_launch < a.chunk)) {
         const int o = it & 1, n = (it + 1) & 1;
         const T alpha = (T)sc.alpha, beta = (T)sc.beta;
+        XStep<T> xs{alpha != T(0) ? 1 : 0, alpha, T(0)};
+        double x_pending = 0.0, x_beta = 0.0;   // left for the next pass
+        if (SCH == 1 && xs.mode == 1) {
+            if (sc.x_pending != 0.0) {
+                xs.mode = 2;
+                xs.c = (T)(sc.x_pending / sc.x_beta);
+            } else if (beta >= T(0.125)) {
+                xs.mode = 0;
+                x_pending = (double)alpha;
+                x_beta = (double)beta;
+            }
+        }
         for (int t = first; t < end; t += stride) {
             double acc[NPART] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
             if constexpr (SCH == 1)
             {
                 if constexpr (CD) {
-                    if (use_codes) pass_tile_coded<BS, NT, PER>(a, t, o, n, alpha, beta, lds0, dict, acc);
-                    else pass_tile40<T, BS, NT, PER>(a, t, o, n, alpha, beta, lds0, acc);
+                    if (use_codes) pass_tile_coded<BS, NT, PER>(a, t, o, n, alpha, beta, xs, lds0, dict, acc);
+                    else pass_tile40<T, BS, NT, PER>(a, t, o, n, alpha, beta, xs, lds0, acc);
                 } else {
-                    pass_tile40<T, BS, NT, PER>(a, t, o, n, alpha, beta, lds0, acc);
+                    pass_tile40<T, BS, NT, PER>(a, t, o, n, alpha, beta, xs, lds0, acc);
                 }
             }
             else
@@ -1706,6 +1752,8 @@ __device__ void run_problem(const KArgs<T>& a, int w, int G, bool xcd_map, unsig
         if (!grid_sync_reduce<BS, NPART>(S, w, G, b, sums(b), a.ntiles, a.timeout_ticks, red, &s_flag, v)) return;
         ++b;
         if (threadIdx.x == 0) {
+            sc.x_pending = x_pending;
+            sc.x_beta = x_beta;
             const double pq = v[0], rrd = v[1], rqd = v[2], qqd = v[3], rr0 = v[4], rq = v[5], qq = v[6];
             if (!(pq > 0.0) || !(pq - pq == 0.0) || !(rrd > 0.0)) {
                 sc.done = 1;
@@ -1730,6 +1778,7 @@ __device__ void run_problem(const KArgs<T>& a, int w, int G, bool xcd_map, unsig
                 S->pq = pq;
                 S->alpha = sc.alpha; S->beta = sc.beta; S->rr = sc.rr; S->iters = sc.iters;
                 S->done = sc.done; S->status = sc.status;
+                S->x_pending = x_pending; S->x_beta = x_beta;
             }
         }
         __syncthreads();
@@ -1740,9 +1789,15 @@ __device__ void run_problem(const KArgs<T>& a, int w, int G, bool xcd_map, unsig
     }
     // ---- last x update with the final alpha and direction (or x = 0); a
     // chunk that stops before convergence leaves the state to be resumed
+    const T* plast = (it & 1) ? a.p[1] : a.p[0];
+    const T* pbefore = (it & 1) ? a.p[0] : a.p[1];
+    const T pending = (T)sc.x_pending;   // of the direction before the last
     if (sc.zero || (sc.done && final_update && sc.status != PB_ERR_BREAKDOWN)) {
-        const T* plast = (it & 1) ? a.p[1] : a.p[0];
-        for (int t = first; t < end; t += stride) final_tile<T, BS>(a, t, (T)sc.alpha, plast, sc.zero != 0);
+        for (int t = first; t < end; t += stride)
+            final_tile<T, BS>(a, t, (T)sc.alpha, plast, pending, pbefore, sc.zero != 0);
+    } else if (sc.status == PB_ERR_BREAKDOWN && pending != T(0)) {
+        for (int t = first; t < end; t += stride)
+            final_tile<T, BS>(a, t, pending, pbefore, T(0), (const T*)nullptr, false);
     }
 }
 

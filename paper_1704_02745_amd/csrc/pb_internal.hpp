@@ -82,13 +82,14 @@ struct Op {
 struct alignas(256) SyncState {
     unsigned int arrive[8][64];   // arrivals of this launch, spread over 8 cache lines
     double alpha;                 // alpha of the last completed iteration
-    double alpha_prev;
+    double x_pending;             // step of a direction not yet added to x (0: none)
     double beta;
     double rho;                   // r.z
     double rr;                    // ||r||^2 (recurrence)
     double bb;                    // ||b||^2
     double pq;
-    double rq, qq, rqd, qqd;
+    double x_beta;                // the beta that the direction after it was formed with
+    double pad1[3];
     int iters;
     int done;                     // 1: stop iterating
     int status;                   // pb_status
