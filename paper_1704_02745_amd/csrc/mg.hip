@@ -1201,7 +1201,8 @@ pb_status mg_pcg_impl(const Layout& L0, double h, const double* ex, const double
     lv[0].op = s.op;
     lv[0].ex = (double*)ex; lv[0].ey = (double*)ey; lv[0].ez = (double*)ez; lv[0].k2 = (double*)k2;
     lv[0].xa = s.z;      // (lv[0].b, the V-cycle's input, is the outer residual; set per iteration)
-    for (size_t l = 1; l < lv.size(); ++l) {
+    const bool built = res && res->mg_built;
+    for (size_t l = 1; l < lv.size() && !built; ++l) {
         const MgLevel<T>& f = lv[l - 1];
         MgLevel<T>& c = lv[l];
         const int64_t tot = (int64_t)(c.L.nx + 1) * c.L.ny * c.L.nz + (int64_t)c.L.nx * (c.L.ny + 1) * c.L.nz +
@@ -1220,7 +1221,10 @@ pb_status mg_pcg_impl(const Layout& L0, double h, const double* ex, const double
     const bool flat = sizeof(T) == 8 || !march_fits(L0);
     if constexpr (sizeof(T) == 4) if (!flat) {
         rd0.ag = {s.op.cx, s.op.cy, s.op.cz, s.op.d};
-        if (coded_coefficients() && lv[0].codes) {
+        if (built) {
+            rd0.coded = res->mg_coded != 0;
+            rd0.cg = {lv[0].codes, res->mg_tab, nullptr};
+        } else if (coded_coefficients() && lv[0].codes) {
             bool fits = false;
             const float* tab = nullptr;
             const pb_status e = build_codes(s.op, L0.npad, lv[0].code_scratch, lv[0].codes, st, fits, &tab);
@@ -1228,16 +1232,23 @@ pb_status mg_pcg_impl(const Layout& L0, double h, const double* ex, const double
             rd0.coded = fits;
             rd0.cg = {lv[0].codes, tab, nullptr};
         }
+        if (res) {
+            res->mg_coded = rd0.coded ? 1 : 0;
+            res->mg_tab = rd0.cg.dict;
+        }
         // the pad slots, which k_mg_march does not write and the flat kernels read
         auto zero_pads = [&](T* a, const Layout& L) {
             if (L.sp > L.plane)
                 hipLaunchKernelGGL(k_mg_zero_pads<T>, dim3(mg_grid((L.sp - L.plane) * L.nz)), dim3(kBS), 0, st, a,
                                    L.plane, L.sp, (L.sp - L.plane) * L.nz);
         };
-        zero_pads(lv[0].xb, L0);
-        zero_pads(s.p1, L0);
-        for (size_t l = 1; l < lv.size(); ++l) zero_pads(lv[l].b, lv[l].L);
+        if (!built) {
+            zero_pads(lv[0].xb, L0);
+            zero_pads(s.p1, L0);
+            for (size_t l = 1; l < lv.size(); ++l) zero_pads(lv[l].b, lv[l].L);
+        }
     }
+    if (res) res->mg_built = 1;
 
     const int64_t npad = L0.npad;
     const Ranges R = ranges_for(npad);

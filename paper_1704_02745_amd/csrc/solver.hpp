@@ -117,6 +117,10 @@ struct SolveResult {
     int coded;               // fused form: 1 when the pass read coded coefficients
     const float* ctab;       // and the dictionary it used (device)
     int untimed;             // input: 1 = record no HIP events (kernel_seconds stays 0)
+    // multigrid: set by a solve whose hierarchy (and level 0's code words) a further
+    // one on the same operator and workspace can take over
+    int mg_built, mg_coded;
+    const float* mg_tab;
 };
 
 // jpcg.hip: one persistent cooperative launch running the whole iteration.
