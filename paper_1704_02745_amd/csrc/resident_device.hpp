@@ -82,11 +82,20 @@ static_assert(kMaxResidentGroups <= kSlotGroup * kSlotGroup, "two rounds of poll
 // 6.96 against 7.0 to 7.3 (129^3), 43 planes 15.1 against 15.6 (161^3). The kernels of
 // up to 6 planes, whose plans have fewer workgroups, go without the choice (0.09 us
 // a pass).
-__host__ __device__ constexpr int slot_groups(int nzb, int G) {
+//
+// The kernels over many problems always take two rounds (one for up to 16
+// workgroups): polling all slots needs eight more registers, which they have only
+// by spilling, and the spilled values' loads stood in the barrier's path (129^3
+// 9.1 us a pass against 7.0, 97^3 7.5 against 7.0, 161^3 16.4 against 16.1; 65^3 6.6
+// against 6.8).
+__host__ __device__ constexpr int slot_groups(int nzb, int G, bool many) {
+    if (many) return G > kSlotGroup ? (G + kSlotGroup - 1) / kSlotGroup : 0;
     return nzb > 6 && (nzb <= 14 || nzb == 24) && G > 128 ? (G + kSlotGroup - 1) / kSlotGroup : 0;
 }
 // Barrier words of a problem, both parities.
-__host__ __device__ constexpr int slot_words(int nzb, int G) { return 2 * (G + slot_groups(nzb, G)) * kSlotWords; }
+__host__ __device__ constexpr int slot_words(int nzb, int G, bool many) {
+    return 2 * (G + slot_groups(nzb, G, many)) * kSlotWords;
+}
 
 // The value, unknown to the optimizer: keeps what is derived from it (1/d,
 // offsets) from being hoisted out of the iteration into registers of its own.
@@ -225,8 +234,10 @@ __host__ __device__ constexpr size_t resident_lds_bytes(int bs, int nzb, int tx,
 // launch goes on with that pass, so the iterates are those of one launch, bit for
 // bit. The last pass stores them before its barrier, from inside the loop: with
 // r and q alive past it the compiler spilled 74 (compact: 170) registers.
-template <typename T, int BS, int NZ, bool PER, bool CP = false, bool KEEPS = false>
-__device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_raw) {
+// MANY: in a launch over many problems. A: RArgs<T>, as a kernel argument or in
+// constant memory.
+template <typename T, int BS, int NZ, bool PER, bool CP, bool MANY, bool KEEPS, typename A>
+__device__ void resident_problem(const A& a, int w, unsigned char* lds_raw) {
 #pragma clang fp contract(off)
     constexpr int ROWS = BS / 64 * 4;
     constexpr int E = (int)sizeof(T);
@@ -460,7 +471,7 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's face values have arrived
         __syncthreads();
         const unsigned tag = (unsigned)(b + 1);
-        GlobalWord* slots = (GlobalWord*)(uintptr_t)a.slots + (size_t)(b & 1) * (G + slot_groups(NZ, G)) * kSlotWords;
+        GlobalWord* slots = (GlobalWord*)(uintptr_t)a.slots + (size_t)(b & 1) * (G + slot_groups(NZ, G, MANY)) * kSlotWords;
         auto put = [&](int slot, double v) {   // lane n's sum n
             if (lane < 8) {
                 const unsigned long long u = (unsigned long long)__double_as_longlong(v);
@@ -471,7 +482,7 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
             }
         };
         double tot;
-        if (slot_groups(NZ, G) > 0) {
+        if (MANY || slot_groups(NZ, G, MANY) > 0) {
             if (wave == 0) {
                 // the sums of up to kSlotGroup slots: lane n polls sum n & 7 of slots n / 8 and
                 // n / 8 + 8, and gets the total of that sum
@@ -506,8 +517,9 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
                     return t;
                 };
                 put(w, lds_rows_sum8(red, ROWS));
-                if (w % kSlotGroup == 0) put(G + w / kSlotGroup, get(w, min(kSlotGroup, G - w)));
-                const double t = get(G, slot_groups(NZ, G));
+                const int ng = slot_groups(NZ, G, MANY);
+                if (ng > 0 && w % kSlotGroup == 0) put(G + w / kSlotGroup, get(w, min(kSlotGroup, G - w)));
+                const double t = ng > 0 ? get(G, ng) : get(0, G);
                 if (lane < 8) red2[lane] = t;
             }
             __syncthreads();
@@ -810,7 +822,7 @@ __device__ void resident_problem(const RArgs<T>& a, int w, unsigned char* lds_ra
 template <typename T, int BS, int NZ, bool PER, bool CP = false>
 __global__ __launch_bounds__(BS) void k_jpcg_resident(RArgs<T> a) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    resident_problem<T, BS, NZ, PER, CP>(a, blockIdx.x, lds_raw);
+    resident_problem<T, BS, NZ, PER, CP, false, false>(a, blockIdx.x, lds_raw);
 }
 
 constexpr int kCompactFrom = 24;   // planes per brick from which a kernel is the compact form's
@@ -820,6 +832,9 @@ constexpr int kCompactFrom = 24;   // planes per brick from which a kernel is th
 // forms spilled, and gave wrong potentials in the last bricks of one of them.
 template <typename T>
 constexpr int batch_planes(bool compact) { return sizeof(T) == 8 ? 8 : (compact ? 43 : 19); }
+
+template <typename T>
+using ConstArgs = __attribute__((address_space(4))) RArgs<T>;
 
 // Many problems in one launch: workgroup g runs the jobs [off[g], off[g + 1]) of
 // its list one after the other, job (problem, its workgroup number there). Jobs
@@ -833,18 +848,13 @@ __global__ __launch_bounds__(512) void k_resident_batch(const RArgs<T>* __restri
     const int end = off[blockIdx.x + 1];
     for (int n = off[blockIdx.x]; n < end; ++n) {
         const int2 job = jobs[n];
-        // the arguments, word by word known uniform: the compiler otherwise
-        // takes the buffer descriptors made of them for divergent
-        union U {
-            RArgs<T> a;
-            int w[sizeof(RArgs<T>) / 4];
-            __device__ U() {}
-        } u;
-        const int* src = reinterpret_cast<const int*>(probs + __builtin_amdgcn_readfirstlane(job.x));
-#pragma unroll
-        for (int i = 0; i < (int)(sizeof(RArgs<T>) / 4); ++i) u.w[i] = __builtin_amdgcn_readfirstlane(src[i]);
-        const RArgs<T> a = u.a;
-        resident_problem<T, 512, batch_planes<T>(CP), false, CP, KEEPS>(a, __builtin_amdgcn_readfirstlane(job.y), lds_raw);
+        // the arguments through the constant address space: known uniform, and read
+        // again by scalar loads where a register is short (as copies in registers
+        // they made the server's kernels spill 28 and 125 vector registers, 16 and 83
+        // like this)
+        const ConstArgs<T>* a = (const ConstArgs<T>*)(uintptr_t)(probs + __builtin_amdgcn_readfirstlane(job.x));
+        resident_problem<T, 512, batch_planes<T>(CP), false, CP, true, KEEPS>(*a, __builtin_amdgcn_readfirstlane(job.y),
+                                                                        lds_raw);
         __syncthreads();
     }
 }

@@ -73,7 +73,7 @@ const void* batch_kernel(bool compact) {
 // polls, or two rounds of polling), the planes of a thread (0.15 each with 512
 // threads), the halo nodes, and the strided x-faces.
 double resident_pass_us(int bs, int nzb, int halo, int grid, bool split_x, bool compact) {
-    const double barrier = slot_groups(nzb, grid) > 0 ? 3.8 : 2.4 + 0.0107 * grid;
+    const double barrier = slot_groups(nzb, grid, false) > 0 ? 3.8 : 2.4 + 0.0107 * grid;
     return barrier + (compact ? 0.19 : 0.149) * nzb * bs / 512 + 0.1 * halo / bs + (split_x ? 0.2 : 0.0);
 }
 
@@ -241,7 +241,7 @@ pb_status resident_solve(const Layout& L, const SolveBufs<T>& s, SyncState* sync
         a.r0 = r0;
     }
     if (launch_clear2((int*)sync, (int64_t)(sizeof(SyncState) / sizeof(int)), (int*)partials,
-                      (int64_t)2 * slot_words(p.nz, p.grid), st) != PB_OK)
+                      (int64_t)2 * slot_words(p.nz, p.grid, false), st) != PB_OK)
         return PB_ERR_HIP;
     hipEvent_t ev[2] = {nullptr, nullptr};
     const bool timed = res && !res->untimed;
@@ -309,7 +309,7 @@ ResBatchPlan resident_batch_plan(const Layout& L) {
     b.groups = std::min(res_device().cus, kMaxResidentGroups);
     b.us = p.us;
     b.lds = p.lds;
-    b.slot_bytes = (size_t)slot_words(p.nz, p.grid) * sizeof(unsigned long long);
+    b.slot_bytes = (size_t)slot_words(p.nz, p.grid, true) * sizeof(unsigned long long);
     return b;
 }
 template <typename T>
