@@ -446,9 +446,10 @@ void pb_batch_graph_destroy(pb_batch_graph* graph);
  * Continuous-batching server. Requests are queued by pb_server_submit; each
  * pb_server_step admits queued requests in arrival order while slots and the
  * caller's HBM arena allow (the arena size is the memory budget), advances
- * every active request by up to `chunk` CG iterations in ONE persistent
- * launch (the requests' work overlaps on the device), and retires requests
- * that converged or failed, freeing their memory for the next admissions.
+ * every active request by `chunk` CG iterations, or a multiple of it (at most
+ * 16) where its iterations are short, in one persistent launch per kernel form
+ * (the requests' work overlaps on the device), and retires requests that
+ * converged or failed, freeing their memory for the next admissions.
  * An unfinished request's CG state stays in the arena and the next step
  * resumes it exactly: a request's result does not depend on chunking or on
  * the other requests in flight. precision PB_F32 runs FP32 Jacobi-PCG to the

@@ -588,8 +588,8 @@ class BatchGraph:
 class Server:
     """Continuous-batching solve server over a device arena of `arena_bytes`
     (the HBM budget). submit() queues a request; step() admits, advances every
-    active request by `chunk` iterations in one launch and returns the
-    requests that finished as [(id, info)]."""
+    active request by `chunk` iterations (a multiple of it where they are
+    short) and returns the requests that finished as [(id, info)]."""
 
     def __init__(self, arena_bytes: int, max_slots: int = 256, device="cuda", keep_outputs=True):
         self.keep_outputs = keep_outputs
