@@ -322,7 +322,8 @@ pb_status pb_get_tuning(int32_t nx, int32_t ny, int32_t nz, int32_t precision, p
  * FP32 coefficients themselves, so potentials, iteration counts and
  * residuals are bitwise those of the uncoded pass. Otherwise (more values,
  * or a grid of fewer than 8,450 padded positions) the uncoded pass runs. A
- * pb_solve_batch or server launch is coded only when all its problems are;
+ * pb_solve_batch or server launch is coded only when all its problems are
+ * (problems that run in the compact resident form each decide for themselves);
  * a batch graph rebuilds every dictionary at each replay and its kernel
  * decides per problem on the device, so coefficients that change between
  * replays are handled. pb_info.coded_launches and

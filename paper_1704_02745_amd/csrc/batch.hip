@@ -67,12 +67,14 @@ struct Plan {
     size_t bytes = 0;
     size_t lds = 0;
     char* table = nullptr;          // device: KArgs records
-    int* first = nullptr;           // device: workgroup offsets (nprob + 1)
+    int* first = nullptr;           // device: workgroup offsets of the streaming launches
     SyncState* sync = nullptr;      // device: one per problem
     ProbRec* rec = nullptr;         // device: one per problem
     int* fit = nullptr;             // device: one per problem (coded coefficients fit the dictionary)
     // problems whose state fits the device run in the resident form, full or
-    // compact, the others in the streaming form, one launch each (choose_forms)
+    // compact, the others in the streaming form, one launch each (choose_forms);
+    // `fall`: compact problems of a recorded batch, whose operator may turn out
+    // not to fit its dictionary, in a streaming launch of their own
     struct Form {
         std::vector<int> of;        // indices of its problems
         size_t lds = 0;
@@ -81,7 +83,10 @@ struct Plan {
         char* jobs = nullptr;       // device: (index in of, workgroup) pairs
     };
     Form res[2];                    // full, compact
-    std::vector<int> str;
+    std::vector<int> str, fall;
+    size_t fall_lds = 0;
+    int fall_grid = 0;              // workgroups of that launch
+    std::vector<int> words;         // per problem: code words given: 0 no, 1 yes, 2 as its fit flag says
     std::vector<ResBatchPlan> rp;   // per problem (grid 0: streaming)
     std::vector<char*> slots;       // device: barrier words per problem
     char* all_slots = nullptr;      // and the range that holds them all
@@ -102,29 +107,34 @@ bool problem_ok(const pb_problem& p) {
            p.eps_z && p.kappa2 && p.rhs && p.x;
 }
 
-// Which problems run in which form. coded 0: no code words, problems that only
-// the compact resident form takes run in the streaming one; 1: every problem
-// has code words; 2: its fit flag says so on the device, so those problems are
-// in both launches and one of the two skips them.
+// Which problems run in which form, from each problem's shape and code words
+// alone, so that its arithmetic does not depend on the others. A problem that
+// only the compact form takes runs in it where it has code words, else in the
+// streaming form. Where the device decides (words 2) it is in both launches, one
+// of which skips it. The second is apart from the streaming launch: workgroups
+// shared out to a problem that is then skipped would be lost to the others.
 template <typename T>
-void choose_forms(Plan<T>& P, int coded) {
+void choose_forms(Plan<T>& P) {
     for (auto& f : P.res) {
         f.of.clear();
         f.lds = 0;
     }
     P.str.clear();
-    P.lds = 0;
+    P.fall.clear();
+    P.lds = P.fall_lds = 0;
     for (int i = 0; i < P.nprob; ++i) {
         const ResBatchPlan& rp = P.rp[i];
-        const bool res = rp.grid > 0 && (!rp.compact || coded);
-        if (res) {
-            auto& f = P.res[rp.compact ? 1 : 0];
-            f.of.push_back(i);
-            f.lds = std::max(f.lds, rp.lds);
-        }
-        if (!res || (rp.compact && coded == 2)) {
+        if (rp.grid <= 0 || (rp.compact && !P.words[i])) {
             P.str.push_back(i);
             P.lds = std::max(P.lds, P.t[i].lds);
+            continue;
+        }
+        auto& f = P.res[rp.compact ? 1 : 0];
+        f.of.push_back(i);
+        f.lds = std::max(f.lds, rp.lds);
+        if (rp.compact && P.words[i] == 2) {
+            P.fall.push_back(i);
+            P.fall_lds = std::max(P.fall_lds, P.t[i].lds);
         }
     }
 }
@@ -141,7 +151,7 @@ bool carve_batch(void* base, int nprob, const pb_problem* probs, Plan<T>& P, int
     };
     P.nprob = nprob;
     P.table = (char*)take(batch_kargs_bytes<T>() * (size_t)nprob);
-    P.first = (int*)take(sizeof(int) * (size_t)(nprob + 1));
+    P.first = (int*)take(sizeof(int) * (size_t)(nprob + 2));
     P.sync = (SyncState*)take(sizeof(SyncState) * (size_t)nprob);
     P.rec = (ProbRec*)take(sizeof(ProbRec) * (size_t)nprob);
     P.fit = (int*)take(sizeof(int) * (size_t)nprob);
@@ -203,7 +213,8 @@ bool carve_batch(void* base, int nprob, const pb_problem* probs, Plan<T>& P, int
             P.res[c].jobs = (char*)take(2 * sizeof(int) * njobs[c]);
         }
     P.bytes = off;
-    choose_forms(P, 0);
+    P.words.assign(nprob, 0);
+    choose_forms(P);
     return true;
 }
 
@@ -277,12 +288,17 @@ pb_status enqueue_finish(const Plan<T>& P, const pb_problem* probs, hipStream_t 
 template <typename T>
 pb_status launch_solves(const Plan<T>& P, int grid, hipStream_t st, bool cooperative, int coded);
 
+// Dynamic LDS of the streaming launch.
+template <typename T>
+size_t streaming_lds(const Plan<T>& P, int coded) {
+    return P.lds + (coded ? kCodedLdsBytes : 0);
+}
+
 // The whole batch on `st`: clear flags and barrier state, prepare, solve,
 // finish; nothing is read back to the host, so it can be recorded in a graph.
-// coded == 2 (FP32): every problem's dictionary, fit flag and code words are
-// rebuilt on the device before the launch, whose kernel reads each problem's
-// fit flag (the arguments table must carry the code words, dictionaries and
-// flags).
+// Where P.words says 2 (FP32), the problem's dictionary, fit flag and code words
+// are rebuilt on the device before the launches, whose kernels read the flag (the
+// argument tables must carry the code words, dictionaries and flags).
 template <typename T>
 pb_status enqueue_batch(const Plan<T>& P, const pb_problem* probs, int grid, bool cooperative, hipStream_t st,
                         int coded = 0) {
@@ -293,8 +309,8 @@ pb_status enqueue_batch(const Plan<T>& P, const pb_problem* probs, int grid, boo
     e = enqueue_prepare<T>(P, probs, st);
     if (e != PB_OK) return e;
     if constexpr (sizeof(T) == sizeof(float)) {
-        if (coded == 2)
-            for (int i = 0; i < P.nprob; ++i) {
+        for (int i = 0; i < P.nprob; ++i)
+            if (P.words[i] == 2) {
                 e = enqueue_dictionary(P.s[i].op, P.L[i].npad, (void*)P.s[i].q, P.fit + i, st);
                 if (e != PB_OK) return e;
                 e = enqueue_encode(P.s[i].op, P.L[i].npad, P.s[i].q, (uint32_t*)P.s[i].q2, st, P.fit + i);
@@ -307,21 +323,25 @@ pb_status enqueue_batch(const Plan<T>& P, const pb_problem* probs, int grid, boo
 }
 
 // Write the per-problem kernel arguments (with each problem's code words and
-// dictionary when `coded`, and its fit flag when coded == 2).
+// dictionary as P.words says). The streaming launches' records follow one
+// another in one table.
 template <typename T>
-pb_status fill_table(const Plan<T>& P, const pb_problem* probs, int coded, hipStream_t st) {
+pb_status fill_table(const Plan<T>& P, const pb_problem* probs, hipStream_t st) {
     auto args = [&](int i, auto&& fill) {
         const int maxiter = probs[i].maxiter > 0 ? probs[i].maxiter
                                                  : 10 * std::max(probs[i].nx, std::max(probs[i].ny, probs[i].nz));
-        fill(maxiter, coded ? (const float*)P.s[i].q2 : nullptr, coded ? dictionary_table(P.s[i].q) : nullptr,
-             coded == 2 ? (const int*)(P.fit + i) : nullptr);
+        const int words = P.words[i];
+        fill(maxiter, words ? (const float*)P.s[i].q2 : nullptr, words ? dictionary_table(P.s[i].q) : nullptr,
+             words == 2 ? (const int*)(P.fit + i) : nullptr);
     };
-    std::vector<char> host(batch_kargs_bytes<T>() * P.str.size()), rhost[2];
-    for (size_t k = 0; k < P.str.size(); ++k) {
-        const int i = P.str[k];
+    const size_t nstr = P.str.size();
+    std::vector<char> host(batch_kargs_bytes<T>() * (nstr + P.fall.size())), rhost[2];
+    for (size_t k = 0; k < nstr + P.fall.size(); ++k) {
+        const bool fall = k >= nstr;
+        const int i = fall ? P.fall[k - nstr] : P.str[k];
         args(i, [&](int maxiter, const float* cw, const float* tab, const int* fit) {
             batch_fill_kargs<T>(host.data() + batch_kargs_bytes<T>() * k, P.L[i], P.s[i], &P.sync[i], P.partials[i],
-                                P.t[i], probs[i].tol, maxiter, 0, 0, cw, tab, fit, P.rp[i].compact && coded == 2);
+                                P.t[i], probs[i].tol, maxiter, 0, 0, cw, tab, fit, fall);
         });
     }
     for (int c = 0; c < 2; ++c) {
@@ -342,8 +362,9 @@ pb_status fill_table(const Plan<T>& P, const pb_problem* probs, int coded, hipSt
     return PB_OK;
 }
 
-// The solves: a launch of each resident form, then a streaming one, each over
-// the problems of its form. grid: workgroups of the streaming launch.
+// The solves: a launch of each resident form, then the streaming ones, each over
+// the problems of its form. grid, coded: workgroups and kernel of the streaming
+// launch (the compact problems' fallback runs uncoded: it has no dictionary).
 template <typename T>
 pb_status launch_solves(const Plan<T>& P, int grid, hipStream_t st, bool cooperative, int coded) {
     pb_status e = PB_OK;
@@ -357,35 +378,47 @@ pb_status launch_solves(const Plan<T>& P, int grid, hipStream_t st, bool coopera
         e = resident_batch_launch<T>(f.table, f.job_off, f.jobs, P.groups, f.lds, c == 1, st, cooperative);
         if (e != PB_OK) return e;
     }
-    if (P.str.empty()) return PB_OK;
-    return batch_launch<T>(P.table, P.first, (int)P.str.size(), grid, coded ? P.lds + kCodedLdsBytes : P.lds, st,
-                           cooperative, coded);
+    const int nstr = (int)P.str.size(), nfall = (int)P.fall.size();
+    if (nstr > 0) e = batch_launch<T>(P.table, P.first, nstr, grid, streaming_lds(P, coded), st, cooperative, coded);
+    if (e == PB_OK && nfall > 0)
+        e = batch_launch<T>(P.table + batch_kargs_bytes<T>() * nstr, P.first + nstr + 1, nfall, P.fall_grid, P.fall_lds,
+                            st, cooperative, 0);
+    return e;
 }
 
-// Settle the forms for `coded` (choose_forms) and upload the per-problem kernel
-// arguments, the workgroup offsets and the job lists.
+// Settle the forms (choose_forms, from P.words) and upload the per-problem kernel
+// arguments, the workgroup offsets and the job lists. coded: the streaming
+// launch's kernel; grid: its workgroups.
 template <typename T>
 pb_status upload_table(Plan<T>& P, const pb_problem* probs, int& grid, int coded, hipStream_t st) {
     grid = 0;
-    choose_forms(P, coded);
-    std::vector<int> first;
+    choose_forms(P);
     // a batch holds at most as many problems as the streaming form has
     // co-resident workgroups, whatever form its problems run in
     if (const int most = batch_capacity<T>(P.str_lds); most < P.nprob) {
         set_error("batch: %d problems but only %d co-resident workgroups; split the batch", P.nprob, most);
         return PB_ERR_ARG;
     }
-    if (!P.str.empty()) {
-        const int cap = batch_capacity<T>(P.lds, coded);
+    auto share = [&](const std::vector<int>& of, int cap) {
         std::vector<Layout> L;
         std::vector<Tiling> t;
-        for (int i : P.str) {
+        for (int i : of) {
             L.push_back(P.L[i]);
             t.push_back(P.t[i]);
         }
-        first = share_workgroups(L, t, cap);
+        return share_workgroups(L, t, cap);
+    };
+    std::vector<int> first, ffirst;
+    if (!P.str.empty()) {
+        first = share(P.str, batch_capacity<T>(streaming_lds(P, coded), coded));
         grid = first.back();
         PB_HIP(hipMemcpyAsync(P.first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice, st));
+    }
+    if (!P.fall.empty()) {
+        ffirst = share(P.fall, batch_capacity<T>(P.fall_lds));
+        P.fall_grid = ffirst.back();
+        PB_HIP(hipMemcpyAsync(P.first + P.str.size() + 1, ffirst.data(), sizeof(int) * ffirst.size(),
+                              hipMemcpyHostToDevice, st));
     }
     std::vector<int> off[2], jobs[2];
     for (int c = 0; c < 2; ++c) {
@@ -401,7 +434,7 @@ pb_status upload_table(Plan<T>& P, const pb_problem* probs, int& grid, int coded
         PB_HIP(hipMemcpyAsync(f.job_off, off[c].data(), sizeof(int) * off[c].size(), hipMemcpyHostToDevice, st));
         PB_HIP(hipMemcpyAsync(f.jobs, jobs[c].data(), sizeof(int) * jobs[c].size(), hipMemcpyHostToDevice, st));
     }
-    return fill_table<T>(P, probs, coded, st);
+    return fill_table<T>(P, probs, st);
 }
 
 // Whether every problem of the batch can have code words: the arrays that hold
@@ -414,45 +447,52 @@ bool can_code(const Plan<T>& P, int coded) {
     return batch_capacity<T>(P.str_lds + kCodedLdsBytes, coded) >= P.nprob;
 }
 
-// The direct (not graph-recorded) batch: as enqueue_batch, with coded
-// coefficients when every problem's FP32 operator fits its dictionary and
-// the coded kernel keeps the grid co-resident. The fit flags are read back
-// to the host once, after the preparation; the code words go to each
-// problem's q2 and the dictionary to its q (the batch's pass form uses
-// neither).
+// Whether a problem runs in the compact form if its operator fits a dictionary.
 template <typename T>
-pb_status enqueue_batch_direct(Plan<T>& P, const pb_problem* probs, hipStream_t st, bool& coded) {
-    coded = false;
+bool wants_words(const Plan<T>& P, int i) {
+    return sizeof(T) == sizeof(float) && P.rp[i].grid > 0 && P.rp[i].compact && coded_coefficients() &&
+           coded_layout_ok(P.L[i]);
+}
+
+// The direct (not graph-recorded) batch: as enqueue_batch, with the fit flags
+// read back to the host once, after the preparation. The compact problems whose
+// operator fits get code words; every problem does where all fit and the coded
+// kernel keeps the grid co-resident (coded). The code words go to a problem's q2
+// and the dictionary to its q (the batch's pass form uses neither).
+template <typename T>
+pb_status enqueue_batch_direct(Plan<T>& P, const pb_problem* probs, hipStream_t st) {
     pb_status e = launch_fill<int>((int*)P.rec, (int64_t)(sizeof(ProbRec) / sizeof(int)) * P.nprob, 0, st);
     if (e != PB_OK) return e;
     e = launch_fill<int>((int*)P.sync, (int64_t)(sizeof(SyncState) / sizeof(int)) * P.nprob, 0, st);
     if (e != PB_OK) return e;
     e = enqueue_prepare<T>(P, probs, st);
     if (e != PB_OK) return e;
+    bool coded = can_code(P, 1);
     if constexpr (sizeof(T) == sizeof(float)) {
-        bool can = can_code(P, 1);
-        if (can) {
-            for (int i = 0; i < P.nprob; ++i) {
-                e = enqueue_dictionary(P.s[i].op, P.L[i].npad, (void*)P.s[i].q, P.fit + i, st);
-                if (e != PB_OK) return e;
-            }
-            std::vector<int> fit(P.nprob, 0);
+        std::vector<int> fit(P.nprob, 0);
+        bool any = false;
+        for (int i = 0; i < P.nprob; ++i) {
+            if (!coded && !wants_words(P, i)) continue;
+            any = true;
+            e = enqueue_dictionary(P.s[i].op, P.L[i].npad, (void*)P.s[i].q, P.fit + i, st);
+            if (e != PB_OK) return e;
+        }
+        if (any) {
             PB_HIP(hipMemcpyAsync(fit.data(), P.fit, sizeof(int) * P.nprob, hipMemcpyDeviceToHost, st));
             PB_HIP(hipStreamSynchronize(st));
-            for (int i = 0; i < P.nprob; ++i) can = can && fit[i] == 1;
         }
-        if (can) {
-            for (int i = 0; i < P.nprob; ++i) {
-                e = enqueue_encode(P.s[i].op, P.L[i].npad, P.s[i].q, (uint32_t*)P.s[i].q2, st);
-                if (e != PB_OK) return e;
-            }
-            coded = true;
+        for (int i = 0; i < P.nprob; ++i) coded = coded && fit[i] == 1;
+        for (int i = 0; i < P.nprob; ++i) {
+            P.words[i] = coded || (wants_words(P, i) && fit[i] == 1) ? 1 : 0;
+            if (!P.words[i]) continue;
+            e = enqueue_encode(P.s[i].op, P.L[i].npad, P.s[i].q, (uint32_t*)P.s[i].q2, st);
+            if (e != PB_OK) return e;
         }
     }
     int grid = 0;
     e = upload_table<T>(P, probs, grid, coded ? 1 : 0, st);
     if (e != PB_OK) return e;
-    e = launch_solves<T>(P, grid, st, true, coded);
+    e = launch_solves<T>(P, grid, st, true, coded ? 1 : 0);
     if (e != PB_OK) return e;
     return enqueue_finish<T>(P, probs, st);
 }
@@ -501,8 +541,7 @@ pb_status solve_batch_impl(int nprob, const pb_problem* probs, void* ws, size_t 
     PB_HIP(hipEventCreate(&ev[0]));
     PB_HIP(hipEventCreate(&ev[1]));
     PB_HIP(hipEventRecord(ev[0], st));
-    bool coded = false;
-    pb_status e = enqueue_batch_direct<T>(P, probs, st, coded);
+    pb_status e = enqueue_batch_direct<T>(P, probs, st);
     if (e != PB_OK) {
         (void)hipEventDestroy(ev[0]);
         (void)hipEventDestroy(ev[1]);
@@ -519,7 +558,7 @@ pb_status solve_batch_impl(int nprob, const pb_problem* probs, void* ws, size_t 
     if (infos)
         for (int i = 0; i < nprob; ++i) {
             infos[i].kernel_seconds = 1e-3 * ms;
-            infos[i].coded_launches = coded ? 1 : 0;
+            infos[i].coded_launches = P.words[i] ? 1 : 0;
         }
     return st_all;
 }
@@ -567,7 +606,8 @@ pb_status batch_autotune_impl(int nprob, const pb_problem* probs, int iters, voi
                     if (e == PB_OK) e = enqueue_encode(P.s[i].op, P.L[i].npad, P.s[i].q, (uint32_t*)P.s[i].q2, st,
                                                        P.fit + i);
                 }
-                if (e != PB_OK || (e = fill_table<T>(P, trial.data(), 2, st)) != PB_OK) break;
+                P.words.assign(nprob, 2);
+                if (e != PB_OK || (e = fill_table<T>(P, trial.data(), st)) != PB_OK) break;
                 coded = 2;
             }
         }
@@ -610,7 +650,7 @@ struct BatchGraph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool cooperative = true;
-    int coded = 0;   // 2: the recorded batch builds dictionaries and its kernel reads each problem's fit flag
+    int coded = 0;   // 2: every problem's dictionary is built and the streaming kernel reads its fit flag
     hipEvent_t ev[2] = {nullptr, nullptr};
 };
 
@@ -695,6 +735,7 @@ pb_status graph_build(pb_batch_graph* G, Plan<T>& P, void* ws, size_t wsb, hipSt
     // coded coefficients, decided on the device at every replay (the
     // coefficients may change between replays)
     G->coded = can_code(P, 2) ? 2 : 0;
+    for (int i = 0; i < P.nprob; ++i) P.words[i] = G->coded || wants_words(P, i) ? 2 : 0;
     int grid = 0;
     pb_status e = upload_table<T>(P, G->probs.data(), grid, G->coded, st);
     if (e != PB_OK) return e;
@@ -775,14 +816,14 @@ extern "C" pb_status pb_batch_graph_results(pb_batch_graph* G, void* stream, pb_
     const pb_status s = G->precision == PB_F64 ? collect<double>(*G->p64, st, infos, 1e-3 * ms)
                                                : collect<float>(*G->p32, st, infos, 1e-3 * ms);
     std::vector<int> fit(G->nprob, 0);
-    if (infos && G->coded == 2) {
+    if (infos && G->p32) {
         PB_HIP(hipMemcpyAsync(fit.data(), G->p32->fit, sizeof(int) * G->nprob, hipMemcpyDeviceToHost, st));
         PB_HIP(hipStreamSynchronize(st));
     }
     if (infos)
         for (int i = 0; i < G->nprob; ++i) {
             infos[i].kernel_seconds = 1e-3 * ms;
-            infos[i].coded_launches = fit[i] == 1 ? 1 : 0;
+            infos[i].coded_launches = G->p32 && G->p32->words[i] && fit[i] == 1 ? 1 : 0;
         }
     return s;
 }
