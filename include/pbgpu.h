@@ -333,8 +333,11 @@ pb_status pb_get_tuning(int32_t nx, int32_t ny, int32_t nz, int32_t precision, p
  * graph replay).
  *
  * pb_set_coded_coefficients(0) turns the coded pass off for the process;
- * 1 (the default) turns it back on. pb_get_coded_coefficients returns the
- * setting. Not synchronised with solves running on other threads.
+ * 1 (the default) turns it back on. Solves in the compact resident form (FP32
+ * grids of about 134 to 171 nodes an edge) hold their operator as code words
+ * under either setting, and count as coded, so that results do not depend on
+ * it. pb_get_coded_coefficients returns the setting. Not synchronised with
+ * solves running on other threads.
  */
 void pb_set_coded_coefficients(int32_t on);
 int32_t pb_get_coded_coefficients(void);

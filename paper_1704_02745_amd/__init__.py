@@ -410,7 +410,9 @@ def set_tuning(nx, ny, nz, precision, block, groups, zchunk, grid, scheme=0, str
 
 def set_coded_coefficients(on: bool) -> None:
     """Process-wide switch of the coded-coefficient 40-byte FP32 pass (on by
-    default; used when the operator holds at most 256 distinct FP32 values)."""
+    default; used when the operator holds at most 256 distinct FP32 values).
+    No result depends on it; the compact resident form reads code words under
+    either setting."""
     lib.pb_set_coded_coefficients(1 if on else 0)
 
 

@@ -447,11 +447,11 @@ bool can_code(const Plan<T>& P, int coded) {
     return batch_capacity<T>(P.str_lds + kCodedLdsBytes, coded) >= P.nprob;
 }
 
-// Whether a problem runs in the compact form if its operator fits a dictionary.
+// Whether a problem runs in the compact form if its operator fits a dictionary
+// (whatever pb_set_coded_coefficients says, as in a solve of its own).
 template <typename T>
 bool wants_words(const Plan<T>& P, int i) {
-    return sizeof(T) == sizeof(float) && P.rp[i].grid > 0 && P.rp[i].compact && coded_coefficients() &&
-           coded_layout_ok(P.L[i]);
+    return sizeof(T) == sizeof(float) && P.rp[i].grid > 0 && P.rp[i].compact && coded_layout_ok(P.L[i]);
 }
 
 // The direct (not graph-recorded) batch: as enqueue_batch, with the fit flags

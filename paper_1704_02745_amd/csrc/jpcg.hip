@@ -2233,7 +2233,9 @@ pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, do
         pb_status e = resident_jpcg<T>(L, s, sync, partials, tol, maxiter, st, res, periodic, nullptr, nullptr, ran);
         if (e != PB_OK || ran) return e;
         if constexpr (sizeof(T) == 4) {
-            if (coded_coefficients() && s.q && s.q2 && coded_layout_ok(L) && resident_fits<T>(L, periodic, true)) {
+            // whatever pb_set_coded_coefficients says, which is about passes that can read
+            // either: the sums of this form come in another order than a pass's
+            if (s.q && s.q2 && coded_layout_ok(L) && resident_fits<T>(L, periodic, true)) {
                 bool fits = s.codes_valid != 0;
                 const float* tab = s.ctab;
                 if (!fits) e = build_codes(s.op, L.npad, (void*)s.q, (uint32_t*)s.q2, st, fits, &tab);

@@ -534,8 +534,9 @@ extern "C" pb_status pb_server_step(pb_server* S, int32_t chunk, void* stream, i
             e = enqueue_outer_residual(s, ad);
             if (e != PB_OK) return e;
         }
-        // coded coefficients: the dictionary now, the code words once the fit flag is read back
-        if (coded_coefficients() && coded_layout_ok(s.L)) {
+        // coded coefficients: the dictionary now, the code words once the fit flag is read
+        // back (the compact form's whatever pb_set_coded_coefficients says)
+        if ((coded_coefficients() || (s.rp.grid > 0 && s.rp.compact)) && coded_layout_ok(s.L)) {
             e = enqueue_dictionary(s.s.op, s.L.npad, (void*)s.s.q, &s.rec->fit, ad);
             if (e != PB_OK) return e;
         }

@@ -199,7 +199,8 @@ const float* dictionary_table(const void* scratch);
 // Extra dynamic LDS of the coded kernels: none, since the dictionary sits in
 // static LDS, which the kernels' own group segment size already counts.
 constexpr size_t kCodedLdsBytes = 0;
-// Process-wide switch (default on): 0 keeps every fused FP32 solve uncoded.
+// Process-wide switch (default on): 0 keeps every FP32 pass uncoded (the compact
+// resident form, which has no other operator, reads code words all the same).
 void set_coded_coefficients(int on);
 int coded_coefficients();
 // Process-wide pass form of periodic fused solves: -1 the model's choice, 0
