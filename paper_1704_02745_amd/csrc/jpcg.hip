@@ -2228,6 +2228,7 @@ unsigned copy_grid(int64_t n) { return (unsigned)std::min<int64_t>((n + 255) / 2
 template <typename T>
 pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, double* partials, double tol,
                      int maxiter, hipStream_t st, SolveResult* res, const Tiling* force, int periodic) {
+    bool unfit = false;   // the operator is known not to fit a dictionary
     if (force ? force->resident != 0 : !streaming_asked<T>(L, periodic)) {
         bool ran = false;
         pb_status e = resident_jpcg<T>(L, s, sync, partials, tol, maxiter, st, res, periodic, nullptr, nullptr, ran);
@@ -2239,6 +2240,7 @@ pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, do
                 bool fits = s.codes_valid != 0;
                 const float* tab = s.ctab;
                 if (!fits) e = build_codes(s.op, L.npad, (void*)s.q, (uint32_t*)s.q2, st, fits, &tab);
+                unfit = !fits;
                 if (e == PB_OK && fits)
                     e = resident_jpcg<T>(L, s, sync, partials, tol, maxiter, st, res, periodic,
                                          (const uint32_t*)s.q2, tab, ran);
@@ -2301,7 +2303,7 @@ pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, do
                 bool fits = s.codes_valid != 0;
                 const float* tab = s.ctab;
                 uint32_t* words = gl ? s.gcodes : (uint32_t*)s.q2;
-                if (!fits) {
+                if (!fits && !unfit) {
                     const pb_status e = gl ? build_codes(s.gop, G.npad, (void*)s.q, words, st, fits, &tab)
                                            : build_codes(s.op, L.npad, (void*)s.q, words, st, fits, &tab);
                     if (e != PB_OK) return e;

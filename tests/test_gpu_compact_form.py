@@ -1,5 +1,7 @@
 """The compact resident form (FP32 grids of about 134 to 171 nodes an edge): its results do not depend
-on pb_set_coded_coefficients, bit for bit, in a solve, a batch, a recorded batch and the server."""
+on pb_set_coded_coefficients, bit for bit, in a solve, a batch, a recorded batch and the server; and an
+operator that does not fit a dictionary is put to the dictionary once per solve."""
+import numpy as np
 import pytest
 import torch
 
@@ -65,3 +67,21 @@ def test_independent_of_the_coded_setting(pb, way, boundary):
         pb.set_coded_coefficients(True)
     assert i1["status"] == i0["status"] == pb.PB_OK
     assert torch.equal(x1, x0) and i1["iters"] == i0["iters"]
+
+
+def test_unfit_operator_meets_the_dictionary_once(pb):
+    s = molecule_system(pb)
+    rng = np.random.default_rng(3)
+    for a in (s.eps_x, s.eps_y, s.eps_z):
+        a.copy_(torch.as_tensor(rng.uniform(1, 80, tuple(a.shape)), device=DEV))
+    torch.cuda.synchronize()
+    act = torch.profiler.ProfilerActivity
+    with torch.profiler.profile(activities=[act.CPU, act.CUDA]) as prof:
+        x, info = pb.solve(s, tol=1e-5, precision="f32")
+        torch.cuda.synchronize()
+    names = [e.name for e in prof.events()]
+    solves = [n for n in names if "jpcg" in n]
+    if not solves:
+        pytest.skip("the profiler recorded no kernels of the library")
+    assert info["coded_launches"] == 0 and len(solves) == 1, solves
+    assert sum("k_dict_insert" in n for n in names) == 1
