@@ -365,7 +365,7 @@ pb_status solve_impl(int32_t nx, int32_t ny, int32_t nz, double h, const double*
         e = run_inner<float>(L, s, w, op, per, opts->tol, maxiter, st, &r);
         if (e != PB_OK) return e;
         ++launches;
-        coded_launches += r.coded;
+        coded_launches += r.coded ? 1 : 0;
         ksec += r.kernel_seconds;
         status = (pb_status)r.status;
         total_iters = r.iters;
@@ -403,9 +403,9 @@ pb_status solve_impl(int32_t nx, int32_t ny, int32_t nz, double h, const double*
             e = run_inner<float>(L, s, w, op, per, inner_tol, maxiter, st, &r);
             if (e != PB_OK) return e;
             ++launches;
-            coded_launches += r.coded;
-            if (r.coded && op == PB_OP_STENCIL) {   // the operator is the same for every inner solve
-                s.codes_valid = 1;
+            coded_launches += r.coded ? 1 : 0;
+            if (op == PB_OP_STENCIL) {   // the operator is the same for every inner solve
+                s.codes_valid = r.coded;
                 s.ctab = r.ctab;
             }
             ksec += r.kernel_seconds;

@@ -2237,7 +2237,7 @@ pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, do
             // whatever pb_set_coded_coefficients says, which is about passes that can read
             // either: the sums of this form come in another order than a pass's
             if (s.q && s.q2 && coded_layout_ok(L) && resident_fits<T>(L, periodic, true)) {
-                bool fits = s.codes_valid != 0;
+                bool fits = s.codes_valid == 1;
                 const float* tab = s.ctab;
                 if (!fits) e = build_codes(s.op, L.npad, (void*)s.q, (uint32_t*)s.q2, st, fits, &tab);
                 unfit = !fits;
@@ -2265,7 +2265,7 @@ pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, do
             return PB_ERR_ARG;
         }
         G = ghost_layout(L);
-        const bool with_op = !s.codes_valid;
+        const bool with_op = s.codes_valid != 2;
         hipLaunchKernelGGL(k_ghost_in<T>, dim3(copy_grid(G.npad)), dim3(256), 0, st, s.op.cx, s.op.cy, s.op.cz,
                            s.op.d, with_op ? (T*)s.gop.cx : nullptr, (T*)s.gop.cy, (T*)s.gop.cz, (T*)s.gop.d, s.b,
                            (const T*)s.x, s.gb, s.gx, s.gr, s.gr2, s.gp0, s.gp1, L.nx, L.ny, L.sp, G.org, G.sp,
@@ -2300,7 +2300,7 @@ pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, do
             const size_t clds = t.lds + kCodedLdsBytes;
             const int cus = di.cus > 0 ? di.cus : 256;
             if (cfn && (int64_t)max_coresident(cfn, t.bs, clds) * cus >= t.grid) {
-                bool fits = s.codes_valid != 0;
+                bool fits = s.codes_valid == (gl ? 2 : 1);
                 const float* tab = s.ctab;
                 uint32_t* words = gl ? s.gcodes : (uint32_t*)s.q2;
                 if (!fits && !unfit) {
@@ -2398,7 +2398,7 @@ pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, do
         res->bb = h.bb;
         res->kernel_seconds = 1e-3 * ms;
         res->tiling = t;
-        res->coded = coded;
+        res->coded = coded ? (gl ? 2 : 1) : 0;
         res->ctab = ctab;
     }
     return PB_OK;

@@ -67,9 +67,11 @@ struct SolveBufs {
     T* z;          // multigrid form only
     T* dia;        // DIA form only: 7 diagonals x npad
     int warm;      // 1: x holds a nonzero initial guess
-    // fused FP32 40-byte form: the code words in q2 and the dictionary (ctab,
-    // inside q) were built for this operator by an earlier inner solve (with
-    // the periodic boundary: the code words in gcodes, the dictionary in q)
+    // fused FP32 forms: the dictionary (ctab, inside q) and the code words were
+    // built for this operator by the inner solve before, which left them in place:
+    // 1 the words in q2, 2 those of the ghost-row layout in gcodes, with gop. (The
+    // form may change from one inner solve to the next, when another thread
+    // records a tiling for the shape.)
     int codes_valid;
     const float* ctab;
     // periodic boundary, 40-byte pass: the operator and the state in the
@@ -114,7 +116,7 @@ struct SolveResult {
     double bb;     // ||b||^2
     double kernel_seconds;   // duration of the iteration kernel / loop (HIP events)
     Tiling tiling;           // fused form: the tiling used
-    int coded;               // fused form: 1 when the pass read coded coefficients
+    int coded;               // fused form: 1 or 2 when it read code words (SolveBufs::codes_valid)
     const float* ctab;       // and the dictionary it used (device)
     int untimed;             // input: 1 = record no HIP events (kernel_seconds stays 0)
     // multigrid: set by a solve whose hierarchy (and level 0's code words) a further
