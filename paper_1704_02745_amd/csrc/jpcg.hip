@@ -40,9 +40,13 @@
 // with p_{l-1} = z + beta p_{l-2}, the pass that has p_{l-1} and z = r/d at hand
 // also has p_{l-2} = (p_{l-1} - z) / beta, so a pass may leave x alone and the next
 // adds both steps, 8 bytes per node in two passes less (36 and 24 bytes on
-// average; 257^3 coded, default tiling, 123 -> 117 us a pass). beta must be at least 1/8: the
-// division then enlarges the rounding of p_{l-1} in one step's share of x eight
-// times at most, against one rounding of x itself that is saved. Whether a pass
+// average; 257^3 coded, default tiling, 123 -> 117 us a pass). beta must be at
+// least kDeferBeta: the division enlarges the rounding of p_{l-1} in one step's
+// share of x by 1/beta, against one rounding of x itself that is saved. From 0.8 on
+// the rounding error of x (root mean square against 64 bits, FP32, 33^3 to
+// 65 x 57 x 61) is that of adding every step by itself to a percent; from 1/8 on it
+// was up to 24% larger while beta is small, in a solve's first ten passes. 47% of the
+// passes at 193^3 and 44% at 97^3 leave x alone (50% from 1/8 on). Whether a pass
 // takes x follows from beta alone, so it is the same in both forms.
 //
 // Reductions and the grid barrier: each tile reduces its sums in a fixed
@@ -854,6 +858,8 @@ __device__ __forceinline__ void ghost_of(const KArgs<T>& a, int64_t q0, int nv, 
         if (u < nv && j >= a.ny - 2) gd[u] = q0 + u - span;
     }
 }
+
+constexpr double kDeferBeta = 0.8;   // least beta at which a pass leaves x to the next
 
 // What a pass of the 40-byte form does with x: nothing, x += a p_old, or also
 // x += c (p_old - r_old/d), the step of the direction before p_old.
@@ -1727,7 +1733,7 @@ __device__ void run_problem(const KArgs<T>& a, int w, int G, bool xcd_map, unsig
             if (sc.x_pending != 0.0) {
                 xs.mode = 2;
                 xs.c = (T)(sc.x_pending / sc.x_beta);
-            } else if (beta >= T(0.125)) {
+            } else if (beta >= T(kDeferBeta)) {
                 xs.mode = 0;
                 x_pending = (double)alpha;
                 x_beta = (double)beta;
