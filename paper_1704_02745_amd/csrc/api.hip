@@ -214,9 +214,10 @@ pb_status prepare(const Layout& L, double h, const double* eps_x, const double* 
 }
 
 // Time `iters` iterations of the fused kernel with tiling t (second of two runs).
+// resident: whether they ran in the resident form.
 template <typename T>
 pb_status time_tiling(const Layout& L, const SolveBufs<T>& s, const SolveWs& w, const Tiling& t, int iters,
-                      hipStream_t st, double& us_per_iter) {
+                      hipStream_t st, double& us_per_iter, bool* resident = nullptr) {
     SolveResult r{};
     for (int rep = 0; rep < 2; ++rep) {
         pb_status e = fused_jpcg<T>(L, s, w.sync, w.partials, 1e-300, iters, st, &r, &t, 0);
@@ -231,6 +232,7 @@ pb_status time_tiling(const Layout& L, const SolveBufs<T>& s, const SolveWs& w, 
         return PB_ERR_ARG;
     }
     us_per_iter = 1e6 * r.kernel_seconds / r.iters;
+    if (resident) *resident = r.tiling.grid == 0;
     return PB_OK;
 }
 
@@ -253,14 +255,16 @@ pb_status autotune_impl(const Layout& L, const SolveBufs<T>& s, const SolveWs& w
             best_t = t;
         }
     }
-    // the resident form of the same solve, where the grid fits it
+    best_t.resident = 2;
+    // the resident form of the same solve, where the grid (and the operator) fits it
     Tiling rt = best_t;
     rt.resident = 1;
     if (resident_fits<T>(L, 0, false) || (sizeof(T) == 4 && resident_fits<T>(L, 0, true))) {
         double us = 0.0;
-        pb_status e = time_tiling<T>(L, s, w, rt, iters, st, us);
+        bool ran = false;
+        pb_status e = time_tiling<T>(L, s, w, rt, iters, st, us, &ran);
         if (e != PB_OK) return e;
-        if (us < best_us) {
+        if (ran && us < best_us) {
             best_us = us;
             best_t = rt;
         }

@@ -2082,14 +2082,14 @@ void record_tiling(const Layout& L, const Tiling& t) {
 }
 
 // Whether a solve of this shape runs the streaming form although the resident
-// one may take it: a tiling recorded by the caller, an autotuner's verdict, or a
-// periodic pass form.
+// one may take it: a tiling recorded by the caller, an autotuner's verdict (for
+// the free boundary, which it timed), or a periodic pass form.
 template <typename T>
 bool streaming_asked(const Layout& L, int periodic) {
     if (periodic && periodic_pass() >= 0) return true;
     std::lock_guard<std::mutex> lk(g_tune_mu);
     const auto it = g_tuned.find(tune_key<T>(L));
-    return it != g_tuned.end() && !it->second.resident;
+    return it != g_tuned.end() && (it->second.resident == 0 || (it->second.resident == 2 && !periodic));
 }
 template void record_tiling<float>(const Layout&, const Tiling&);
 template void record_tiling<double>(const Layout&, const Tiling&);
@@ -2235,7 +2235,7 @@ template <typename T>
 pb_status fused_jpcg(const Layout& L, const SolveBufs<T>& s, SyncState* sync, double* partials, double tol,
                      int maxiter, hipStream_t st, SolveResult* res, const Tiling* force, int periodic) {
     bool unfit = false;   // the operator is known not to fit a dictionary
-    if (force ? force->resident != 0 : !streaming_asked<T>(L, periodic)) {
+    if (force ? force->resident == 1 : !streaming_asked<T>(L, periodic)) {
         bool ran = false;
         pb_status e = resident_jpcg<T>(L, s, sync, partials, tol, maxiter, st, res, periodic, nullptr, nullptr, ran);
         if (e != PB_OK || ran) return e;

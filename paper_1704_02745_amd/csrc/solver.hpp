@@ -46,7 +46,10 @@ struct Tiling {
     int nseg, nzc, ntiles;
     int halo;        // in-plane halo, >= nx, multiple of the vector width
     int grid;        // workgroups of the cooperative launch
-    int resident;    // 1: the resident form was the faster one for this shape (autotuner)
+    // a recorded tiling's form: 0 streaming (the caller's choice), 1 resident where it
+    // takes the solve, 2 streaming because it was the faster one in the autotuner's
+    // trials, which are of the free boundary
+    int resident;
 };
 
 constexpr int kMaxTiles = 65536;
