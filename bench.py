@@ -54,7 +54,10 @@ PASS_BYTES_BY_SCHEME = {0: 48, 1: 40}
 CODED_PASS_BYTES = 28
 
 
-def form_bytes(scheme: int, coded: bool) -> int:
+def form_bytes(scheme: int, coded: bool):
+    """Bytes per unknown and iteration of a pass form; None for the resident form (scheme + 2)."""
+    if scheme >= 2:
+        return None
     return CODED_PASS_BYTES if (scheme == 1 and coded) else PASS_BYTES_BY_SCHEME[scheme]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "jpcg_fused_f32_257_traffic.txt")
 KERNEL_SRC = os.path.join(ROOT, "paper_1704_02745_amd", "csrc", "jpcg.hip")
@@ -222,10 +225,10 @@ def bench_c1(pbgpu, torch, synth, dev, reps=3):
                    "iter_loop_ms": round(1e3 * info["kernel_seconds"], 3),
                    "us_per_iter": round(1e6 * info["kernel_seconds"] / max(info["iters"], 1), 2),
                    "algorithmic_gbs": round(ITER_BYTES * n * info["iters"] / info["kernel_seconds"] / 1e9, 1),
-                   "form_gbs": round(per * n * info["iters"] / info["kernel_seconds"] / 1e9, 1),
+                   "form_gbs": per and round(per * n * info["iters"] / info["kernel_seconds"] / 1e9, 1),
                    "form_bytes_per_node_iter": per, "relres_true": info["relres_true"]}
         if op == "stencil":
-            out[op]["pass_form"] = sch
+            out[op]["pass_form"] = sch if sch < 2 else "resident"
             out[op]["coded"] = coded
     out["speedup_stencil_vs_dia"] = round(out["dia"]["iter_loop_ms"] / out["stencil"]["iter_loop_ms"], 2)
     del sm
@@ -669,7 +672,7 @@ def main():
         tuning = pbgpu.autotune(sys0, precision="f32", iters_per_trial=20, workspace=ws)
         del sys0
     print(f"bench: tuning {tuning}", file=sys.stderr, flush=True)
-    scheme = tuning["scheme"]
+    scheme = tuning["scheme"] % 2   # (257^3 does not fit the resident form)
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()

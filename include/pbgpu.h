@@ -265,7 +265,11 @@ typedef struct {
     double us_per_iter;     /* measured microseconds per CG iteration (pb_autotune only) */
     int32_t candidates;     /* tilings timed (pb_autotune only) */
     int32_t scheme;         /* pass form: 0 stores A.p (48 B/node/iteration in FP32),
-                               1 recomputes A.p_old from p_old (40 B/node/iteration) */
+                               1 recomputes A.p_old from p_old (40 B/node/iteration); plus 2 where
+                               solves run in the resident form instead (the iteration state in
+                               registers and LDS), the tiling being that of the solves it does not
+                               take: operators without code words on grids of about 134 to 171 nodes
+                               an edge */
     int32_t streaming;      /* 1: nontemporal loads and stores for the streams no step reads again
                                (the default once a pass's arrays exceed 1.75 times the 256 MiB
                                last-level cache); 0: cached accesses; -1 (pb_set_tuning only): the
@@ -280,7 +284,8 @@ typedef struct {
  * for `iters_per_trial` iterations on the given system, and record the
  * fastest for this device, grid shape and precision (FP64 vs FP32/REFINE64)
  * in the library's per-process table; later pb_solve calls on that shape use
- * it. The iteration itself is the solver's own (section 2.2 with M = diag A);
+ * it. The resident form is timed too, where it takes the system; its verdict
+ * holds for the free boundary. The iteration itself is the solver's own (section 2.2 with M = diag A);
  * only its launch shape is searched. Arrays and workspace as for pb_solve
  * (opts->op must be PB_OP_STENCIL; opts->tol and maxiter are ignored).
  * best (host, nullable) receives the winner. Errors: PB_ERR_ARG (also for a
@@ -294,16 +299,17 @@ pb_status pb_autotune(int32_t nx, int32_t ny, int32_t nz, double h,
 
 /*
  * pb_set_tuning: record a tiling (for instance one saved from an earlier
- * pb_autotune) for this grid shape and precision on the current device.
- * Fields us_per_iter/candidates are ignored. PB_ERR_ARG if the tiling is not
- * feasible for this shape and device.
+ * pb_autotune or pb_get_tuning) for this grid shape and precision on the
+ * current device. scheme 0 or 1 makes solves of the shape run that pass; 2 or 3
+ * leaves them to the resident form. Fields us_per_iter/candidates are ignored.
+ * PB_ERR_ARG if the tiling is not feasible for this shape and device.
  */
 pb_status pb_set_tuning(int32_t nx, int32_t ny, int32_t nz, int32_t precision, const pb_tuning* tuning);
 
 /*
- * pb_get_tuning: the tiling pb_solve will use for this grid shape and
- * precision on the current device: the one recorded by pb_autotune or
- * pb_set_tuning, else the library's default choice. us_per_iter and
+ * pb_get_tuning: the tiling and form pb_solve (free boundary) will use for this
+ * grid shape and precision on the current device: the one recorded by
+ * pb_autotune or pb_set_tuning, else the library's default choice. us_per_iter and
  * candidates are 0. Errors: PB_ERR_ARG (bad dims or precision, null out, or
  * no feasible tiling: nx too large for the in-plane halo).
  */

@@ -399,7 +399,8 @@ def autotune(sysm: System, precision="f32", iters_per_trial=20,
 
 def set_tuning(nx, ny, nz, precision, block, groups, zchunk, grid, scheme=0, streaming=-1, segments=0) -> None:
     """Record a tiling of the fused kernel for this grid shape and precision;
-    scheme 0 is the pass that stores A.p, 1 the 40-byte pass that recomputes it;
+    scheme 0 is the pass that stores A.p, 1 the 40-byte pass that recomputes it,
+    2 and 3 leave solves that the resident form takes to it;
     streaming 1 / 0 selects nontemporal / cached accesses, -1 the shape's default;
     segments > 0 picks the tiling with that many in-plane segments."""
     t = Tuning()
@@ -465,7 +466,8 @@ def load_tuning(path) -> int:
     n = 0
     for e in json.load(open(path)):
         try:
-            set_tuning(e["nx"], e["ny"], e["nz"], e["precision"], e["block"], e["groups"], e["zchunk"], e["grid"])
+            set_tuning(e["nx"], e["ny"], e["nz"], e["precision"], e["block"], e["groups"], e["zchunk"], e["grid"],
+                       e.get("scheme", 0), e.get("streaming", -1), e.get("segments", 0))
             n += 1
         except PBError:
             pass

@@ -213,6 +213,8 @@ pb_status prepare(const Layout& L, double h, const double* eps_x, const double* 
     return PB_OK;
 }
 
+constexpr int kTuningResident = 2;   // pb_tuning.scheme: added for the resident form
+
 // Time `iters` iterations of the fused kernel with tiling t (second of two runs).
 // resident: whether they ran in the resident form.
 template <typename T>
@@ -273,7 +275,7 @@ pb_status autotune_impl(const Layout& L, const SolveBufs<T>& s, const SolveWs& w
     if (best) {
         best->block = best_t.bs;
         best->groups = best_t.mc;
-        best->scheme = best_t.scheme;
+        best->scheme = best_t.scheme + (best_t.resident == 1 ? kTuningResident : 0);
         best->streaming = best_t.nt;
         best->zchunk = best_t.zchunk;
         best->grid = best_t.grid;
@@ -567,6 +569,7 @@ extern "C" pb_status pb_get_tuning(int32_t nx, int32_t ny, int32_t nz, int32_t p
     t.zchunk = c.zchunk;
     t.grid = c.grid;
     t.scheme = c.scheme;
+    if (precision == PB_F64 ? resident_chosen<double>(L) : resident_chosen<float>(L)) t.scheme += kTuningResident;
     t.streaming = c.nt;
     t.segments = c.nseg;
     *out = t;
@@ -606,9 +609,13 @@ extern "C" pb_status pb_set_tuning(int32_t nx, int32_t ny, int32_t nz, int32_t p
     auto apply = [&](auto tag) -> pb_status {
         using T = decltype(tag);
         const int nt = t->streaming >= 0 ? t->streaming : streaming_for<T>(L);
-        for (const Tiling& c : tiling_candidates<T>(L)) {
-            if (c.bs == t->block && c.mc == t->groups && c.scheme == t->scheme && c.nt == nt &&
+        const bool resident = t->scheme >= kTuningResident &&
+                              (resident_fits<T>(L, 0, false) || (sizeof(T) == 4 && resident_fits<T>(L, 0, true)));
+        const int scheme = resident ? t->scheme - kTuningResident : t->scheme;
+        for (Tiling c : tiling_candidates<T>(L)) {
+            if (c.bs == t->block && c.mc == t->groups && c.scheme == scheme && c.nt == nt &&
                 c.zchunk == t->zchunk && c.grid == t->grid && (t->segments <= 0 || c.nseg == t->segments)) {
+                c.resident = resident ? 1 : 0;
                 record_tiling<T>(L, c);
                 return PB_OK;
             }

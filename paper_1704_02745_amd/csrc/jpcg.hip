@@ -2091,6 +2091,13 @@ bool streaming_asked(const Layout& L, int periodic) {
     const auto it = g_tuned.find(tune_key<T>(L));
     return it != g_tuned.end() && (it->second.resident == 0 || (it->second.resident == 2 && !periodic));
 }
+template <typename T>
+bool resident_chosen(const Layout& L) {
+    return !streaming_asked<T>(L, 0) &&
+           (resident_fits<T>(L, 0, false) || (sizeof(T) == 4 && resident_fits<T>(L, 0, true)));
+}
+template bool resident_chosen<float>(const Layout&);
+template bool resident_chosen<double>(const Layout&);
 template void record_tiling<float>(const Layout&, const Tiling&);
 template void record_tiling<double>(const Layout&, const Tiling&);
 

@@ -231,6 +231,10 @@ template <typename T>
 std::vector<Tiling> tiling_candidates(const Layout& L);
 template <typename T>
 void record_tiling(const Layout& L, const Tiling& t);
+// Whether a solve with the free boundary runs in the resident form (for a grid
+// that only the compact form takes: if its operator fits a dictionary).
+template <typename T>
+bool resident_chosen(const Layout& L);
 
 // dia.hip: DIA SpMV plus separate vector kernels, host-driven loop.
 template <typename T>

@@ -50,3 +50,42 @@ def test_verdict_is_of_the_boundary_it_was_timed_on(pb):
     assert form(pb, box, **kw) == "resident" and form(pb, free, **kw) == "fused"
     pb.autotune(free, precision="f32", iters_per_trial=3)
     assert form(pb, free, **kw) == "fused" and form(pb, box, **kw) == "resident"
+
+
+# 257^3-class grids stream; the others run resident, full or compact, whatever the autotuner found
+@pytest.mark.parametrize("dims,prec", [((65, 57, 61), "f32"), ((141, 139, 137), "f32"), ((61, 53, 47), "f64"),
+                                       ((201, 193, 189), "f32")])
+def test_saved_tuning_restores_the_form(pb, dims, prec, tmp_path):
+    sysm = molecule_system(pb, dims, 100, 5)
+    kw = dict(tol=1e-4, precision=prec)
+    best = pb.autotune(sysm, precision=prec, iters_per_trial=20)
+    tuned = form(pb, sysm, **kw)
+    assert (best["scheme"] >= 2) == (tuned == "resident")
+    entry = dict(best, nx=dims[0], ny=dims[1], nz=dims[2], precision=prec)
+    pb.save_tuning(tmp_path / "tuning.json", [entry])
+    # from another record for the shape back to the saved one
+    c = pb.tiling_candidates(*dims, prec)[0]
+    pb.set_tuning(*dims, prec, c["block"], c["groups"], c["zchunk"], c["grid"], c["scheme"], c["streaming"], c["segments"])
+    assert form(pb, sysm, **kw) == "fused" and pb.get_tuning(*dims, prec)["scheme"] == c["scheme"]
+    assert pb.load_tuning(tmp_path / "tuning.json") == 1
+    got = pb.get_tuning(*dims, prec)
+    assert form(pb, sysm, **kw) == tuned and all(got[k] == best[k] for k in got)
+
+
+@pytest.mark.parametrize("dims,prec,resident", [((45, 41, 47), "f32", True), ((133, 141, 149), "f32", True),
+                                                ((41, 45, 37), "f64", True), ((191, 193, 189), "f32", False),
+                                                ((129, 127, 131), "f64", False)])
+def test_default_tuning_is_what_runs(pb, dims, prec, resident):
+    """pb_get_tuning of a shape nothing was recorded for names the form that runs, and recording what it
+    returned changes nothing; the resident form is refused where the grid does not fit it."""
+    sysm = molecule_system(pb, dims, 60, 6)
+    t = pb.get_tuning(*dims, prec)
+    kw = dict(tol=1e-3, precision=prec)
+    want = "resident" if resident else "fused"
+    assert (t["scheme"] >= 2) == resident and form(pb, sysm, **kw) == want
+    args = (t["block"], t["groups"], t["zchunk"], t["grid"])
+    pb.set_tuning(*dims, prec, *args, t["scheme"], t["streaming"], t["segments"])
+    assert form(pb, sysm, **kw) == want and pb.get_tuning(*dims, prec) == t
+    if not resident:
+        with pytest.raises(pb.PBError):
+            pb.set_tuning(*dims, prec, *args, t["scheme"] + 2, t["streaming"], t["segments"])
