@@ -1801,7 +1801,7 @@ __device__ void run_problem(const KArgs<T>& a, int w, int G, bool xcd_map, unsig
     if (sc.zero || (sc.done && final_update && sc.status != PB_ERR_BREAKDOWN)) {
         for (int t = first; t < end; t += stride)
             final_tile<T, BS>(a, t, (T)sc.alpha, plast, pending, pbefore, sc.zero != 0);
-    } else if (sc.status == PB_ERR_BREAKDOWN && pending != T(0)) {
+    } else if (sc.status == PB_ERR_BREAKDOWN && this_launch > 0 && pending != T(0)) {   // (in this launch)
         for (int t = first; t < end; t += stride)
             final_tile<T, BS>(a, t, pending, pbefore, T(0), (const T*)nullptr, false);
     }
