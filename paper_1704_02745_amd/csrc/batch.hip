@@ -327,11 +327,12 @@ pb_status enqueue_batch(const Plan<T>& P, const pb_problem* probs, int grid, boo
 // another in one table.
 template <typename T>
 pb_status fill_table(const Plan<T>& P, const pb_problem* probs, hipStream_t st) {
+    auto limit = [&](int i) {
+        return probs[i].maxiter > 0 ? probs[i].maxiter : 10 * std::max(probs[i].nx, std::max(probs[i].ny, probs[i].nz));
+    };
     auto args = [&](int i, auto&& fill) {
-        const int maxiter = probs[i].maxiter > 0 ? probs[i].maxiter
-                                                 : 10 * std::max(probs[i].nx, std::max(probs[i].ny, probs[i].nz));
         const int words = P.words[i];
-        fill(maxiter, words ? (const float*)P.s[i].q2 : nullptr, words ? dictionary_table(P.s[i].q) : nullptr,
+        fill(limit(i), words ? (const float*)P.s[i].q2 : nullptr, words ? dictionary_table(P.s[i].q) : nullptr,
              words == 2 ? (const int*)(P.fit + i) : nullptr);
     };
     const size_t nstr = P.str.size();
@@ -347,11 +348,13 @@ pb_status fill_table(const Plan<T>& P, const pb_problem* probs, hipStream_t st) 
     for (int c = 0; c < 2; ++c) {
         const auto& f = P.res[c];
         rhost[c].resize(resident_batch_args_bytes<T>() * f.of.size());
+        double pass_us = 0.0;
+        for (int i : f.of) pass_us += P.rp[i].us * limit(i);
         for (size_t k = 0; k < f.of.size(); ++k) {
             const int i = f.of[k];
             args(i, [&](int maxiter, const float* cw, const float* tab, const int* fit) {
                 resident_batch_fill<T>(rhost[c].data() + resident_batch_args_bytes<T>() * k, P.L[i], P.s[i], &P.sync[i],
-                                       P.slots[i], probs[i].tol, maxiter, (int)f.of.size(), cw, tab, fit);
+                                       P.slots[i], probs[i].tol, maxiter, (int)f.of.size(), pass_us, cw, tab, fit);
             });
         }
         if (!f.of.empty())

@@ -20,9 +20,10 @@ PB_RES_INSTANCES(float)
 // start's residual is; q, or where x by brick takes both direction arrays p, in
 // the place of b, which only the first launch reads, and q then in that of x.
 pb_status resident_serve_fill(void* dst, const Layout& L, const SolveBufs<float>& s, SyncState* S, void* slots,
-                              double tol, int maxiter, int problems, const float* cw, const float* ctab, int chunk,
-                              bool resume) {
-    const pb_status e = resident_batch_fill<float>(dst, L, s, S, slots, tol, maxiter, problems, cw, ctab, nullptr);
+                              double tol, int maxiter, int problems, double pass_us, const float* cw,
+                              const float* ctab, int chunk, bool resume) {
+    const pb_status e =
+        resident_batch_fill<float>(dst, L, s, S, slots, tol, maxiter, problems, pass_us, cw, ctab, nullptr);
     RArgs<float>& a = *(RArgs<float>*)dst;
     const bool compact = resident_batch_plan<float>(L).compact;
     a.keep_r = compact ? s.r2 : s.p0;

@@ -209,6 +209,15 @@ RArgs<T> resident_args(const Layout& L, const SolveBufs<T>& s, const ResPlan& p,
     return a;
 }
 
+// Bound of the wait in the first barrier of one of `problems` in a launch, in ticks:
+// a workgroup may come to it from all the others, each of which may take a bounded
+// wait and all its passes (by the model, which the real ones exceed up to twofold, more
+// where the device is shared: ten times), and must not give up on them.
+long long first_wait_ticks(long long wait_ticks, int problems, double pass_us, double ticks_per_us) {
+    const double t = (double)wait_ticks * (1.0 + problems) + 10.0 * pass_us * ticks_per_us;
+    return t < 4e18 ? (long long)t : (long long)4e18;
+}
+
 template <typename T>
 pb_status launch_resident_start(const Layout& L, const Op<T>& op, const T* b, const T* x, T* r, int periodic,
                                 hipStream_t st) {
@@ -318,7 +327,8 @@ size_t resident_batch_args_bytes() {
 }
 template <typename T>
 pb_status resident_batch_fill(void* dst, const Layout& L, const SolveBufs<T>& s, SyncState* S, void* slots, double tol,
-                              int maxiter, int problems, const float* cw, const float* ctab, const int* fit) {
+                              int maxiter, int problems, double pass_us, const float* cw, const float* ctab,
+                              const int* fit) {
     ResPlan p = resident_plan<T>(L, 0, true, false);
     const bool compact = p.grid <= 0;
     if (compact) p = resident_plan<T>(L, 0, true, true);
@@ -328,7 +338,7 @@ pb_status resident_batch_fill(void* dst, const Layout& L, const SolveBufs<T>& s,
     a.faces[1] = xmem ? s.r + (int64_t)p.grid * face_len(p.bs, p.nz, p.tx, p.ty) : s.r2;
     a.xs = s.p0;
     if (s.warm) a.r0 = xmem ? s.r2 : s.p0;
-    a.first_timeout_ticks = a.timeout_ticks * (1 + (long long)problems);
+    a.first_timeout_ticks = first_wait_ticks(a.timeout_ticks, problems, pass_us, (double)a.timeout_ticks / 20e6);
     a.cw = (const uint32_t*)cw;
     a.ctab = ctab;
     a.fit = fit;
@@ -365,7 +375,7 @@ pb_status resident_batch_launch(const void* d_args, const int* d_off, const void
     template ResBatchPlan resident_batch_plan<T>(const Layout&);                                                  \
     template size_t resident_batch_args_bytes<T>();                                                               \
     template pb_status resident_batch_fill<T>(void*, const Layout&, const SolveBufs<T>&, SyncState*, void*, double, \
-                                              int, int, const float*, const float*, const int*);                  \
+                                              int, int, double, const float*, const float*, const int*);          \
     template pb_status resident_batch_start<T>(const Layout&, const SolveBufs<T>&, hipStream_t);                  \
     template pb_status resident_batch_launch<T>(const void*, const int*, const void*, int, size_t, bool, hipStream_t, \
                                                 bool);

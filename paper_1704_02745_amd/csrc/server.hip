@@ -648,10 +648,12 @@ extern "C" pb_status pb_server_step(pb_server* S, int32_t chunk, void* stream, i
             std::vector<int> grids;
             std::vector<double> cost;
             int sum = 0;
+            double pass_us = 0.0;
+            for (size_t k = 0; k < Rs[c].size(); ++k) pass_us += Rs[c][k].us * rchunk[k];
             for (size_t k = 0; k < Rs[c].size(); ++k, ++i) {
                 Slot& s = *run[i];
                 e = resident_serve_fill(S->host_rtable.data() + rkb * i, s.L, s.s, s.S, s.partials, tol_of(s), s.maxiter,
-                                        nres, code_words(s), code_table(s), rchunk[k], s.resume);
+                                        nres, pass_us, code_words(s), code_table(s), rchunk[k], s.resume);
                 if (e != PB_OK) return e;
                 e = launch_fill<int>((int*)s.partials, (int64_t)(s.rp.slot_bytes / sizeof(int)), 0, st);
                 if (e != PB_OK) return e;

@@ -159,10 +159,12 @@ template <typename T>
 ResBatchPlan resident_batch_plan(const Layout& L);
 template <typename T>
 size_t resident_batch_args_bytes();
-// `problems`: how many share the launch (bounds the wait of a first barrier).
+// problems, pass_us: how many share the launch, and what their passes take by the
+// model at their iteration limits (they bound the wait of a first barrier).
 template <typename T>
 pb_status resident_batch_fill(void* dst, const Layout& L, const SolveBufs<T>& s, SyncState* S, void* slots, double tol,
-                              int maxiter, int problems, const float* cw, const float* ctab, const int* fit);
+                              int maxiter, int problems, double pass_us, const float* cw, const float* ctab,
+                              const int* fit);
 template <typename T>
 pb_status resident_batch_start(const Layout& L, const SolveBufs<T>& s, hipStream_t st);   // warm starts: b - A x0
 template <typename T>
@@ -273,8 +275,8 @@ pb_status batch_state_digests(const void* d_kargs, int nprob, StateDigest* out, 
 // advancing a request by up to `chunk` iterations. Between launches the state
 // arrays hold r and p; in the compact form p takes the place of b.
 pb_status resident_serve_fill(void* dst, const Layout& L, const SolveBufs<float>& s, SyncState* S, void* slots,
-                              double tol, int maxiter, int problems, const float* cw, const float* ctab, int chunk,
-                              bool resume);
+                              double tol, int maxiter, int problems, double pass_us, const float* cw,
+                              const float* ctab, int chunk, bool resume);
 pb_status resident_serve_launch(const void* d_args, const int* d_off, const void* d_jobs, int grid, size_t lds,
                                 bool compact, hipStream_t st);
 pb_status resident_serve_digests(const void* d_args, int n, StateDigest* out, hipStream_t st);
