@@ -81,6 +81,7 @@ struct KArgs {
     T* q[2];
     T* p[2];
     int nx, ny, nz;
+    int unless_fit;      // 1: nothing to do when *fit is 1 (another launch solves the problem)
     int64_t sp;
     // Owned positions of a plane: [org, org + own). The plain layout owns the
     // whole padded plane (org 0, own sp); the ghost-row layout of the
@@ -99,7 +100,6 @@ struct KArgs {
     const float* cw;     // coded 40-byte pass: one word of coefficient codes per position (bit patterns)
     const float* ctab;   // and the dictionary (kCodedTableSize values)
     const int* fit;      // runtime-checked coded launches: 1 when this problem's dictionary holds its operator
-    int unless_fit;      // 1: nothing to do when it does (another launch solved the problem)
 };
 
 // LDS scratch of the reductions below, in doubles.

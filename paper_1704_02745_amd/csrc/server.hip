@@ -249,9 +249,13 @@ struct Server {
     size_t arena_bytes = 0;
     int max_slots = 0;
     char* table = nullptr;        // device: kernel-argument records for max_slots
-    char* rtable = nullptr;       // device: the same of the resident form
-    int* job_off = nullptr;       // device: its job lists (resident_schedule)
+    // the resident launches' job lists (resident_schedule): pinned host memory that the
+    // kernels read (two words a workgroup and a pair a job, once a launch), so that the
+    // arena holds requests. A step waits for its launches, so the next may write them.
+    int* job_off = nullptr;
     int* jobs = nullptr;
+    size_t jobs_cap = 0;          // pairs
+    bool lists_busy = false;      // a step ended (in an error) without that wait
     int* first = nullptr;         // device: workgroup offsets
     StateDigest* digests = nullptr;   // device: each running request's scalars after a launch
     SlotRec* recs = nullptr;      // device: one record per admitted slot (max_slots)
@@ -266,11 +270,25 @@ struct Server {
     hipEvent_t ev[2] = {nullptr, nullptr};
     hipEvent_t ev_in = nullptr;      // the caller's stream at the start of a step
     hipStream_t adm = nullptr;       // admissions (setup, preparation), overlapping the running launch
-    std::vector<char> host_table, host_rtable;
+    std::vector<char> host_table;
     std::vector<int> host_first;
     std::vector<StateDigest> host_digests;
     std::vector<SlotRec> host_recs;
     std::vector<int> free_recs;   // unused record indices
+
+    // the lists free to be written, with room for `pairs` jobs
+    pb_status open_lists(size_t pairs) {
+        if (lists_busy) PB_HIP(hipDeviceSynchronize());
+        lists_busy = true;
+        if (pairs <= jobs_cap) return PB_OK;
+        const size_t cap = std::max(pairs, 2 * jobs_cap);
+        if (jobs) PB_HIP(hipHostFree(jobs));
+        jobs = nullptr;
+        jobs_cap = 0;
+        PB_HIP(hipHostMalloc((void**)&jobs, 2 * sizeof(int) * cap, hipHostMallocDefault));
+        jobs_cap = cap;
+        return PB_OK;
+    }
 
     // one copy of every record, on the stream (the caller synchronises)
     pb_status read_recs(hipStream_t st) {
@@ -355,29 +373,25 @@ extern "C" pb_status pb_server_create(void* arena, size_t arena_bytes, int32_t m
     S->arena = (char*)arena;
     S->arena_bytes = arena_bytes;
     S->max_slots = max_slots;
-    const size_t tb = align_up(batch_kargs_bytes<float>() * (size_t)max_slots, 256);
+    // (a running request has a record of either form)
+    const size_t tb =
+        align_up(std::max(batch_kargs_bytes<float>(), resident_batch_args_bytes<float>()) * (size_t)max_slots, 256);
     const size_t fb = align_up(sizeof(int) * (size_t)(max_slots + 1), 256);
     const size_t db = align_up(sizeof(StateDigest) * (size_t)max_slots, 256);
     const size_t rb = align_up(sizeof(SlotRec) * (size_t)max_slots, 256);
-    const size_t ab = align_up(resident_batch_args_bytes<float>() * (size_t)max_slots, 256);
-    const size_t ob = align_up(2 * sizeof(int) * (kServeGroups + 1), 256);
-    const size_t jb = align_up(2 * sizeof(int) * kServeGroups * (size_t)max_slots, 256);
-    PB_ARG(arena_bytes > tb + fb + db + rb + ab + ob + jb, "pb_server_create: arena too small");
+    PB_ARG(arena_bytes > tb + fb + db + rb, "pb_server_create: arena too small");
     S->table = S->arena;
     S->first = (int*)(S->arena + tb);
     S->digests = (StateDigest*)(S->arena + tb + fb);
     S->recs = (SlotRec*)(S->arena + tb + fb + db);
-    S->rtable = S->arena + tb + fb + db + rb;
-    S->job_off = (int*)(S->rtable + ab);
-    S->jobs = (int*)(S->rtable + ab + ob);
-    S->reserved = tb + fb + db + rb + ab + ob + jb;
+    S->reserved = tb + fb + db + rb;
     S->host_digests.resize(max_slots);
     S->host_recs.resize(max_slots);
     for (int i = max_slots - 1; i >= 0; --i) S->free_recs.push_back(i);
     S->free_list.push_back({S->reserved, arena_bytes - S->reserved});
-    S->host_table.resize(batch_kargs_bytes<float>() * (size_t)max_slots);
-    S->host_rtable.resize(resident_batch_args_bytes<float>() * (size_t)max_slots);
+    S->host_table.resize(tb);
     S->host_first.resize(max_slots + 1);
+    PB_HIP(hipHostMalloc((void**)&S->job_off, 2 * sizeof(int) * (kServeGroups + 1), hipHostMallocDefault));
     PB_HIP(hipEventCreate(&S->ev[0]));
     PB_HIP(hipEventCreate(&S->ev[1]));
     PB_HIP(hipEventCreateWithFlags(&S->ev_in, hipEventDisableTiming));
@@ -639,9 +653,11 @@ extern "C" pb_status pb_server_step(pb_server* S, int32_t chunk, void* stream, i
         auto code_words = [&](const Slot& s) { return reads_codes(s) ? (const float*)s.s.q2 : nullptr; };
         auto code_table = [&](const Slot& s) { return reads_codes(s) ? dictionary_table(s.s.q) : nullptr; };
         auto tol_of = [](const Slot& s) { return s.precision == PB_F32 ? s.req.tol : kInnerTol; };
+        // one table: the resident requests' records, then the pass form's
         std::vector<int> joff[2], jobs[2], first(npass + 1, 0), chunks(npass, chunk);
-        int rgroups[2] = {0, 0}, job0[2] = {0, 0};
-        const size_t rkb = resident_batch_args_bytes<float>();
+        int rgroups[2] = {0, 0};
+        size_t job0[2] = {0, 0};
+        const size_t rkb = resident_batch_args_bytes<float>(), pass0 = rkb * nres;
         for (int c = 0, i = 0; c < 2; ++c) {
             if (Rs[c].empty()) continue;
             const std::vector<int> rchunk = resident_chunks(Rs[c], chunk);
@@ -652,7 +668,7 @@ extern "C" pb_status pb_server_step(pb_server* S, int32_t chunk, void* stream, i
             for (size_t k = 0; k < Rs[c].size(); ++k) pass_us += Rs[c][k].us * rchunk[k];
             for (size_t k = 0; k < Rs[c].size(); ++k, ++i) {
                 Slot& s = *run[i];
-                e = resident_serve_fill(S->host_rtable.data() + rkb * i, s.L, s.s, s.S, s.partials, tol_of(s), s.maxiter,
+                e = resident_serve_fill(S->host_table.data() + rkb * i, s.L, s.s, s.S, s.partials, tol_of(s), s.maxiter,
                                         nres, pass_us, code_words(s), code_table(s), rchunk[k], s.resume);
                 if (e != PB_OK) return e;
                 e = launch_fill<int>((int*)s.partials, (int64_t)(s.rp.slot_bytes / sizeof(int)), 0, st);
@@ -664,24 +680,29 @@ extern "C" pb_status pb_server_step(pb_server* S, int32_t chunk, void* stream, i
             }
             rgroups[c] = std::min({sum, Rs[c][0].groups, kServeGroups});
             resident_schedule(grids, cost, rgroups[c], joff[c], jobs[c]);
-            job0[c] = c == 0 ? 0 : (int)jobs[0].size();
-            PB_HIP(hipMemcpyAsync(S->job_off + c * (kServeGroups + 1), joff[c].data(), sizeof(int) * joff[c].size(),
-                                  hipMemcpyHostToDevice, st));
-            PB_HIP(hipMemcpyAsync(S->jobs + job0[c], jobs[c].data(), sizeof(int) * jobs[c].size(),
-                                  hipMemcpyHostToDevice, st));
         }
-        if (nres > 0) PB_HIP(hipMemcpyAsync(S->rtable, S->host_rtable.data(), rkb * nres, hipMemcpyHostToDevice, st));
+        if (nres > 0) {
+            job0[1] = jobs[0].size();
+            if ((e = S->open_lists((jobs[0].size() + jobs[1].size()) / 2)) != PB_OK) return e;
+            for (int c = 0; c < 2; ++c) {
+                std::copy(joff[c].begin(), joff[c].end(), S->job_off + c * (kServeGroups + 1));
+                std::copy(jobs[c].begin(), jobs[c].end(), S->jobs + job0[c]);
+            }
+        }
         if (npass > 0) {
             share_launch(Ts, cap, chunk, first, chunks);
             const size_t kb = batch_kargs_bytes<float>();
             for (int i = 0; i < npass; ++i) {
                 Slot& s = *run[nres + i];
-                batch_fill_kargs<float>(S->host_table.data() + kb * i, s.L, s.s, s.S, s.partials, s.t, tol_of(s),
+                batch_fill_kargs<float>(S->host_table.data() + pass0 + kb * i, s.L, s.s, s.S, s.partials, s.t, tol_of(s),
                                         s.maxiter, s.resume ? 1 : 0, chunks[i], code_words(s), code_table(s));
             }
-            PB_HIP(hipMemcpyAsync(S->table, S->host_table.data(), kb * npass, hipMemcpyHostToDevice, st));
+        }
+        PB_HIP(hipMemcpyAsync(S->table, S->host_table.data(), pass0 + batch_kargs_bytes<float>() * npass,
+                              hipMemcpyHostToDevice, st));
+        if (npass > 0) {
             PB_HIP(hipMemcpyAsync(S->first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice, st));
-            e = batch_reset_arrivals<float>(S->table, npass, st);
+            e = batch_reset_arrivals<float>(S->table + pass0, npass, st);
             if (e != PB_OK) return e;
         }
         PB_HIP(hipEventRecord(S->ev[0], st));
@@ -690,23 +711,24 @@ extern "C" pb_status pb_server_step(pb_server* S, int32_t chunk, void* stream, i
         // waiting for a slot get one as the admissions' kernels finish
         for (int c = 0; c < 2; ++c) {
             if (Rs[c].empty()) continue;
-            e = resident_serve_launch(S->rtable + (c == 0 ? 0 : rkb * count[kFull]), S->job_off + c * (kServeGroups + 1),
+            e = resident_serve_launch(S->table + (c == 0 ? 0 : rkb * count[kFull]), S->job_off + c * (kServeGroups + 1),
                                       S->jobs + job0[c], rgroups[c], rlds[c], c == kCompact, st);
             if (e != PB_OK) return e;
         }
         if (npass > 0) {
-            e = batch_launch<float>(S->table, S->first, npass, first.back(), lds, st, false, coded);
+            e = batch_launch<float>(S->table + pass0, S->first, npass, first.back(), lds, st, false, coded);
             if (e != PB_OK) return e;
         }
         PB_HIP(hipEventRecord(S->ev[1], st));
         // every running request's scalars in one read-back
-        if (nres > 0 && (e = resident_serve_digests(S->rtable, nres, S->digests, st)) != PB_OK) return e;
-        if (npass > 0 && (e = batch_state_digests<float>(S->table, npass, S->digests + nres, st)) != PB_OK) return e;
+        if (nres > 0 && (e = resident_serve_digests(S->table, nres, S->digests, st)) != PB_OK) return e;
+        if (npass > 0 && (e = batch_state_digests<float>(S->table + pass0, npass, S->digests + nres, st)) != PB_OK) return e;
         PB_HIP(hipMemcpyAsync(S->host_digests.data(), S->digests, sizeof(StateDigest) * run.size(),
                               hipMemcpyDeviceToHost, st));
         // this step's admissions, while the launch runs
         if (!admitted.empty() && (e = process_admitted()) != PB_OK) return e;
         PB_HIP(hipStreamSynchronize(st));
+        S->lists_busy = false;
         float ms = 0;
         PB_HIP(hipEventElapsedTime(&ms, S->ev[0], S->ev[1]));
         S->device_seconds += 1e-3 * ms;
@@ -833,9 +855,12 @@ extern "C" pb_status pb_server_stats(const pb_server* S, pb_server_stats_t* out)
 extern "C" void pb_server_destroy(pb_server* S) {
     if (!S) return;
     if (S->adm) (void)hipStreamSynchronize(S->adm);
+    if (S->lists_busy) (void)hipDeviceSynchronize();
     if (S->ev[0]) (void)hipEventDestroy(S->ev[0]);
     if (S->ev[1]) (void)hipEventDestroy(S->ev[1]);
     if (S->ev_in) (void)hipEventDestroy(S->ev_in);
     if (S->adm) (void)hipStreamDestroy(S->adm);
+    if (S->jobs) (void)hipHostFree(S->jobs);
+    if (S->job_off) (void)hipHostFree(S->job_off);
     delete S;
 }
