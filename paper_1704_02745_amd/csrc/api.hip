@@ -338,12 +338,12 @@ pb_status solve_impl(int32_t nx, int32_t ny, int32_t nz, double h, const double*
     hipStream_t st = (hipStream_t)stream_;
     bool singular = false;
     // where the solve is short, the flags are read with its results: on a refused
-    // system the solve ends by itself (no access depends on a value), and nothing of
-    // it is handed back. With one pass less at the end, 33^3 in FP64 510 -> 492 us a
-    // solve, 97 x 105 x 89 1,987 -> 1,939.
-    const bool later = op == PB_OP_STENCIL && !per &&
-                       (prec == PB_F64 ? resident_fits<double>(L, 0, false)
-                                       : prec == PB_F32 && resident_fits<float>(L, 0, false));
+    // system its kernel does nothing, and nothing is handed back. With one pass less at
+    // the end, 33^3 in FP64 510 -> 492 us a solve, 97 x 105 x 89 1,987 -> 1,939.
+    const bool later =
+        op == PB_OP_STENCIL && !per &&
+        (prec == PB_F64 ? resident_fits<double>(L, 0, false) && resident_chosen<double>(L)
+                        : prec == PB_F32 && resident_fits<float>(L, 0, false) && resident_chosen<float>(L));
     pb_status e = prepare(L, h, eps_x, eps_y, eps_z, kappa2, rhs, x, opts->warm_start ? 1 : 0, per, w, prec, st,
                           &singular, later);
     if (e != PB_OK) return e;
@@ -351,6 +351,7 @@ pb_status solve_impl(int32_t nx, int32_t ny, int32_t nz, double h, const double*
     const int* refuse = later ? (const int*)(w.small + kFlagsAt) : nullptr;
     SolveResult r{};
     r.untimed = untimed ? 1 : 0;
+    r.refuse = refuse;
     int total_iters = 0, outer = 0, launches = 0, coded_launches = 0;
     double ksec = 0.0;
     double relres_recur = 0.0;

@@ -239,7 +239,6 @@ __global__ void k_add_correction(double* __restrict__ x, const float* __restrict
 
 // Padded (T) -> caller's unpadded FP64 array.
 // refuse: nothing is written when *refuse has one of the bits of a refused system.
-constexpr int kRefused = FLAG_BAD_COEF | FLAG_BAD_RHS | FLAG_BAD_GUESS;
 template <typename T>
 __global__ void k_unpad(const T* __restrict__ xp, int nx, int ny, int nz, int64_t sp,
                         double* __restrict__ out, const int* __restrict__ refuse) {

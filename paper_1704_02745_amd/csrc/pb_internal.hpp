@@ -104,6 +104,7 @@ enum PrepFlags {
     FLAG_BAD_GUESS = 4,   // NaN / Inf in the initial guess
     FLAG_HAS_SALT = 8,    // some node has kbar^2 > 0 (the periodic operator is then definite)
 };
+constexpr int kRefused = FLAG_BAD_COEF | FLAG_BAD_RHS | FLAG_BAD_GUESS;   // bits of a refused system
 
 // ---------------------------------------------------------------- helpers
 

@@ -60,6 +60,7 @@ struct RArgs {
     const uint32_t* cw;
     const float* ctab;
     const int* fit;
+    const int* refuse;    // given (a solve of its own): nothing to do when it holds a bit of kRefused
     // a solve in chunks (KEEPS): r, q and p between launches, the iterations of this
     // launch, and whether it goes on from them
     T *keep_r, *keep_q, *keep_p;
@@ -247,6 +248,7 @@ __device__ void resident_problem(const A& a, int w, unsigned char* lds_raw) {
     constexpr bool XM = x_in_memory<T>(NZ, CP);
     constexpr bool KEEP = E == 8 || NZ <= (LL ? 17 : 12);
     constexpr int SZ = NZ | 1;   // LDS stride of a column
+    if (!MANY && a.refuse && (*a.refuse & kRefused)) return;
     const int G = a.nxt * a.nyt * a.nzc;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int64_t sp = a.sp;

@@ -244,6 +244,7 @@ pb_status resident_solve(const Layout& L, const SolveBufs<T>& s, SyncState* sync
     a.cw = cw;
     a.ctab = ctab;
     a.xs = s.p0;
+    a.refuse = res ? res->refuse : nullptr;
     if (s.warm) {
         T* r0 = x_in_memory<T>(p.nz, cw != nullptr) ? s.r2 : s.q2;   // q2 holds the code words
         if (launch_resident_start<T>(L, s.op, s.b, s.x, r0, periodic, st) != PB_OK) return PB_ERR_HIP;

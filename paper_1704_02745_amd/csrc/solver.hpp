@@ -122,6 +122,8 @@ struct SolveResult {
     int coded;               // fused form: 1 or 2 when it read code words (SolveBufs::codes_valid)
     const float* ctab;       // and the dictionary it used (device)
     int untimed;             // input: 1 = record no HIP events (kernel_seconds stays 0)
+    const int* refuse;       // input (device, nullable): the preparation's flags, not read back yet; a
+                             // solve of its own in the resident form does nothing on a refused system
     // multigrid: set by a solve whose hierarchy (and level 0's code words) a further
     // one on the same operator and workspace can take over
     int mg_built, mg_coded;
