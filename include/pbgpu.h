@@ -418,8 +418,13 @@ pb_status pb_solve_batch(int32_t nprob, const pb_problem* probs, int32_t precisi
  * setting a problem's tiling, and so its result, depends on its shape alone.
  * pb_batch_set_zchunk takes 1..4096 (PB_ERR_ARG otherwise).
  *
- * pb_batch_autotune times the batch kernel on the given problems for each
- * candidate z-chunk (16, 24, 32, 48, 64). Every problem is capped at
+ * It matters to problems whose state does not fit the registers and LDS of the
+ * device (above about 171 nodes an edge in FP32, 100 in FP64); the others do not
+ * run in z-chunks.
+ *
+ * pb_batch_autotune times the streaming batch kernel on the given problems that
+ * run in it (on all of them if none does) for each candidate z-chunk (16, 24,
+ * 32, 48, 64). Every problem is capped at
  * iters_per_trial iterations, and the problems' x arrays are read (warm start)
  * but not written. The fastest candidate becomes the device's setting;
  * best_zchunk and best_seconds (host, nullable) receive it and its trial's

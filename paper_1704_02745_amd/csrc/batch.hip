@@ -389,6 +389,16 @@ pb_status launch_solves(const Plan<T>& P, int grid, hipStream_t st, bool coopera
     return e;
 }
 
+// A batch holds at most as many problems as the streaming form has co-resident
+// workgroups, whatever form its problems run in.
+template <typename T>
+pb_status check_count(const Plan<T>& P) {
+    const int most = batch_capacity<T>(P.str_lds);
+    if (most >= P.nprob) return PB_OK;
+    set_error("batch: %d problems but only %d co-resident workgroups; split the batch", P.nprob, most);
+    return PB_ERR_ARG;
+}
+
 // Settle the forms (choose_forms, from P.words) and upload the per-problem kernel
 // arguments, the workgroup offsets and the job lists. coded: the streaming
 // launch's kernel; grid: its workgroups.
@@ -396,12 +406,7 @@ template <typename T>
 pb_status upload_table(Plan<T>& P, const pb_problem* probs, int& grid, int coded, hipStream_t st) {
     grid = 0;
     choose_forms(P);
-    // a batch holds at most as many problems as the streaming form has
-    // co-resident workgroups, whatever form its problems run in
-    if (const int most = batch_capacity<T>(P.str_lds); most < P.nprob) {
-        set_error("batch: %d problems but only %d co-resident workgroups; split the batch", P.nprob, most);
-        return PB_ERR_ARG;
-    }
+    if (const pb_status e = check_count(P); e != PB_OK) return e;
     auto share = [&](const std::vector<int>& of, int cap) {
         std::vector<Layout> L;
         std::vector<Tiling> t;
@@ -569,15 +574,21 @@ pb_status solve_batch_impl(int nprob, const pb_problem* probs, void* ws, size_t 
 // z-chunks the batch autotuner times.
 constexpr int kBatchZCandidates[] = {16, 24, 32, 48, 64};
 
-// Time the batch kernel for each candidate z-chunk on these problems, each
-// capped at `iters` iterations (state cleared and prepared as for a solve,
-// but no hand-back: the problems' x arrays are not written), and make the
-// fastest the device's batch z-chunk.
+// Time the streaming batch kernel for each candidate z-chunk, each problem capped
+// at `iters` iterations (state cleared and prepared as for a solve, but no
+// hand-back: the problems' x arrays are not written), and make the fastest the
+// device's batch z-chunk. The problems that stream are timed (the z-chunk is of no
+// effect on the others); all of them where none does.
 template <typename T>
 pb_status batch_autotune_impl(int nprob, const pb_problem* probs, int iters, void* ws, size_t wsb, hipStream_t st,
                               int* best_z, double* best_seconds) {
-    std::vector<pb_problem> trial(probs, probs + nprob);
+    std::vector<pb_problem> trial;
+    for (int i = 0; i < nprob; ++i)
+        if (resident_batch_plan<T>(make_layout(probs[i].nx, probs[i].ny, probs[i].nz)).grid == 0)
+            trial.push_back(probs[i]);
+    if (trial.empty()) trial.assign(probs, probs + nprob);
     for (auto& p : trial) p.maxiter = iters;
+    const int ntrial = (int)trial.size();
     hipEvent_t ev[2];
     PB_HIP(hipEventCreate(&ev[0]));
     PB_HIP(hipEventCreate(&ev[1]));
@@ -585,37 +596,40 @@ pb_status batch_autotune_impl(int nprob, const pb_problem* probs, int iters, voi
     int bz = 0;
     pb_status e = PB_OK;
     for (int z : kBatchZCandidates) {
-        Plan<T> P;
-        if (!carve_batch<T>(ws, nprob, trial.data(), P, z, false)) { e = PB_ERR_ARG; break; }
-        if (wsb < P.bytes) {
-            set_error("pb_batch_autotune: workspace of %zu bytes, %zu needed", wsb, P.bytes);
+        // (the whole batch as its solve would be checked)
+        Plan<T> all, P;
+        if (!carve_batch<T>(nullptr, nprob, probs, all, z, false)) { e = PB_ERR_ARG; break; }
+        if (wsb < all.bytes) {
+            set_error("pb_batch_autotune: workspace of %zu bytes, %zu needed", wsb, all.bytes);
             e = PB_ERR_NOMEM;
             break;
         }
+        if ((e = check_count(all)) != PB_OK) break;
+        if (!carve_batch<T>(ws, ntrial, trial.data(), P, z, false)) { e = PB_ERR_ARG; break; }
         int grid = 0;
         if ((e = upload_table<T>(P, trial.data(), grid, 0, st)) != PB_OK) break;
-        if ((e = launch_fill<int>((int*)P.rec, (int64_t)(sizeof(ProbRec) / sizeof(int)) * nprob, 0, st)) != PB_OK) break;
-        if ((e = launch_fill<int>((int*)P.sync, (int64_t)(sizeof(SyncState) / sizeof(int)) * nprob, 0, st)) != PB_OK) break;
+        if ((e = launch_fill<int>((int*)P.rec, (int64_t)(sizeof(ProbRec) / sizeof(int)) * ntrial, 0, st)) != PB_OK) break;
+        if ((e = launch_fill<int>((int*)P.sync, (int64_t)(sizeof(SyncState) / sizeof(int)) * ntrial, 0, st)) != PB_OK) break;
         if ((e = enqueue_prepare<T>(P, trial.data(), st)) != PB_OK) break;
         // solves run coded where they can: time the kernel they will run (the
         // per-problem checked form, which needs no read-back here)
         int coded = 0;
         if constexpr (sizeof(T) == sizeof(float)) {
             bool can = coded_coefficients() != 0 && batch_capacity<T>(P.lds + kCodedLdsBytes, 2) >= grid;
-            for (int i = 0; i < nprob && can; ++i) can = coded_layout_ok(P.L[i]);
+            for (int i = 0; i < ntrial && can; ++i) can = coded_layout_ok(P.L[i]);
             if (can) {
-                for (int i = 0; i < nprob && e == PB_OK; ++i) {
+                for (int i = 0; i < ntrial && e == PB_OK; ++i) {
                     e = enqueue_dictionary(P.s[i].op, P.L[i].npad, (void*)P.s[i].q, P.fit + i, st);
                     if (e == PB_OK) e = enqueue_encode(P.s[i].op, P.L[i].npad, P.s[i].q, (uint32_t*)P.s[i].q2, st,
                                                        P.fit + i);
                 }
-                P.words.assign(nprob, 2);
+                P.words.assign(ntrial, 2);
                 if (e != PB_OK || (e = fill_table<T>(P, trial.data(), st)) != PB_OK) break;
                 coded = 2;
             }
         }
         if (hipEventRecord(ev[0], st) != hipSuccess) { e = PB_ERR_HIP; break; }
-        if ((e = batch_launch<T>(P.table, P.first, nprob, grid, coded ? P.lds + kCodedLdsBytes : P.lds, st, true,
+        if ((e = batch_launch<T>(P.table, P.first, ntrial, grid, coded ? P.lds + kCodedLdsBytes : P.lds, st, true,
                                  coded)) != PB_OK)
             break;
         if (hipEventRecord(ev[1], st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess) { e = PB_ERR_HIP; break; }

@@ -82,3 +82,21 @@ def test_recorded_mix_takes_no_longer(pb):
         g.close()
     print(f"direct {min(direct)*1e3:.2f} ms, recorded {min(recorded)*1e3:.2f} ms", flush=True)
     assert min(recorded) <= 1.25 * min(direct)
+
+
+def test_autotune_times_what_streams(pb):
+    """Of a batch with one problem that streams, that one is timed, as it is alone (1.3: two timings); what
+    the whole batch is refused for stays refused."""
+    big = molecule_system(pb, (201, 193, 189), 200, 60)
+    systems = [molecule_system(pb, (117, 113, 121), 100, 70 + k) for k in range(12)] + [big]
+    z0 = pb.get_batch_zchunk()
+    try:
+        alone = min(pb.batch_autotune([big], precision="f32", iters_per_trial=20)["seconds"] for _ in range(2))
+        mixed = min(pb.batch_autotune(systems, precision="f32", iters_per_trial=20)["seconds"] for _ in range(2))
+        print(f"autotune: alone {alone*1e3:.2f} ms, in the batch {mixed*1e3:.2f} ms", flush=True)
+        assert mixed <= 1.3 * alone
+        small = molecule_system(pb, (9, 8, 7), 2, 1)
+        with pytest.raises(pb.PBError):
+            pb.batch_autotune([small] * 5000 + [big], precision="f32", iters_per_trial=1)
+    finally:
+        pb.set_batch_zchunk(z0)
