@@ -64,6 +64,19 @@ def test_streaming_batch(pb, prec):
         x, i = pb.solve_batch([s], tol=tol, precision=prec)
         assert i[0]["coded_launches"] == (1 if prec == "f32" and CASES[prec][k][2] else 0)
         assert torch.equal(x[0], xs[k]) and i[0]["iters"] == infos[k]["iters"], k
+    # another z-chunk: other tiles, the same problem, and alone as in a mix
+    z0 = pb.get_batch_zchunk()
+    try:
+        pb.set_batch_zchunk(7)
+        xz, iz = pb.solve_batch(systems, tol=tol, precision=prec)
+        for k, s in enumerate(systems):
+            x, i = pb.solve_batch([s], tol=tol, precision=prec)
+            assert torch.equal(x[0], xz[k]) and i[0]["iters"] == iz[k]["iters"], k
+            assert abs(iz[k]["iters"] - infos[k]["iters"]) <= 1
+            if iz[k]["iters"] == infos[k]["iters"]:
+                assert float((xz[k] - xs[k]).abs().max()) <= bound * float(xs[k].abs().max())
+    finally:
+        pb.set_batch_zchunk(z0)
     warm = [0.9 * x for x in xs]
     xw, iw = pb.solve_batch(systems, tol=tol, precision=prec, x0s=warm)
     for i, j in zip(iw, infos):
