@@ -78,9 +78,10 @@ static_assert(kMaxResidentGroups <= kSlotGroup * kSlotGroup, "two rounds of poll
 // One round costs a latency less, two rounds a fraction of the traffic: with 99
 // workgroups (65 x 57 x 61) 4.24 us a pass against 4.66, with 143 (81 x 77 x 85) 5.27
 // against 5.04, with 200 (97^3) 6.30 against 5.51, with 210 (97 x 105 x 89 FP64) 7.61
-// against 6.43, with 252 (141^3) 12.2 against 10.4. Where the passes are long the
-// workgroups come to the barrier one by one and the traffic is hidden: 19 planes
-// 6.96 against 7.0 to 7.3 (129^3), 43 planes 15.1 against 15.6 (161^3). The kernels of
+// against 6.43, with 252 (24 planes, 141^3) 12.2 against 10.4, with 225 and 250 (32
+// planes, 145^3 and 159^3) 14.1 against 13.1 and 14.3 against 12.7. Two kernels are
+// slower with two rounds, those whose registers are full (256, and some spilled): 19
+// planes 6.96 against 7.0 to 7.3 (129^3), 43 planes 15.1 against 15.6 (161^3). Those of
 // up to 6 planes, whose plans have fewer workgroups, go without the choice (0.09 us
 // a pass).
 //
@@ -91,7 +92,7 @@ static_assert(kMaxResidentGroups <= kSlotGroup * kSlotGroup, "two rounds of poll
 // against 6.8).
 __host__ __device__ constexpr int slot_groups(int nzb, int G, bool many) {
     if (many) return G > kSlotGroup ? (G + kSlotGroup - 1) / kSlotGroup : 0;
-    return nzb > 6 && (nzb <= 14 || nzb == 24) && G > 128 ? (G + kSlotGroup - 1) / kSlotGroup : 0;
+    return nzb > 6 && (nzb <= 14 || nzb == 24 || nzb == 32) && G > 128 ? (G + kSlotGroup - 1) / kSlotGroup : 0;
 }
 // Barrier words of a problem, both parities.
 __host__ __device__ constexpr int slot_words(int nzb, int G, bool many) {
