@@ -18,8 +18,8 @@
 
 namespace pb {
 
-// Problems in order of decreasing expected duration (wider ones first among
-// equals), each on the workgroups that are free first.
+// Problems in order of decreasing width (the longer first among equals), each on
+// the workgroups that are free first.
 void resident_schedule(const std::vector<int>& grid, const std::vector<double>& cost, int groups,
                        std::vector<int>& off, std::vector<int>& jobs) {
     const int n = (int)grid.size();

@@ -199,14 +199,13 @@ __device__ __forceinline__ void agent_store(Rsrc r, uint32_t off, double v) {
 // two y-faces of tx * NZ, two z-faces of one value per thread.
 __host__ __device__ constexpr int face_len(int bs, int nzb, int tx, int ty) { return 2 * (tx + ty) * nzb + 2 * bs; }
 
-// LDS of one workgroup, in bytes: the reduction scratch, p by columns (the NZ
-// values of a column together, at an odd stride, so that a lane's accesses
-// are one address plus constants and the lanes fall into different banks) over
-// the tile and its halo, and r and 1/d of the halo.
 // Whether the couplings to the lower x and y neighbours sit in LDS (each thread
-// its own) instead of registers: from 17 planes of FP32 or 9 of FP64 on the
-// rest of the state fills the 256 registers of a thread and they would spill
-// (129^3, 19 planes: 13.1 us per iteration with the spills, 7.5 without).
+// its own) instead of registers: from 15 planes of FP32 or 7 of FP64 on, where the
+// rest of the state fills the 256 registers of a thread and they would spill (129^3,
+// 19 planes: 13.1 us per iteration with the spills, 7.5 without). Beside the line it
+// matters little: 8 planes of FP64 (97 x 105 x 89) 6.50 us in LDS and 6.52 in registers,
+// 9 (101 x 99 x 97) 6.94 and 6.86, 14 of FP32 (113 x 111 x 112, 117 x 117 x 113) 6.22 and
+// 6.45 in LDS and 6.27 and 6.79 in registers.
 template <typename T>
 __host__ __device__ constexpr bool lower_in_lds(int bs, int nzb) { return nzb > (sizeof(T) == 4 ? 14 : 6); }
 // Whether x goes to memory by brick instead of registers (each thread reads and
@@ -217,6 +216,10 @@ template <typename T>
 __host__ __device__ constexpr bool x_in_memory(int nzb, bool compact) {
     return compact || (sizeof(T) == 8 && nzb > 6);
 }
+// LDS of one workgroup, in bytes: the reduction scratch, p by columns (the NZ
+// values of a column together, at an odd stride, so that a lane's accesses
+// are one address plus constants and the lanes fall into different banks) over
+// the tile and its halo, and r and 1/d of the halo.
 template <typename T>
 __host__ __device__ constexpr size_t resident_lds_bytes(int bs, int nzb, int tx, int ty, bool compact) {
     return (!compact && lower_in_lds<T>(bs, nzb) ? sizeof(T) * 2 * (size_t)bs * nzb : 0) +
@@ -832,7 +835,9 @@ constexpr int kCompactFrom = 24;   // planes per brick from which a kernel is th
 // Planes per brick of a batch: the largest that leave the registers unspilled,
 // so that a problem takes few workgroups and the barrier's latency is shared by
 // many nodes. One number per form: a kernel that chose between four inlined
-// forms spilled, and gave wrong potentials in the last bricks of one of them.
+// forms spilled, and gave wrong potentials in the last bricks of one of them (the
+// cause is not known; nothing here was found to depend on the number of forms, and
+// partial last bricks are held to the streaming form's potentials by tests).
 template <typename T>
 constexpr int batch_planes(bool compact) { return sizeof(T) == 8 ? 8 : (compact ? 43 : 19); }
 
@@ -853,8 +858,8 @@ __global__ __launch_bounds__(512) void k_resident_batch(const RArgs<T>* __restri
         const int2 job = jobs[n];
         // the arguments through the constant address space: known uniform, and read
         // again by scalar loads where a register is short (as copies in registers
-        // they made the server's kernels spill 28 and 125 vector registers, 16 and 83
-        // like this)
+        // they made the server's kernels spill 28 and 125 vector registers, full and
+        // compact, 6 and 77 like this; the batch's 3 and 6)
         const ConstArgs<T>* a = (const ConstArgs<T>*)(uintptr_t)(probs + __builtin_amdgcn_readfirstlane(job.x));
         resident_problem<T, 512, batch_planes<T>(CP), false, CP, true, KEEPS>(*a, __builtin_amdgcn_readfirstlane(job.y),
                                                                         lds_raw);

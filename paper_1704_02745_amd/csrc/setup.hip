@@ -691,7 +691,7 @@ __global__ __launch_bounds__(kDhBlock) void k_setup_small(
 //
 // The points bound it (1.3 ms of 1.63 at 257^3): the same FP64 issue, a sixth of
 // the terms. Measured: the whole preparation of 257^3 with 20,000 atoms 11.7 -> 2.4 ms,
-// 193 x 177 x 161 with 8,000 2.5 -> 1.0 ms; against the exact sum the faces are
+// 193 x 177 x 161 with 8,000 2.26 -> 0.87 ms; against the exact sum the faces are
 // nearer than the direct sum's (largest error 1.8e-15 of the largest value, 1.2e-14
 // before).
 constexpr int kDhP = 32;                   // Chebyshev points per tile and direction
