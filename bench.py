@@ -13,8 +13,8 @@ whichever pass form runs (the floor of any schedule that keeps the operator
 as four FP32 arrays), so it scales with iterations per second: an effective
 rate. The roofline block reports the fused kernel alone: the same bytes over
 its own summed duration (HIP events on the solve stream, recorded by the
-library), beside the bytes the running form itself moves (28 B with coded
-coefficients, the default when the operator fits its dictionary:
+library), beside the bytes the running form itself moves (24.5 B on average with
+coded coefficients, the default when the operator fits its dictionary:
 form_achieved, form_frac), the counted HBM traffic (when the committed
 counter summary matches the kernel source) and three streaming ceilings
 measured in the same run: the runtime's device copy and the library's own
@@ -47,11 +47,14 @@ PEAK_GBS = 8000.0
 # skips (8 B). The pass forms themselves move 48 B (form 0, stores A.p),
 # 40 B (form 1, recomputes it) or 28 B (form 1 with coded coefficients: the
 # operator read as one 4-byte word of dictionary codes per unknown) per
-# unknown per iteration; that figure is reported beside the metric.
+# unknown per iteration. Form 1 reads and writes x (8 B) in every second pass
+# where beta is at least 0.8, which leaves it out of some 44% of the passes of
+# the refined 257^3 solve: 3.5 B less on average. That figure is reported beside
+# the metric.
 ITER_BYTES = 40
 INIT_BYTES = 12 - 8 + 12
-PASS_BYTES_BY_SCHEME = {0: 48, 1: 40}
-CODED_PASS_BYTES = 28
+PASS_BYTES_BY_SCHEME = {0: 48, 1: 36.5}
+CODED_PASS_BYTES = 24.5
 
 
 def form_bytes(scheme: int, coded: bool):

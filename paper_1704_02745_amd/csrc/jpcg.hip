@@ -39,8 +39,8 @@
 // The 40-byte form and its coded form take x every second pass where they can:
 // with p_{l-1} = z + beta p_{l-2}, the pass that has p_{l-1} and z = r/d at hand
 // also has p_{l-2} = (p_{l-1} - z) / beta, so a pass may leave x alone and the next
-// adds both steps, 8 bytes per node in two passes less (36 and 24 bytes on
-// average; 257^3 coded, default tiling, 123 -> 117 us a pass). beta must be at
+// adds both steps, 8 bytes per node in two passes less (about 36.5 and
+// 24.5 bytes on average; 257^3 coded, default tiling, 123.3 -> 118.6 us a pass). beta must be at
 // least kDeferBeta: the division enlarges the rounding of p_{l-1} in one step's
 // share of x by 1/beta, against one rounding of x itself that is saved. From 0.8 on
 // the rounding error of x (root mean square against 64 bits, FP32, 33^3 to
