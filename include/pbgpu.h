@@ -397,12 +397,12 @@ typedef struct {
 size_t pb_batch_workspace_bytes(int32_t nprob, const pb_problem* probs, int32_t precision);
 
 /*
- * pb_solve_batch: solve all problems (section 2.2 with M = diag(A)) in ONE
- * persistent launch. Workgroups are shared out in proportion to each
- * problem's expected work; each problem synchronises only its own
- * workgroups, and its tiling and reduction order depend on its shape and the
- * device's batch z-chunk alone, so a problem's result is bitwise identical
- * alone and in any mix.
+ * pb_solve_batch: solve all problems (section 2.2 with M = diag(A)) in one
+ * persistent launch per kernel form (resident full, resident compact,
+ * streaming). Each problem synchronises only its own workgroups, and its form,
+ * tiling and reduction order depend on its shape, on its operator (whether that
+ * fits a dictionary, for the compact form) and on the device's batch z-chunk
+ * alone, so a problem's result is bitwise identical alone and in any mix.
  * precision: PB_F32 or PB_F64. infos (host, nprob entries, nullable) receive
  * per-problem iterations, status and FP64 true residuals; kernel_seconds is
  * the whole batch's device time. Returns PB_OK, PB_NOT_CONVERGED if any
@@ -440,7 +440,7 @@ pb_status pb_batch_autotune(int32_t nprob, const pb_problem* probs, int32_t prec
 
 /*
  * The same batch recorded once in a HIP graph (preparation, the persistent
- * solve and the hand-back), replayed by pb_batch_graph_launch. Array
+ * solves and the hand-back), replayed by pb_batch_graph_launch. Array
  * pointers and shapes are fixed at creation; their contents may change
  * between launches (e.g. new snapshots written into the same buffers).
  * pb_batch_graph_results synchronises `stream` and reads per-problem infos.

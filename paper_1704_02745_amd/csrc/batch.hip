@@ -1,12 +1,15 @@
 // Batched solves: many independent systems of uneven size in one persistent
-// launch (and the same work recorded once in a HIP graph for replay).
+// launch per kernel form (and the same work recorded once in a HIP graph for
+// replay).
 //
-// Each problem is prepared into its own padded operator and state, gets a
-// tiling that depends on its shape only, and a share of the co-resident
-// workgroups proportional to its expected work (nodes x max edge, since the
-// Jacobi-CG iteration count grows with the grid edge). Workgroups of one
-// problem synchronise only with each other, so problems never wait for one
-// another, and every problem's result is bitwise the same alone or in any mix.
+// Each problem is prepared into its own padded operator and state and runs in the
+// resident form where its state fits the device (bricks that depend on its shape
+// only, workgroups working through job lists), else in the streaming one: a tiling
+// that depends on its shape only, and a share of the co-resident workgroups
+// proportional to its expected work (nodes x max edge, since the Jacobi-CG
+// iteration count grows with the grid edge). Workgroups of one problem
+// synchronise only with each other, and every problem's result is bitwise the same
+// alone or in any mix.
 #include "solver.hpp"
 
 #include <algorithm>
