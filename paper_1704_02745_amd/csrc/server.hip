@@ -252,9 +252,8 @@ struct Server {
     // the resident launches' job lists (resident_schedule): pinned host memory that the
     // kernels read (two words a workgroup and a pair a job, once a launch), so that the
     // arena holds requests. A step waits for its launches, so the next may write them.
-    int* job_off = nullptr;
-    int* jobs = nullptr;
-    size_t jobs_cap = 0;          // pairs
+    int* job_off = nullptr;       // of either form
+    int* jobs = nullptr;          // kServeGroups pairs a slot
     bool lists_busy = false;      // a step ended (in an error) without that wait
     int* first = nullptr;         // device: workgroup offsets
     StateDigest* digests = nullptr;   // device: each running request's scalars after a launch
@@ -275,20 +274,6 @@ struct Server {
     std::vector<StateDigest> host_digests;
     std::vector<SlotRec> host_recs;
     std::vector<int> free_recs;   // unused record indices
-
-    // the lists free to be written, with room for `pairs` jobs
-    pb_status open_lists(size_t pairs) {
-        if (lists_busy) PB_HIP(hipDeviceSynchronize());
-        lists_busy = true;
-        if (pairs <= jobs_cap) return PB_OK;
-        const size_t cap = std::max(pairs, 2 * jobs_cap);
-        if (jobs) PB_HIP(hipHostFree(jobs));
-        jobs = nullptr;
-        jobs_cap = 0;
-        PB_HIP(hipHostMalloc((void**)&jobs, 2 * sizeof(int) * cap, hipHostMallocDefault));
-        jobs_cap = cap;
-        return PB_OK;
-    }
 
     // one copy of every record, on the stream (the caller synchronises)
     pb_status read_recs(hipStream_t st) {
@@ -391,7 +376,10 @@ extern "C" pb_status pb_server_create(void* arena, size_t arena_bytes, int32_t m
     S->free_list.push_back({S->reserved, arena_bytes - S->reserved});
     S->host_table.resize(tb);
     S->host_first.resize(max_slots + 1);
-    PB_HIP(hipHostMalloc((void**)&S->job_off, 2 * sizeof(int) * (kServeGroups + 1), hipHostMallocDefault));
+    const size_t offs = 2 * (kServeGroups + 1);
+    PB_HIP(hipHostMalloc((void**)&S->job_off, sizeof(int) * (offs + 2 * kServeGroups * (size_t)max_slots),
+                         hipHostMallocDefault));
+    S->jobs = S->job_off + offs;
     PB_HIP(hipEventCreate(&S->ev[0]));
     PB_HIP(hipEventCreate(&S->ev[1]));
     PB_HIP(hipEventCreateWithFlags(&S->ev_in, hipEventDisableTiming));
@@ -683,7 +671,8 @@ extern "C" pb_status pb_server_step(pb_server* S, int32_t chunk, void* stream, i
         }
         if (nres > 0) {
             job0[1] = jobs[0].size();
-            if ((e = S->open_lists((jobs[0].size() + jobs[1].size()) / 2)) != PB_OK) return e;
+            if (S->lists_busy) PB_HIP(hipDeviceSynchronize());
+            S->lists_busy = true;
             for (int c = 0; c < 2; ++c) {
                 std::copy(joff[c].begin(), joff[c].end(), S->job_off + c * (kServeGroups + 1));
                 std::copy(jobs[c].begin(), jobs[c].end(), S->jobs + job0[c]);
@@ -860,7 +849,6 @@ extern "C" void pb_server_destroy(pb_server* S) {
     if (S->ev[1]) (void)hipEventDestroy(S->ev[1]);
     if (S->ev_in) (void)hipEventDestroy(S->ev_in);
     if (S->adm) (void)hipStreamDestroy(S->adm);
-    if (S->jobs) (void)hipHostFree(S->jobs);
     if (S->job_off) (void)hipHostFree(S->job_off);
     delete S;
 }
