@@ -1116,12 +1116,23 @@ __global__ void k_energy_atoms(const double* __restrict__ xyz, const double* __r
     qphi[a] = charge[a] * phi;
 }
 
-// Fixed-order sum of n doubles by one workgroup of 1024 threads.
+// Fixed-order sum of n doubles by one workgroup of 1024 threads. Each load's latency
+// bounds it where the adds wait for their own load: 16 are on their way at a time
+// (201^3, whose arrays have left the last-level cache once all fields are written: 2.7
+// ms with one at a time, 1.1 now).
 __global__ __launch_bounds__(1024) void k_sum_fixed(const double* __restrict__ v, int64_t n,
                                                     double* __restrict__ out) {
     __shared__ double s[1024];
     double acc = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += 1024) acc += v[i];
+    int64_t i = threadIdx.x;
+    for (; i + 15 * 1024 < n; i += 16 * 1024) {
+        double x[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) x[k] = v[i + k * 1024];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) acc += x[k];
+    }
+    for (; i < n; i += 1024) acc += v[i];
     s[threadIdx.x] = acc;
     __syncthreads();
     for (int w = 512; w > 0; w >>= 1) {
