@@ -665,6 +665,17 @@ __global__ __launch_bounds__(kDhBlock) void k_setup_small(
     else if (block <= natoms) classify_atom(block - 1, xyz, radius, nx, ny, nz, h, ox, oy, oz, per, mask);
     else dh_direct_block(block - 1 - natoms, xyz, charge, natoms, nx, ny, nz, h, ox, oy, oz, kd, eout, ghost, nghost);
 }
+// Whether it is the faster form, a direct boundary sum provided: the keys fit the
+// LDS, and its one workgroup, whose threads sum the charges of up to eight nodes one
+// after another, is done with them soon. Where many share a node it is not (256 atoms
+// on 7^3 nodes: 237 us against 191; 200 on 7^3, 128 on 5^3: equal), and in a
+// periodic box, which has no boundary sum beside it, not with many keys on few
+// nodes (256 atoms, 12^3: 173 us against 152, 25^3: 156 against 152, 33^3: 148 against
+// 164; 128 atoms, 9^3: 132 against 126, 12^3: equal, 20^3: 116 against 126).
+bool setup_in_one(int64_t nkeys, int64_t natoms, int64_t nn, bool per) {
+    const int64_t per_atom = !per || nkeys <= 512 ? 2 : (nkeys <= 1024 ? 16 : 128);   // nodes, at least
+    return nkeys <= kSortChunk && per_atom * natoms <= nn;
+}
 
 // ---- the same sum with interpolated far fields
 //
@@ -1257,8 +1268,8 @@ pb_status setup_enqueue(const pb_grid* g, int64_t natoms, const double* xyz, con
 
     const int64_t P = next_pow2(std::max<int64_t>(2, 8 * natoms));
     const double kd = std::sqrt(kappa_d2);
-    // one launch where the keys fit a workgroup's LDS and the boundary sum is direct
-    const bool small = P <= kSortChunk && (per || dh_direct(dh_plan(nx, ny, nz, natoms, h, ox, oy, oz, kd), natoms));
+    const bool small = setup_in_one(P, natoms, nn, per) &&
+                       (per || dh_direct(dh_plan(nx, ny, nz, natoms, h, ox, oy, oz, kd), natoms));
     hipLaunchKernelGGL(k_setup_clear, dim3(blocks_for(std::max(nmask / 8, nn), 256)), dim3(256), 0, st, w.flags, m,
                        nmask, q, nn);
     if (small)
