@@ -1,5 +1,5 @@
 """Which boundary sum a molecule gets, told by the names of the kernels: interpolated where its terms are
-many, and with salt only where a face is wide enough for the second level of tiles."""
+many, but where no face is wide enough for the second level of tiles only without salt and on small grids."""
 import pytest
 import torch
 
@@ -17,6 +17,7 @@ def pb():
 # 78 x 78 nodes hold 1.49 times the points of four tiles, 79 x 78 are 1.504 times
 @pytest.mark.parametrize("dims,natoms,kd2,interpolated", [
     ((65, 65, 65), 4200, 0.0159051, False), ((65, 65, 65), 4200, 0.0, True), ((78, 78, 78), 2900, 0.0159051, False),
+    ((65, 65, 66), 4200, 0.0, False), ((78, 78, 78), 2900, 0.0, False), ((79, 78, 78), 2900, 0.0, True),
     ((79, 78, 78), 2900, 0.0159051, True), ((41, 41, 41), 10500, 0.0159051, False),
     ((97, 97, 97), 1600, 0.0159051, False)])
 def test_rule(pb, dims, natoms, kd2, interpolated):
