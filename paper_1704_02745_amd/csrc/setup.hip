@@ -1027,24 +1027,23 @@ DhPlan dh_plan(int nx, int ny, int nz, int64_t natoms, double h, double ox, doub
     P.chunks = (int)std::max<int64_t>(1, std::min<int64_t>(16, std::max(natoms / 512, std::min(natoms / 64, fill))));
     return P;
 }
-// The direct sum: nothing to interpolate, more tiles than a grid takes, or so few
+// The direct sum: more tiles than a grid takes, or so few
 // terms that they cost less than the four launches (97 x 105 x 89 with 900 atoms:
 // 120 us against 157; 129^3 with 2,000: 395 against 216). In a flat box fewer atoms
 // are far from its large faces (129 x 60 x 300 with 2,000 atoms, the whole
-// preparation: 639 us against 693). On faces too small for the second level (78
-// nodes a side) most atoms are near, and the few blocks of k_dh_near take as long as
-// the direct sum: with salt, whose terms take the longer (65^3 with 4,142 atoms in a
-// ball: 704 us direct, 759 interpolated; 78^3 with 2,876: 538 and 586), and without
-// it where the direct sum has more than about 100 blocks (70 x 75 x 78 with 3,532: 388 and
-// 409; 65^3 with 8,678: 702 and 683, 41^3 with 10,410: 820 and 796). 79^3 with
-// 2,804: 534 and 394, without salt 345 and 315.
+// preparation: 639 us against 693). And where all tiles are as large as their faces,
+// or halves of them: most atoms are then near, and the few blocks of k_dh_near take as
+// long as the direct sum (with salt and the atoms in an ellipsoid of three quarters of
+// the box: 65^3 with 4,142 704 us direct, 759 interpolated, 78^3 with 2,876 538 and 586,
+// 60 x 131 x 78 with 5,036 830 and 914; without salt 431 and 441, 348 and 362, 500 and 525;
+// with quarters of a face: 79^3 with 2,804 534 and 394, 131^3 with 1,019 390 and 290,
+// 131 x 131 x 60 with 3,486 822 and 671).
 bool dh_direct(const DhPlan& P, int64_t natoms) {
     const double flat = (double)std::max(P.nx, std::max(P.ny, P.nz)) / (double)std::min(P.nx, std::min(P.ny, P.nz));
     const double nghost = 2.0 * ((double)P.nx * P.ny + (double)P.nx * P.nz + (double)P.ny * P.nz);
-    bool second = false;
-    for (const DhFace& f : P.f) second = second || f.on2;
-    return P.tiles == 0 || P.tiles2 > 65535 || nghost * (double)natoms < 1e8 * flat ||
-           (!second && (P.kd > 0.0 || nghost > 100.0 * kDhBlock));
+    bool quarters = false;
+    for (const DhFace& f : P.f) quarters = quarters || f.on2 || (f.on1 && f.ku > 1 && f.kv > 1);
+    return !quarters || P.tiles2 > 65535 || nghost * (double)natoms < 1e8 * flat;
 }
 size_t dh_scratch_bytes(int nx, int ny, int nz, int64_t natoms) {
     const DhPlan P = dh_plan(nx, ny, nz, natoms, 0.0, 0.0, 0.0, 0.0, 0.0);

@@ -1,5 +1,5 @@
 """Which boundary sum a molecule gets, told by the names of the kernels: interpolated where its terms are
-many, but where no face is wide enough for the second level of tiles only without salt and on small grids."""
+many and some face has tiles of at most a quarter of it."""
 import pytest
 import torch
 
@@ -14,12 +14,14 @@ def pb():
     return m
 
 
-# 78 x 78 nodes hold 1.49 times the points of four tiles, 79 x 78 are 1.504 times
+# 78 x 78 nodes hold 1.49 times the points of four tiles, 79 x 78 are 1.504 times; 131 nodes are two tiles
 @pytest.mark.parametrize("dims,natoms,kd2,interpolated", [
-    ((65, 65, 65), 4200, 0.0159051, False), ((65, 65, 65), 4200, 0.0, True), ((78, 78, 78), 2900, 0.0159051, False),
-    ((65, 65, 66), 4200, 0.0, False), ((78, 78, 78), 2900, 0.0, False), ((79, 78, 78), 2900, 0.0, True),
-    ((79, 78, 78), 2900, 0.0159051, True), ((41, 41, 41), 10500, 0.0159051, False),
-    ((97, 97, 97), 1600, 0.0159051, False)])
+    ((41, 41, 41), 10500, 0.0159051, False), ((65, 65, 65), 4200, 0.0159051, False), ((65, 65, 65), 4200, 0.0, False),
+    ((78, 78, 78), 2900, 0.0159051, False), ((78, 78, 78), 2900, 0.0, False), ((79, 78, 78), 2900, 0.0159051, True),
+    ((79, 78, 78), 2900, 0.0, True), ((97, 97, 97), 1600, 0.0159051, False), ((97, 97, 97), 1900, 0.0159051, True),
+    ((130, 75, 75), 4000, 0.0159051, True), ((131, 75, 75), 4000, 0.0159051, False),
+    ((131, 131, 60), 3500, 0.0159051, True), ((131, 131, 131), 1100, 0.0159051, True),
+    ((156, 156, 156), 750, 0.0159051, True), ((156, 156, 156), 750, 0.0, True)])
 def test_rule(pb, dims, natoms, kd2, interpolated):
     gen = torch.Generator().manual_seed(1)
     half = torch.tensor([0.25 * (d - 1) for d in dims], dtype=torch.float64)
